@@ -41,12 +41,12 @@ void launch_rhs(const double* tx, const double* ty, int nx, int ny, const int* b
                 const double* f, const double* g, double h, double* b, hipStream_t s);
 
 // ---- preconditioner apply (arithmetic T, factor storage S) ------------------
-// Boxes are solved by lane groups of 16, 32 or 64 lanes (>= the widest box,
-// at most 64 cells wide); LDS per workgroup: box_lds_bytes() (all ones when a
-// single group exceeds 64 KB).  t, w: bytes of the arithmetic type T and of
+// A box (at most 64 cells wide) is solved by one lane group per end of its
+// factor; LDS per workgroup: box_lds_bytes() (all ones when a
+// single box is too large).  t, w: bytes of the arithmetic type T and of
 // the factor storage type S.
 size_t box_lds_bytes(int max_bx, int max_cells, size_t t, size_t w);
-// Lane groups per workgroup of the box kernels (the most that fit; a launch
+// Boxes per workgroup of the box kernels (the most that fit; a launch
 // may take fewer, groups_cap > 0, which changes no result).
 int box_groups(int max_bx, int max_cells, size_t t, size_t w);
 // Source-driven solves on the oversampled boxes (boxes[i]: hat-Omega_i with

@@ -116,17 +116,30 @@ struct Blk {
 __device__ __forceinline__ Blk hw_blk() { return Blk{(int)blockIdx.x, (int)gridDim.x}; }
 
 // ---- batched box solves ---------------------------------------------------
-// One lane group of GS lanes (GS = 16, 32 or 64 >= the box width bx, 64 / GS
-// boxes per wave) solves one cell box with the block LDL^T factor of its cell
-// rows.  Lane r owns cell column r of every row j:
-//   forward  u_j = D_j^-1 (b_j + T_j u_{j-1}),
-//   backward x_j = u_j + D_j^-1 (T_{j+1} x_{j+1}).
-// The blocks are symmetric and stored as half blocks (setup_jobs.h): lane r
-// loads the entries D(r, r + k), k = 0 .. NB / 2, of each block and fetches
-// D(r, r - k) = D(r - k, r) from the registers of lane r - k.  All exchange
-// between the lanes of a group is wave-local (no workgroup barrier): the
-// vector of a step goes through the group's slot of LDS, the mirrored
-// entries through cross-lane permutes.
+// A cell box is solved with the block LDL^T factor of its cell rows
+// (setup_jobs.h) by one lane group per end of the elimination: the factors in
+// FP64 are two-ended (the group of end 0 eliminates the rows below the middle
+// row h upward, the group of end 1 the rows above it downward, both solve row h,
+// and each substitutes back from it on its own side), the ones stored in FP32
+// one-ended (end 0 only, h the last row):
+//   end 0  u_j = D_j^-1 (b_j + T_j u_{j-1}),      x_j = u_j + D_j^-1 (T_{j+1} x_{j+1}),
+//   end 1  u_j = D_j^-1 (b_j + T_{j+1} u_{j+1}),  x_j = u_j + D_j^-1 (T_j x_{j-1}),
+//   middle x_h = D_h^-1 (b_h + T_h u_{h-1} + T_{h+1} u_{h+1}).
+// Two ends halve the chain of dependent row steps, which bounds the solve
+// wherever the boxes do not fill the GPU several times over.
+// A group is one wave: R row lanes, R = 64 for boxes wider than 32 columns, else
+// R = 32 with two lanes per row (halves), which halves
+// the instructions of a row step, the other thing a step waits for.  Lane r of
+// a half owns cell column r of every row.
+// The blocks are symmetric and stored as half blocks (setup_jobs.h): row r's
+// lanes load the entries D(r, r + k), k = 0 .. NB / 2, of each block and fetch
+// D(r, r - k) = D(r - k, r) from the registers of row r - k's lanes.  Exchange
+// inside a group is wave-local: the vector of a step goes through the group's
+// slot of LDS, the mirrored entries through cross-lane permutes.  The two groups
+// of a box meet at two workgroup barriers around the middle row.  The row of a
+// step, its addresses and its phase are the same in the whole wave and live in
+// scalar registers; lanes past the box's width repeat its last column (same
+// values to the same addresses), so that a step masks nothing.
 __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_wave_barrier(); }
 
 // a * b + c with one rounding, spelled out so that the one-RHS and the
@@ -169,17 +182,34 @@ __device__ __forceinline__ int opaque(int v) {
 }
 
 // Shape of the half blocks of a launch of column width NB: rows 0 .. H, the
-// first K0 of them single words, the others NH quads.
+// first K0 of them single words, the others NH quads; R row lanes per half and
+// HV halves per group (one wave).
 template <int NB>
 struct Half {
   static constexpr int H = NB / 2;
   static constexpr int K0 = half_k0(NB);
   static constexpr int NH = half_quads(NB);
+  static constexpr int R = NB <= 32 ? 32 : 64;
+  static constexpr int HV = 64 / R;
+  static constexpr int NT = (H + 3) / 4;          // steps of four mirrored entries
+  static constexpr int NM = HV == 2 ? 2 * NT : H;  // mirrored entries a lane fetches, at most
+  static_assert(HV == 1 || K0 == 1 || K0 == 3, "halves of a row: one or three single words");
 };
+// Ends of the factors of storage type S (groups per box).
+template <typename S>
+constexpr int box_ends() { return sizeof(S) == 8 ? 2 : 1; }
 
-// A lane's rows of one half block.  row(k) is entry D(r, r + k) of lane r
-// (k a constant after unrolling).
-template <typename S, int NB>
+// Two consecutive words of a factor block.
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+template <typename S> struct PairOf;
+template <> struct PairOf<float> { typedef f32x2 type; };
+template <> struct PairOf<double> { typedef f64x2 type; };
+
+// A lane's words of one half block.  One lane per row: all of them (row(k) is
+// entry D(r, r + k), k a constant after unrolling).  Two lanes per row: words 2 hf
+// and 2 hf + 1 of every quad, and the single words that half hf multiplies
+// (s[0]: word 2 hf) or passes on (s[1]: word 1).
+template <typename S, int NB, int HV = Half<NB>::HV>
 struct HalfRow {
   Quad<S> q[Half<NB>::NH];
   S h[Half<NB>::K0 > 0 ? Half<NB>::K0 : 1];
@@ -188,35 +218,59 @@ struct HalfRow {
     return k < K0 ? h[k] : q[(k - K0) >> 2][(k - K0) & 3];
   }
 };
-
-// The largest power of two <= d, between 2 and 8.  A sweep runs its step
-// count rounded up to a multiple of the depth, and powers of two divide the
-// common box heights (16, 20, 32, 36 rows), where a depth of 5 would run 20
-// steps for 16 rows.
-constexpr int pow2_depth(int d) { return d >= 8 ? 8 : d >= 4 ? 4 : 2; }
-
-// Blocks in flight per lane: as many as about 48 VGPRs of rows hold (more
-// would cost waves per SIMD: a sweep over 48, 64, 80 and 96 found 48 and 64
-// equal, 96 a third slower on 36-wide patches).
 template <typename S, int NB>
-constexpr int reg_depth() {
-  constexpr int per_block = half_rows(NB) * (int)sizeof(S) / 4;
-  return pow2_depth(48 / per_block);
+struct HalfRow<S, NB, 2> {
+  typename PairOf<S>::type p[Half<NB>::NH];
+  S s[2];
+};
+
+// VGPRs of a lane's words of one block.
+template <typename S, int NB>
+constexpr int block_regs() {
+  return (int)sizeof(S) / 4 *
+         (Half<NB>::HV == 1 ? half_rows(NB) : 2 * Half<NB>::NH + (Half<NB>::K0 == 3 ? 2 : 1));
 }
-
-// Lane rc's rows of one block of a box n cells wide: the quads at words
-// (q n + rc) 4, the single words at 4 NH n + k n + rc, so the group reads
-// contiguous pieces.
+// Blocks in flight per lane, 2 or 4: as many as about 64 VGPRs of rows hold (more
+// would cost waves per SIMD; 36-wide FP32 patches with four in flight instead
+// of two were a third slower).
+constexpr int sweep_depth(int vgprs, int per_block) { return vgprs / per_block >= 4 ? 4 : 2; }
 template <typename S, int NB>
-__device__ __forceinline__ void load_half(HalfRow<S, NB>& d, const S* __restrict__ blk, int n,
-                                          int rc) {
+constexpr int reg_depth() { return sweep_depth(64, block_regs<S, NB>()); }
+
+// Lane rc's words of one block of a box n cells wide: the quads at words
+// (q n + rc) 4, the single words at 4 NH n + k n + rc, so the group reads
+// contiguous pieces.  blk is the same in the whole wave; a lane's places in the
+// block are 32-bit offsets from it that do not change from block to block.
+template <typename S, int NB>
+struct BlockPlaces {
+  unsigned q, h, n;  // words of the lane's first quad piece and first single word; columns
+  __device__ BlockPlaces(int n_, int rc, int hf) : n(n_) {
+    q = 4 * rc + 2 * hf;
+    h = 4 * Half<NB>::NH * n_ + rc + (Half<NB>::K0 == 3 ? 2 * hf * n_ : 0);
+    if constexpr (Half<NB>::HV == 1) {
+      // one register each: the places are recomputed from these at every use
+      q = opaque(q);
+      h = opaque(h);
+    }
+  }
+};
+template <typename S, int NB>
+__device__ __forceinline__ void load_half(HalfRow<S, NB>& d, const S* __restrict__ blk,
+                                          const BlockPlaces<S, NB>& at, int rc) {
   constexpr int NH = Half<NB>::NH, K0 = Half<NB>::K0;
-  const S* p = blk + 4 * rc;
+  if constexpr (Half<NB>::HV == 1) {
 #pragma unroll
-  for (int q = 0; q < NH; ++q) load_quad(d.q[q], p + (long long)q * 4 * n);
-  const S* t = blk + (long long)4 * NH * n + rc;
+    for (int q = 0; q < NH; ++q) load_quad(d.q[q], blk + (size_t)(at.q + q * 4 * at.n));
 #pragma unroll
-  for (int k = 0; k < K0; ++k) d.h[k] = t[(long long)k * n];
+    for (int k = 0; k < K0; ++k) d.h[k] = blk[(size_t)(at.h + k * at.n)];
+  } else {
+    typedef typename PairOf<S>::type P;
+#pragma unroll
+    for (int q = 0; q < NH; ++q)
+      d.p[q] = *reinterpret_cast<const P*>(blk + (size_t)(at.q + q * 4 * at.n));
+    d.s[0] = blk[(size_t)at.h];
+    if constexpr (K0 == 3) d.s[1] = blk[(size_t)(4 * NH * at.n + rc + at.n)];
+  }
 }
 
 // Value v of the lane whose byte address (4 x lane index) is addr.
@@ -230,248 +284,417 @@ __device__ __forceinline__ double lane_fetch(int addr, double v) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// Byte addresses of the lanes that hold D(rc, rc - k), k = 1 .. H: lane
-// (rc - k) mod n of the group starting at lane g0 (lane g0 for k > n, where
-// every lane holds a zero row), one byte each, four to a word.
-template <int H>
-__device__ __forceinline__ void mirror_lanes(int (&src)[(H + 3) / 4], int g0, int rc, int n) {
-#pragma unroll
-  for (int w = 0; w < (H + 3) / 4; ++w) src[w] = 0;
-#pragma unroll
-  for (int k = 1; k <= H; ++k) {
+// Sum of v over the two halves of the wave (lanes l and l ^ 32), the same in both.
+__device__ __forceinline__ float sum_halves(float v) {
+  const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false,
+                                                  false);
+  return __uint_as_float(w[0]) + __uint_as_float(w[1]);
+}
+__device__ __forceinline__ double sum_halves(double v) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+  const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+  return __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+         __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+}
+
+// Where a lane's mirrored entries D(rc, rc - k) are held: row lane (rc - k) mod n
+// (row lane 0 for k > n, where every lane holds
+// a zero row).  One lane per row: k = 1 .. H, byte addresses packed four to a word
+// (held unpacked they would fill the registers).  Two lanes per row and one single
+// word in a block: half hf takes k = 4 t + 1 + 2 hf + e (e = 0, 1) at [2 t + e], the
+// words it holds itself.  Three single words: in FP64 arithmetic (OWN) half hf takes
+// the words it holds, k = 3 + 4 q + 2 hf + e at [2 q + e] and k = 1 + hf last; in
+// FP32 arithmetic, whose sums keep the order of one lane per row, k = 4 t + 1 + 2 hf
+// + e, which the other half holds (its two selects per entry cost 5 us of the 45
+// of a 20-wide patch sweep at 1024^2).
+template <int NB, bool OWN>
+struct Mirror {
+  static constexpr int H = Half<NB>::H, HV = Half<NB>::HV, NT = Half<NB>::NT;
+  static constexpr int NH = Half<NB>::NH, K0 = Half<NB>::K0;
+  int src[HV == 1 ? (H + 3) / 4 : 2 * NT];
+  __device__ static int col(int rc, int k, int n) {
     int c = rc - k;
     c = c < 0 ? c + n : c;
-    c = c < 0 ? 0 : c;
-    src[(k - 1) >> 2] |= (4 * (g0 + c)) << (8 * ((k - 1) & 3));
+    return c < 0 ? 0 : c;
   }
-}
+  __device__ Mirror(int rc, int hf, int n) {
+    if constexpr (HV == 1) {
+#pragma unroll
+      for (int w = 0; w < (H + 3) / 4; ++w) src[w] = 0;
+#pragma unroll
+      for (int k = 1; k <= H; ++k)
+        src[(k - 1) >> 2] |= (4 * col(rc, k, n)) << (8 * ((k - 1) & 3));
+    } else if constexpr (K0 == 3 && OWN) {
+#pragma unroll
+      for (int i = 0; i < 2 * NT; ++i)
+        src[i] = 4 * (hf * Half<NB>::R +
+                      col(rc, i < 2 * NH ? 3 + 4 * (i >> 1) + 2 * hf + (i & 1) : 1 + hf, n));
+    } else {
+      const int base = (K0 == 3 ? 1 - hf : hf) * Half<NB>::R;
+#pragma unroll
+      for (int i = 0; i < 2 * NT; ++i)
+        src[i] = 4 * (base + col(rc, 4 * (i >> 1) + 1 + 2 * hf + (i & 1), n));
+    }
+  }
+};
 
-// The mirrored entries rot[k - 1] = D(rc, rc - k) of one block.  The packed
-// addresses are unpacked at each use (opaque keeps the optimiser from
+// The mirrored entries of one block (one lane per row: the packed
+// addresses are unpacked at each use; opaque keeps the optimiser from
 // holding all H of them in registers across the sweep).
-template <typename S, int NB>
-__device__ __forceinline__ void mirror_rows(S (&rot)[Half<NB>::H], const HalfRow<S, NB>& d,
-                                            const int (&src)[(Half<NB>::H + 3) / 4]) {
-  int w[(Half<NB>::H + 3) / 4];
+template <typename S, int NB, bool OWN>
+__device__ __forceinline__ void mirror_rows(S (&rot)[Half<NB>::NM], const HalfRow<S, NB>& d,
+                                            const Mirror<NB, OWN>& m, int hf) {
+  constexpr int H = Half<NB>::H, NT = Half<NB>::NT, NH = Half<NB>::NH;
+  if constexpr (Half<NB>::HV == 1) {
+    int w[(H + 3) / 4];
 #pragma unroll
-  for (int i = 0; i < (Half<NB>::H + 3) / 4; ++i) w[i] = opaque(src[i]);
+    for (int i = 0; i < (H + 3) / 4; ++i) w[i] = opaque(m.src[i]);
 #pragma unroll
-  for (int k = 1; k <= Half<NB>::H; ++k)
-    rot[k - 1] = lane_fetch((w[(k - 1) >> 2] >> (8 * ((k - 1) & 3))) & 255, d.row(k));
-}
-
-// acc = sum_c D(rc, c) v[c]: the lane's rows k against vo[k] = v[(rc + k)
-// mod n], the mirrored entries against vr[-k] = v[(rc - k) mod n] (vo and vr
-// point into the group's doubled copy of v); four partial sums shorten the
-// chain of dependent additions.
-template <typename T, typename S, int NB>
-__device__ __forceinline__ T half_dot(const HalfRow<S, NB>& d, const S (&rot)[Half<NB>::H],
-                                      const T* vo, const T* vr) {
-  constexpr int NH = Half<NB>::NH, K0 = Half<NB>::K0, H = Half<NB>::H;
-  T a[4] = {T(0), T(0), T(0), T(0)};
+    for (int k = 1; k <= H; ++k)
+      rot[k - 1] = lane_fetch((w[(k - 1) >> 2] >> (8 * ((k - 1) & 3))) & 255, d.row(k));
+  } else if constexpr (Half<NB>::K0 == 1) {
 #pragma unroll
-  for (int q = 0; q < NH; ++q)
+    for (int i = 0; i < 2 * NT; ++i) rot[i] = lane_fetch(m.src[i], d.p[i >> 1][i & 1]);
+  } else if constexpr (OWN) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) a[i] = fmat((T)d.q[q][i], vo[K0 + 4 * q + i], a[i]);
+    for (int i = 0; i < 2 * NH; ++i) rot[i] = lane_fetch(m.src[i], d.p[i >> 1][i & 1]);
+    rot[2 * NH] = lane_fetch(m.src[2 * NH], hf ? d.s[0] : d.s[1]);
+  } else {
+    // what this lane passes to the other half: half 1 the single words 1 and 2,
+    // then its pair of quad t - 1; half 0 its pair of quad t
 #pragma unroll
-  for (int k = 0; k < K0; ++k) a[k] = fmat((T)d.h[k], vo[k], a[k]);
-#pragma unroll
-  for (int k = 1; k <= H; ++k) a[(k - 1) & 3] = fmat((T)rot[k - 1], vr[-k], a[(k - 1) & 3]);
-  return (a[0] + a[1]) + (a[2] + a[3]);
-}
-
-// Largest value of v over the 64 lanes of the wave, as a wave-uniform value.
-__device__ __forceinline__ int wave_max(int v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
-  return __builtin_amdgcn_readfirstlane(v);
-}
-
-// One sweep over the block rows of the boxes of a wave.  Step s uses block
-// blk(s), whose rows were loaded into register set s % DEPTH at step
-// s - DEPTH; right after its use the set is refilled with block s + DEPTH,
-// so every block has DEPTH - 1 steps to arrive.  The boxes of a wave have
-// different heights, so the wave runs nmax steps (its largest count, rounded
-// up to a multiple of DEPTH); a group's steps past its own nsteps re-load its
-// last block and are told valid = false.  No load is conditional, so the
-// compiler counts the loads in flight exactly and waits only for the block
-// a step uses (an early exit from the unrolled steps instead of the rounding
-// made the compiler wait for more loads and was slower).
-template <typename S, int NB, int DEPTH, typename Blk, typename Step>
-__device__ __forceinline__ void pipelined_sweep(int nsteps, int nmax, Blk blk, Step step,
-                                                const S* __restrict__ Dinv, int bstride,
-                                                int n, int r) {
-  const int last = nsteps > 0 ? nsteps - 1 : 0;
-  auto src = [&](int s) {
-    const int b = blk(s < last ? s : last);
-    return Dinv + (long long)(b > 0 ? b : 0) * bstride;
-  };
-  HalfRow<S, NB> reg[DEPTH];
-#pragma unroll
-  for (int u = 0; u < DEPTH; ++u) load_half<S, NB>(reg[u], src(u), n, opaque(r));
-  for (int s0 = 0; s0 < nmax; s0 += DEPTH) {
-#pragma unroll
-    for (int u = 0; u < DEPTH; ++u) {
-      const int s = s0 + u;
-      step(s, reg[u], s < nsteps);
-      load_half<S, NB>(reg[u], src(s + DEPTH), n, opaque(r));
+    for (int i = 0; i < 2 * NT; ++i) {
+      const int t = i >> 1, e = i & 1;
+      const S up = t == 0 ? (e ? d.s[0] : d.s[1]) : d.p[t > 0 ? t - 1 : 0][e];
+      const S dn = t < NH ? d.p[t < NH ? t : 0][e] : S(0);
+      rot[i] = lane_fetch(m.src[i], hf ? up : dn);
     }
   }
 }
 
-// Steps a wave runs for the largest of n over its groups: rounded up to a
-// multiple of DEPTH.
-template <int DEPTH>
-__device__ __forceinline__ int wave_steps(int n) {
-  const int m = wave_max(n);
-  return (m + DEPTH - 1) / DEPTH * DEPTH;
+// acc = sum_c D(rc, c) v[c]: the rows k against vo[k] = v[(rc + k)
+// mod n], the mirrored entries against vr[-k] = v[(rc - k) mod n] (vo and vr
+// point into the group's doubled copy of v); four partial sums shorten the
+// chain of dependent additions.  Two lanes per row: half hf forms the partial
+// sums 2 hf and 2 hf + 1 (vo and vr shifted by 2 hf by the caller), so the result
+// is that of one lane, bit for bit, unless half hf takes the mirrored words it holds
+// (Mirror).
+template <typename T, typename S, int NB>
+__device__ __forceinline__ T half_dot(const HalfRow<S, NB>& d, const S (&rot)[Half<NB>::NM],
+                                      const T* vo, const T* vr, int hf) {
+  constexpr int NH = Half<NB>::NH, K0 = Half<NB>::K0, H = Half<NB>::H, NT = Half<NB>::NT;
+  if constexpr (Half<NB>::HV == 1) {
+    T a[4] = {T(0), T(0), T(0), T(0)};
+#pragma unroll
+    for (int q = 0; q < NH; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = fmat((T)d.q[q][i], vo[K0 + 4 * q + i], a[i]);
+#pragma unroll
+    for (int k = 0; k < K0; ++k) a[k] = fmat((T)d.h[k], vo[k], a[k]);
+#pragma unroll
+    for (int k = 1; k <= H; ++k) a[(k - 1) & 3] = fmat((T)rot[k - 1], vr[-k], a[(k - 1) & 3]);
+    return (a[0] + a[1]) + (a[2] + a[3]);
+  } else {
+    T a[2] = {T(0), T(0)};
+#pragma unroll
+    for (int q = 0; q < NH; ++q)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) a[e] = fmat((T)d.p[q][e], vo[K0 + 4 * q + e], a[e]);
+    const T s0 = fmat((T)d.s[0], vo[0], a[0]);
+    if constexpr (K0 == 3) {
+      const T s1 = fmat((T)d.s[1], vo[1], a[1]);
+      a[0] = s0;
+      a[1] = hf ? a[1] : s1;
+    } else {
+      a[0] = hf ? a[0] : s0;
+    }
+    if constexpr (K0 == 3 && sizeof(T) == 8) {
+#pragma unroll
+      for (int q = 0; q < NH; ++q)
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+          a[e] = fmat((T)rot[2 * q + e], vr[-(3 + 4 * q + e)], a[e]);
+      a[1] = fmat((T)rot[2 * NH], vr[hf - 1], a[1]);
+    } else {
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const T v = fmat((T)rot[2 * t + e], vr[-(4 * t + 1 + e)], a[e]);
+          a[e] = 4 * t + 3 + e <= H ? v : hf ? a[e] : v;  // the last step of half 1 may lack it
+        }
+    }
+    return sum_halves(a[0] + a[1]);
+  }
 }
 
-// Words of the group's copy of the step vector for column width NB and group
-// size GS: v at [H, H + n) and again at [H + n, H + 2 n), zeros around it
+// One sweep over n row blocks of a box, the first at blk and each next one at
+// `dir` words from the one before.  Step s uses its block's words, loaded into
+// register set s % DEPTH at step
+// s - DEPTH; right after its use the set is refilled with block s + DEPTH (the
+// last block past the end), so every block has DEPTH - 1 steps to arrive.  No load
+// is conditional, so the
+// compiler counts the loads in flight exactly and waits only for the block
+// a step uses; the n % DEPTH last steps, which load nothing, run after the loop
+// (rounding the count up instead ran 24 steps for the 17 to 20 of a 20-wide patch).
+template <typename S, int NB, int DEPTH, typename Step>
+__device__ __forceinline__ void pipelined_sweep(int n, const S* __restrict__ blk, int dir,
+                                                Step step, int bx, int rc, int hf) {
+  const BlockPlaces<S, NB> at(bx, rc, hf);
+  HalfRow<S, NB> reg[DEPTH];
+  int left = n - 1;  // blocks after the one at blk
+  auto next = [&]() {
+    blk += left > 0 ? dir : 0;
+    --left;
+  };
+#pragma unroll
+  for (int u = 0; u < DEPTH; ++u) {
+    load_half<S, NB>(reg[u], blk, at, rc);
+    next();
+  }
+  int s0 = 0;
+  for (; s0 + DEPTH <= n; s0 += DEPTH) {
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) {
+      step(s0 + u, reg[u]);
+      load_half<S, NB>(reg[u], blk, at, rc);
+      next();
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < DEPTH - 1; ++u)
+    if (s0 + u < n) step(s0 + u, reg[u]);
+}
+
+// Words of the group's copy of the step vector for column width NB:
+// v at [H, H + n) and again at [H + n, H + 2 n), zeros around it
 // (the lane's rows past the box meet finite values).
-template <int NB, int GS>
-constexpr int vec_words() { return (NB / 2 + 2 * GS + 3) / 4 * 4; }
+template <int NB>
+constexpr int vec_words() { return (NB / 2 + 2 * Half<NB>::R + 3) / 4 * 4; }
 
 // Zero the group's vector slots (count words) before the first step.
-template <typename T, int GS>
-__device__ __forceinline__ void zero_slots(T* v, int count, int lane) {
-  for (int i = lane; i < count; i += GS) v[i] = T(0);
+template <typename T>
+__device__ __forceinline__ void zero_slots(T* v, int count) {
+  for (int i = threadIdx.x & 63; i < count; i += 64) v[i] = T(0);
 }
 
-// Block LDL^T solve of one box by a group; us holds b on entry and x on exit
-// in rows stop .. by - 1 (by rows of bx words, LDS; the backward pass ends at
-// row stop, the first row the caller reads, and rows below it keep their
-// forward values); cp holds the couplings T_j (LDS); vv is the group's vector
-// slot (vec_words, zeroed); g0 the group's first lane in the wave.  S is the storage type of the factors, T the arithmetic and vector
-// type (FP32 factors may be applied in FP64 arithmetic).  Lanes at or past
-// bx (and whole groups with live = false) take part in every step but read
-// only inside the box and write nothing outside their slot.
-template <typename T, typename S, int NB, int GS>
+// Meet the other group of the box, if it has two.
+template <int ENDS>
+__device__ __forceinline__ void pair_sync() {
+  if constexpr (ENDS == 2)
+    __syncthreads();
+  else
+    wave_sync();
+}
+
+// The row steps of one end of a box of by rows: from row first, step by dir rows,
+// the elimination up to and with the middle row h (one-ended factors: the last
+// row), n of them; then back substitution from the row before it, the other
+// way, down to row lo (end 0) or up to row hi (end 1), nb of them.
+template <int ENDS>
+struct EndSteps {
+  int h, first, dir, n, nb;
+  bool top;
+  __device__ EndSteps(int by, int end, int lo, int hi)
+      : h(ENDS == 2 ? by / 2 : by - 1), top(ENDS == 2 && end != 0) {
+    first = top ? by - 1 : 0;
+    dir = top ? -1 : 1;
+    n = (top ? by - 1 - h : h) + 1;
+    nb = top ? hi - h : h - lo;
+  }
+};
+
+// Block LDL^T solve of one box by the group of one end; us holds b on
+// entry and x on exit in rows lo .. hi (by rows of bx words, LDS, shared by the
+// groups; lo and hi are the first and the last row the caller reads, and
+// rows beyond them keep their elimination values); cp holds the couplings T_j
+// (LDS); vv is the group's vector slot (vec_words, zeroed); r the row lane and hf
+// the half of the lane.  S is the storage
+// type of the factors, T the arithmetic and vector type (FP32 factors may be
+// applied in FP64 arithmetic).  A step waits for its vector's way through LDS and
+// for its sums; what it reads of us and cp is fetched one step ahead.
+template <typename T, typename S, int NB>
 __device__ __forceinline__ void box_solve(T* us, T* vv, const S* cp, const S* __restrict__ Dinv,
-                                          int bx, int by, int bstride, int r, int g0,
-                                          bool live, int stop) {
-  constexpr int H = Half<NB>::H;
+                                          int bx, int by, int bstride, int r, int hf, int end,
+                                          int lo, int hi) {
+  constexpr int H = Half<NB>::H, HV = Half<NB>::HV, ENDS = box_ends<S>();
   constexpr int DEPTH = reg_depth<S, NB>();
-  const bool act = live && r < bx;
+  const EndSteps<ENDS> st(by, end, lo, hi);
   const int rc = r < bx ? r : bx - 1;
-  int src[(H + 3) / 4];
-  mirror_lanes<H>(src, g0, rc, bx);
-  const T* vo = vv + H + rc;
-  const T* vr = vv + H + rc + bx;
-  T carry = T(0);
-  pipelined_sweep<S, NB, DEPTH>(
-      live ? by : 0, wave_steps<DEPTH>(live ? by : 0), [](int s) { return s; },
-      [&](int s, const HalfRow<S, NB>& d, bool valid) {
-        S rot[H];
-        mirror_rows<S, NB>(rot, d, src);
-        const int j = s < by ? s : by - 1;
-        const T uj = us[j * bx + rc];
-        const T y = j > 0 ? fmat((T)cp[j * bx + rc], carry, uj) : uj;
-        const bool w = act && valid;
-        if (r < bx) vv[H + r] = vv[H + bx + r] = w ? y : T(0);
-        wave_sync();
-        const T acc = half_dot<T, S, NB>(d, rot, vo, vr);
-        wave_sync();
-        if (w) us[j * bx + r] = acc;
-        carry = w ? acc : carry;
-      },
-      Dinv, bstride, bx, rc);
-  // carry = x_{by-1} = u_{by-1}; rows by - 2 down to stop
-  const int nb = live && by - 1 - stop > 0 ? by - 1 - stop : 0;
-  pipelined_sweep<S, NB, DEPTH>(
-      nb, wave_steps<DEPTH>(nb), [by](int s) { return by - 2 - s; },
-      [&](int s, const HalfRow<S, NB>& d, bool valid) {
-        S rot[H];
-        mirror_rows<S, NB>(rot, d, src);
-        int j = by - 2 - s;
-        j = j < 0 ? 0 : j;
-        const int jn = j + 1 < by ? j + 1 : by - 1;
-        const bool w = act && valid;
-        const T y = (T)cp[jn * bx + rc] * carry;
-        if (r < bx) vv[H + r] = vv[H + bx + r] = w ? y : T(0);
-        wave_sync();
-        const T acc = half_dot<T, S, NB>(d, rot, vo, vr);
-        wave_sync();
-        const T xj = us[j * bx + rc] + acc;
-        if (w) us[j * bx + r] = xj;
-        carry = w ? xj : carry;
-      },
-      Dinv, bstride, bx, rc);
+  const Mirror<NB, sizeof(T) == 8> mir(rc, hf, bx);
+  const T* vo = vv + H + rc + 2 * hf;
+  const T* vr = vv + H + rc + bx - 2 * hf;
+  T* put = vv + H + rc + hf * bx;
+  T* ur = us + rc;
+  const S* cr = cp + rc;
+  const int dx = st.dir * bx;
+  T xh = T(0);
+  auto product = [&](const T& y, const HalfRow<S, NB>& d, const S (&rot)[Half<NB>::NM]) {
+    put[0] = y;
+    if constexpr (HV == 1) put[bx] = y;
+    wave_sync();
+    const T acc = half_dot<T, S, NB>(d, rot, vo, vr, hf);
+    wave_sync();
+    return acc;
+  };
+  // elimination: row j's couplings to the row before it are T_j at end 0 and
+  // T_{j+1} at end 1 (none at the first row)
+  {
+    int at = st.first * bx, ca = (st.top ? by : 0) * bx;
+    T carry = T(0), b = ur[at], c = T(0);
+    pipelined_sweep<S, NB, DEPTH>(
+        st.n, Dinv + st.first * bstride, st.dir * bstride,
+        [&](int s, const HalfRow<S, NB>& d) {
+          S rot[Half<NB>::NM];
+          mirror_rows<S, NB>(rot, d, mir, hf);
+          T y = fmat(c, carry, b);
+          if (ENDS == 2 && s == st.n - 1) {
+            pair_sync<ENDS>();  // both ends have reached the middle row
+            y = b;
+            if (st.h > 0) y = fmat((T)cr[st.h * bx], ur[(st.h - 1) * bx], y);
+            if (st.h + 1 < by) y = fmat((T)cr[(st.h + 1) * bx], ur[(st.h + 1) * bx], y);
+            pair_sync<ENDS>();  // both have read it and its neighbours
+          }
+          // the next step's row (the last step stays on its own)
+          const int on = s + 1 < st.n ? dx : 0, cur = at;
+          at += on;
+          ca += on;
+          b = ur[at];
+          c = (T)cr[ca];
+          carry = product(y, d, rot);
+          if (!(st.top && s == st.n - 1)) ur[cur] = carry;  // end 0 writes the middle row
+        },
+        bx, rc, hf);
+    xh = carry;
+  }
+  // substitution: row j's couplings to the row before it are T_{j+1} at end 0 and
+  // T_j at end 1
+  if (st.nb > 0) {
+    const int row = st.h - st.dir;
+    int at = row * bx, ca = (st.top ? row : st.h) * bx;
+    T carry = xh, b = ur[at], c = (T)cr[ca];
+    pipelined_sweep<S, NB, DEPTH>(
+        st.nb, Dinv + row * bstride, -st.dir * bstride,
+        [&](int s, const HalfRow<S, NB>& d) {
+          S rot[Half<NB>::NM];
+          mirror_rows<S, NB>(rot, d, mir, hf);
+          const T y = c * carry, u = b;
+          const int on = s + 1 < st.nb ? dx : 0, cur = at;
+          at -= on;
+          ca -= on;
+          b = ur[at];
+          c = (T)cr[ca];
+          carry = u + product(y, d, rot);
+          ur[cur] = carry;
+        },
+        bx, rc, hf);
+  }
 }
 
 // Stage a box for its solve: rows [0, by) of a grid vector (bx cells wide,
-// lane r: column r) and the box's couplings (by rows of bx words) into LDS,
-// sixteen rows of both in flight at a time, so that a box of up to sixteen
-// rows costs one memory latency.  Loads are unconditional (row and column
-// clamped into the box); the wave runs the rows of its tallest box.
-template <typename T, typename G, typename S>
+// row lane r: column r) and the box's couplings (by rows of bx words) into LDS,
+// the box's NSET sets of row lanes (halves and groups) taking runs of rows in
+// turn, both arrays' loads of a run in flight at a time, so that a box of up to
+// 32 rows (16 with one set) costs one memory
+// latency.  Loads are unconditional (row and column clamped into the box).
+template <int NSET, typename T, typename G, typename S>
 __device__ __forceinline__ void stage_box(T* dst, const G* __restrict__ src, long long origin,
                                           int nx, S* cdst, const S* __restrict__ csrc, int bx,
-                                          int by, int lane, bool live) {
-  const int rows = wave_max(live ? by : 0);
-  const int col = lane < bx ? lane : bx - 1;
-  const bool act = live && lane < bx;
-  for (int j0 = 0; j0 < rows; j0 += 16) {
-    G v[16];
-    S c[16];
+                                          int by, int r, int set) {
+  constexpr int RUN = NSET == 4 ? 8 : 16;
+  const int col = r < bx ? r : bx - 1;
+  const bool act = r < bx;
+  for (int jj = 0; jj < by; jj += RUN * NSET) {
+    const int j0 = jj + RUN * set;
+    G v[RUN];
+    S c[RUN];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
+    for (int u = 0; u < RUN; ++u) {
       const int j = j0 + u < by ? j0 + u : by - 1;
       v[u] = src[origin + (long long)j * nx + col];
       c[u] = csrc[j * bx + col];
     }
 #pragma unroll
-    for (int u = 0; u < 16; ++u)
+    for (int u = 0; u < RUN; ++u)
       if (act && j0 + u < by) {
-        dst[(j0 + u) * bx + lane] = (T)v[u];
-        cdst[(j0 + u) * bx + lane] = c[u];
+        dst[(j0 + u) * bx + r] = (T)v[u];
+        cdst[(j0 + u) * bx + r] = c[u];
       }
   }
 }
 
-// Copy count (>= 1) contiguous words from global memory into LDS with the
-// whole group, eight unconditional loads in flight per lane at a time.
-template <typename S, int GS>
+// Copy count (>= 1) contiguous words from global memory into LDS with a
+// box's NL lanes, eight unconditional loads in flight per lane at a time.
+template <typename S, int NL>
 __device__ __forceinline__ void words_to_lds(S* dst, const S* __restrict__ src, int count,
-                                             int lane, bool live) {
-  const int total = wave_max(live ? count : 0);
-  for (int q0 = 0; q0 < total; q0 += 8 * GS) {
+                                             int lane) {
+  for (int q0 = 0; q0 < count; q0 += 8 * NL) {
     S v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int q = q0 + u * GS + lane;
+      const int q = q0 + u * NL + lane;
       v[u] = src[q < count ? q : count - 1];
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int q = q0 + u * GS + lane;
-      if (live && q < count) dst[q] = v[u];
+      const int q = q0 + u * NL + lane;
+      if (q < count) dst[q] = v[u];
     }
   }
 }
 
-// LDS slot of one lane group:
-//   vv[vec_words] (T) | cp[max cells] (S) | us[max cells] (T),
-// every part 16-byte aligned; cp_words (the coupling area) is a multiple of
-// 16 bytes.
-template <typename T, typename S, int NB, int GS>
+// LDS slot of one box:
+//   vv[ends][vec_words] (T) | cp[max cells] (S) | us[max cells] (T),
+// every part 16-byte aligned; cp_words (the coupling area, also the trace
+// moments' buffer) is a multiple of 16 bytes.
+template <typename T, typename S, int NB>
 struct BoxSlot {
   T* vv;
   S* cp;
   T* us;
-  __device__ BoxSlot(char* base, int cp_words) {
-    constexpr int VW = vec_words<NB, GS>();
-    vv = reinterpret_cast<T*>(base);
-    cp = reinterpret_cast<S*>(base + VW * sizeof(T));
-    us = reinterpret_cast<T*>(base + VW * sizeof(T) + (long long)cp_words * sizeof(S));
+  __device__ BoxSlot(char* base, int cp_words, int end) {
+    constexpr int VW = vec_words<NB>(), ENDS = box_ends<S>();
+    vv = reinterpret_cast<T*>(base) + end * VW;
+    cp = reinterpret_cast<S*>(base + ENDS * VW * sizeof(T));
+    us = reinterpret_cast<T*>(base + ENDS * VW * sizeof(T) + (long long)cp_words * sizeof(S));
   }
 };
 
-// Legendre polynomial P_q at the face parameter xi_j = (2 j + 1) / n - 1
-// (three-term recurrence).
-__device__ __forceinline__ double legendre_face(int q, int j, int n) {
-  const double xi = (2.0 * j + 1.0) / n - 1.0;
+// The box of a thread in a launch of the box kernels: the box index (clamped:
+// groups past the last box, live = false, run along on it in their own slot and
+// write nothing outside), the end its group (wave) works on, its row lane r and
+// half hf; lane: its index among the box's NL threads, set: among the
+// box's sets of row lanes.
+template <typename S, int NB>
+struct BoxThread {
+  static constexpr int R = Half<NB>::R, HV = Half<NB>::HV;
+  static constexpr int ENDS = box_ends<S>(), NL = ENDS * 64, NSET = ENDS * HV;
+  int slot, end, lane, r, hf, set, i;
+  bool live;
+  __device__ BoxThread(int block, int m) {
+    const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    slot = g / ENDS;
+    end = g % ENDS;
+    lane = end * 64 + l;
+    r = l % R;
+    hf = l / R;
+    set = end * HV + hf;
+    const int i0 = block * (int)(blockDim.x / NL) + slot;
+    live = i0 < m;
+    i = live ? i0 : m - 1;
+  }
+};
+// First and last row of the box that the owned rows' traces read: one beyond
+// the owned rows on either side, inside the box.
+__device__ __forceinline__ int trace_lo(const BoxDesc& d) { return d.oy > 0 ? d.oy - 1 : 0; }
+__device__ __forceinline__ int trace_hi(const BoxDesc& d) {
+  return d.oy + d.oby < d.by ? d.oy + d.oby : d.by - 1;
+}
+
+// Legendre polynomial P_q at xi (three-term recurrence).
+__device__ __forceinline__ double legendre_at(int q, double xi) {
   double pm = 1.0, pq = xi;
   if (q == 0) return 1.0;
   for (int k = 1; k < q; ++k) {
@@ -504,49 +727,79 @@ __device__ __forceinline__ void face_cells(const BoxDesc& d, int side, int j, in
   cout = (r2 < 0 || r2 >= d.by || c2 < 0 || c2 >= d.bx) ? cin : r2 * d.bx + c2;
 }
 
-// Flux and pressure moments of one coarse dof k = (i, side, q) over the faces
-// of its side: sum_j P_q(xi_j) (cUi p_in + cUo p_out) and likewise with the
-// pressure weights; fw: the four weights of each face, from the dof's first
-// face.  v(c) reads the solution at box-local cell c.  One fixed order.
-template <typename V>
-__device__ __forceinline__ void trace_moments(const BoxDesc& d, int side, int q,
-                                              const double* __restrict__ fw, V v, double& su,
-                                              double& sp) {
-  const int len = side <= 1 ? d.oby : d.obx;
-  su = 0.0;
-  sp = 0.0;
-  for (int j0 = 0; j0 < len; j0 += 8) {
-    f64x2 w[8][2];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int j = j0 + u < len ? j0 + u : len - 1;
-      w[u][0] = *reinterpret_cast<const f64x2*>(fw + 4 * j);
-      w[u][1] = *reinterpret_cast<const f64x2*>(fw + 4 * j + 2);
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int j = j0 + u;
-      if (j < len) {
+// Flux and pressure moments of the coarse dofs k = (i, side, q) of a subdomain
+// over the faces of their sides: sum_j P_q(xi_j) (cUi p_in + cUo p_out) and
+// likewise with the pressure weights; face_w: the four weights of each face, the
+// subdomain's faces side after side.  v(c) reads the solution at box-local cell
+// c.  The box's NL threads take a face each (flux, pressure and xi_j into buf,
+// 3 NL words of LDS), then one thread per dof adds its side's faces in order:
+// the divisions, weights and cells of all faces cost one pass instead of one per
+// face and dof (14 of k_local's 89 us at 1024^2 in FP64, 8 of 33 us at 505 x 387,
+// were this serial).
+template <int ENDS, typename V>
+__device__ __forceinline__ void trace_moments(const BoxDesc& d, int lane, bool live,
+                                              const int* __restrict__ dof_side,
+                                              const int* __restrict__ dof_q,
+                                              const int* __restrict__ dof_face0, int k0, int nd,
+                                              const double* __restrict__ face_w, double* buf,
+                                              V v, double* __restrict__ mU,
+                                              double* __restrict__ mP) {
+  constexpr int NL = ENDS * 64;
+  const int f0 = dof_face0[k0];
+  const int last = dof_face0[k0 + nd - 1] - f0 +
+                   (dof_side[k0 + nd - 1] <= 1 ? d.oby : d.obx);  // faces of the subdomain
+  for (int kb = 0; kb < nd; kb += NL) {
+    const bool mine = kb + lane < nd;
+    const int k = k0 + (mine ? kb + lane : 0);
+    const int side = dof_side[k], q = dof_q[k], len = side <= 1 ? d.oby : d.obx;
+    const int fa = dof_face0[k] - f0;
+    double su = 0.0, sp = 0.0;
+    for (int base = 0; base < last; base += NL) {
+      const int f = base + lane;
+      if (f < last) {
+        // the face's side: the last dof whose faces start at or before it
+        int fs = 0, fb = 0;
+        for (int e = 0; e < nd; ++e) {
+          const int b = dof_face0[k0 + e] - f0;
+          if (b <= f) {
+            fs = dof_side[k0 + e];
+            fb = b;
+          }
+        }
+        const f64x2* w = reinterpret_cast<const f64x2*>(face_w + 4LL * (f0 + f));
+        const f64x2 wu = w[0], wp = w[1];
+        const int j = f - fb;
         int ci, co;
-        face_cells(d, side, j, ci, co);
+        face_cells(d, fs, j, ci, co);
         const double pin = v(ci), pout = v(co);
-        const double lw = legendre_face(q, j, len);
-        const double U = fmat(w[u][0][1], pout, w[u][0][0] * pin);
-        const double P = fmat(w[u][1][1], pout, w[u][1][0] * pin);
-        su = fmat(lw, U, su);
-        sp = fmat(lw, P, sp);
+        buf[lane] = fmat(wu[1], pout, wu[0] * pin);
+        buf[NL + lane] = fmat(wp[1], pout, wp[0] * pin);
+        buf[2 * NL + lane] = (2.0 * j + 1.0) / (fs <= 1 ? d.oby : d.obx) - 1.0;
       }
+      pair_sync<ENDS>();
+      if (mine) {
+        const int a = fa > base ? fa : base;
+        const int b = fa + len < base + NL ? fa + len : base + NL;
+        for (int t = a; t < b; ++t) {
+          const double lw = legendre_at(q, buf[2 * NL + t - base]);
+          su = fmat(lw, buf[t - base], su);
+          sp = fmat(lw, buf[NL + t - base], sp);
+        }
+      }
+      pair_sync<ENDS>();
+    }
+    if (mine && live) {
+      mU[k] = su;
+      mP[k] = sp;
     }
   }
 }
 
-// Source-driven solves of the apply, one lane group per subdomain: the
+// Source-driven solves of the apply: the
 // oversampled problem on hat-Omega_i (box d) with source r and zero Robin
 // data, p = its restriction to Omega_i (the owned cells of d), fused with
-// the trace moments of the coarse right-hand side (one lane per coarse dof
-// of the subdomain, FP64 sums).  Groups past the last subdomain (live =
-// false) run along on the last one and write nothing.
-template <typename T, typename S, int NB, int GS>
+// the trace moments of the coarse right-hand side (FP64 sums).
+template <typename T, typename S, int NB>
 __device__ __forceinline__ void local_body(
     const Blk blk, const BoxDesc* __restrict__ boxes, int m, int group_bytes, int cp_words,
     const S* __restrict__ dinv, const S* __restrict__ coup, const double* __restrict__ r,
@@ -555,37 +808,34 @@ __device__ __forceinline__ void local_body(
     const int* __restrict__ dof_face0, const double* __restrict__ face_w,
     double* __restrict__ mU, double* __restrict__ mP) {
   extern __shared__ __align__(16) char smem_raw[];
-  const int grp = threadIdx.x / GS, lane = threadIdx.x % GS;
-  const int i0 = blk.id * (blockDim.x / GS) + grp;
-  const bool live = i0 < m;
-  const int i = live ? i0 : m - 1;
-  BoxSlot<T, S, NB, GS> L(smem_raw + (long long)grp * group_bytes, cp_words);
-  const BoxDesc d = boxes[i];
+  typedef BoxThread<S, NB> BT;
+  const BT t(blk.id, m);
+  BoxSlot<T, S, NB> L(smem_raw + (long long)t.slot * group_bytes, cp_words, t.end);
+  const BoxDesc d = boxes[t.i];
   const int bx = d.bx, by = d.by;
   const long long origin = (long long)d.y0 * nx + d.x0;
-  stage_box(L.us, r, origin, nx, L.cp, coup + d.coff, bx, by, lane, live);
-  zero_slots<T, GS>(L.vv, vec_words<NB, GS>(), lane);
-  wave_sync();
-  if (live && d.pin && lane == 0) L.us[0] = T(0);
-  wave_sync();
-  // rows from the one across Omega_i's south side (its traces) upward
-  box_solve<T, S, NB, GS>(L.us, L.vv, L.cp, dinv + d.doff, bx, by, d.bs, lane,
-                         (threadIdx.x & 63) - lane, live, d.oy > 0 ? d.oy - 1 : 0);
-  wave_sync();
-  if (live && lane >= d.ox && lane < d.ox + d.obx) {
+  stage_box<BT::NSET>(L.us, r, origin, nx, L.cp, coup + d.coff, bx, by, t.r, t.set);
+  zero_slots(L.vv, vec_words<NB>());
+  pair_sync<BT::ENDS>();
+  if (d.pin) {  // one box covers the grid: the same in every group
+    if (t.lane == 0) L.us[0] = T(0);
+    pair_sync<BT::ENDS>();
+  }
+  box_solve<T, S, NB>(L.us, L.vv, L.cp, dinv + d.doff, bx, by, d.bs, t.r, t.hf, t.end,
+                            trace_lo(d), trace_hi(d));
+  pair_sync<BT::ENDS>();
+  if (t.live && t.r >= d.ox && t.r < d.ox + d.obx) {
     const long long o2 = origin + (long long)d.oy * nx;
-    for (int j = 0; j < d.oby; ++j) p[o2 + (long long)j * nx + lane] = L.us[(d.oy + j) * bx + lane];
+    for (int j = t.set; j < d.oby; j += BT::NSET)
+      p[o2 + (long long)j * nx + t.r] = L.us[(d.oy + j) * bx + t.r];
   }
-  if (!live) return;
-  for (int k = dof_off[i] + lane; k < dof_off[i + 1]; k += GS) {
-    double su, sp;
-    trace_moments(d, dof_side[k], dof_q[k], face_w + 4LL * dof_face0[k],
-                  [&](int c) { return (double)L.us[c]; }, su, sp);
-    mU[k] = su;
-    mP[k] = sp;
-  }
+  const int k0 = dof_off[t.i], nd = dof_off[t.i + 1] - k0;
+  if (nd > 0)
+    trace_moments<BT::ENDS>(d, t.lane, t.live, dof_side, dof_q, dof_face0, k0, nd,
+                                    face_w, reinterpret_cast<double*>(L.cp),
+                                    [&](int c) { return (double)L.us[c]; }, mU, mP);
 }
-template <typename T, typename S, int NB, int GS = (NB <= 16 ? 16 : NB <= 32 ? 32 : 64)>
+template <typename T, typename S, int NB>
 __global__ void __launch_bounds__(kBoxThreads)
     k_local(const BoxDesc* __restrict__ boxes, int m, int group_bytes, int cp_words,
             const S* __restrict__ dinv, const S* __restrict__ coup,
@@ -594,8 +844,8 @@ __global__ void __launch_bounds__(kBoxThreads)
             const int* __restrict__ dof_q, const int* __restrict__ dof_face0,
             const double* __restrict__ face_w, double* __restrict__ mU,
             double* __restrict__ mP) {
-  local_body<T, S, NB, GS>(hw_blk(), boxes, m, group_bytes, cp_words, dinv, coup, r, p, nx,
-                           dof_off, dof_side, dof_q, dof_face0, face_w, mU, mP);
+  local_body<T, S, NB>(hw_blk(), boxes, m, group_bytes, cp_words, dinv, coup, r, p, nx,
+                             dof_off, dof_side, dof_q, dof_face0, face_w, mU, mP);
 }
 
 // Interface right-hand side in tree order: for tree position t, gsrc[t] =
@@ -1030,11 +1280,10 @@ __global__ void __launch_bounds__(kVecThreads)
   residual_body<T>(hw_blk(), tx, ty, nx, ny, r, p, rho);
 }
 
-// Restricted additive Schwarz: solve A[S_i] e = rho[S_i] on patch i (one
-// lane group per patch) and add e on the owned subdomain Omega_i (each cell
-// is written by one patch only).  Groups past the last patch run along on
-// the last one and write nothing.
-template <typename T, typename S, int NB, int GS>
+// Restricted additive Schwarz: solve A[S_i] e = rho[S_i] on patch i
+// and add e on the owned subdomain Omega_i (each cell
+// is written by one patch only).
+template <typename T, typename S, int NB>
 __device__ __forceinline__ void patch_body(const Blk blk, const BoxDesc* __restrict__ boxes,
                                            int m, int group_bytes, int cp_words,
                                            const S* __restrict__ dinv,
@@ -1042,47 +1291,49 @@ __device__ __forceinline__ void patch_body(const Blk blk, const BoxDesc* __restr
                                            const T* __restrict__ rho, T* __restrict__ p,
                                            int nx) {
   extern __shared__ __align__(16) char smem_raw[];
-  const int grp = threadIdx.x / GS, lane = threadIdx.x % GS;
-  const int i0 = blk.id * (blockDim.x / GS) + grp;
-  const bool live = i0 < m;
-  const int i = live ? i0 : m - 1;
-  BoxSlot<T, S, NB, GS> L(smem_raw + (long long)grp * group_bytes, cp_words);
-  const BoxDesc d = boxes[i];
+  typedef BoxThread<S, NB> BT;
+  const BT t(blk.id, m);
+  BoxSlot<T, S, NB> L(smem_raw + (long long)t.slot * group_bytes, cp_words, t.end);
+  const BoxDesc d = boxes[t.i];
   const int bx = d.bx, by = d.by;
   const long long origin = (long long)d.y0 * nx + d.x0;
-  stage_box(L.us, rho, origin, nx, L.cp, coup + d.coff, bx, by, lane, live);
-  zero_slots<T, GS>(L.vv, vec_words<NB, GS>(), lane);
-  wave_sync();
-  if (live && d.pin && lane == 0) L.us[0] = T(0);
-  wave_sync();
-  // the owned rows upward
-  box_solve<T, S, NB, GS>(L.us, L.vv, L.cp, dinv + d.doff, bx, by, d.bs, lane,
-                         (threadIdx.x & 63) - lane, live, d.oy);
-  wave_sync();
-  // p += e on the owned cells, sixteen rows of read-modify-write in flight
-  const bool own = live && lane >= d.ox && lane < d.ox + d.obx;
-  const int col = own ? lane : d.ox;
+  stage_box<BT::NSET>(L.us, rho, origin, nx, L.cp, coup + d.coff, bx, by, t.r, t.set);
+  zero_slots(L.vv, vec_words<NB>());
+  pair_sync<BT::ENDS>();
+  if (d.pin) {  // one box covers the grid: the same in every group
+    if (t.lane == 0) L.us[0] = T(0);
+    pair_sync<BT::ENDS>();
+  }
+  box_solve<T, S, NB>(L.us, L.vv, L.cp, dinv + d.doff, bx, by, d.bs, t.r, t.hf, t.end,
+                            d.oy, d.oy + d.oby - 1);
+  pair_sync<BT::ENDS>();
+  // p += e on the owned cells, each set of row lanes a run of rows in turn, all
+  // of a run's read-modify-writes in flight
+  constexpr int RUN = BT::NSET == 4 ? 4 : BT::NSET == 2 ? 8 : 16;
+  const bool own = t.live && t.r >= d.ox && t.r < d.ox + d.obx;
+  const int col = own ? t.r : d.ox;
   const long long o2 = origin + (long long)d.oy * nx;
-  const int rows = wave_max(live ? d.oby : 0);
-  for (int j0 = 0; j0 < rows; j0 += 16) {
-    T v[16];
+  const int rows = d.oby;
+  for (int jj = 0; jj < rows; jj += RUN * BT::NSET) {
+    const int j0 = jj + RUN * t.set;
+    T v[RUN];
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
+    for (int u = 0; u < RUN; ++u) {
       const int j = j0 + u < d.oby ? j0 + u : d.oby - 1;
       v[u] = p[o2 + (long long)j * nx + col];
     }
 #pragma unroll
-    for (int u = 0; u < 16; ++u)
+    for (int u = 0; u < RUN; ++u)
       if (own && j0 + u < d.oby)
-        p[o2 + (long long)(j0 + u) * nx + lane] = v[u] + L.us[(d.oy + j0 + u) * bx + lane];
+        p[o2 + (long long)(j0 + u) * nx + t.r] = v[u] + L.us[(d.oy + j0 + u) * bx + t.r];
   }
 }
-template <typename T, typename S, int NB, int GS = (NB <= 16 ? 16 : NB <= 32 ? 32 : 64)>
+template <typename T, typename S, int NB>
 __global__ void __launch_bounds__(kBoxThreads)
     k_patch(const BoxDesc* __restrict__ boxes, int m, int group_bytes, int cp_words,
             const S* __restrict__ dinv, const S* __restrict__ coup, const T* __restrict__ rho,
             T* __restrict__ p, int nx) {
-  patch_body<T, S, NB, GS>(hw_blk(), boxes, m, group_bytes, cp_words, dinv, coup, rho, p, nx);
+  patch_body<T, S, NB>(hw_blk(), boxes, m, group_bytes, cp_words, dinv, coup, rho, p, nx);
 }
 
 template <typename T>
@@ -1381,15 +1632,6 @@ struct RhsPtrs {
   T* v[kMaxRhs];
 };
 
-// Blocks in flight per lane for K right-hand sides: about 64 VGPRs of rows
-// (the K columns need their own registers), 2 or 4.
-template <typename S, int NB, int K>
-constexpr int reg_depth_k() {
-  constexpr int per_block = half_rows(NB) * (int)sizeof(S) / 4;
-  constexpr int d = pow2_depth((K == 1 ? 96 : 64) / per_block);
-  return d > 4 ? 4 : d;
-}
-
 // acc[k] = sum_c D(rc, c) v_k[c] for the K vectors of the group (column k's
 // doubled copy at vo / vr + k * VW): each factor entry is converted once and
 // used for every column; per column, the order of half_dot.  A scheduling
@@ -1397,40 +1639,99 @@ constexpr int reg_depth_k() {
 // all the vector reads at once (which would need more registers than a lane
 // has).
 template <typename T, typename S, int NB, int K, int VW>
-__device__ __forceinline__ void half_dot_k(const HalfRow<S, NB>& d, const S (&rot)[Half<NB>::H],
-                                           const T* vo, const T* vr, T (&acc)[K]) {
-  constexpr int NH = Half<NB>::NH, K0 = Half<NB>::K0, H = Half<NB>::H;
-  T a[K][4];
+__device__ __forceinline__ void half_dot_k(const HalfRow<S, NB>& d,
+                                           const S (&rot)[Half<NB>::NM], const T* vo,
+                                           const T* vr, T (&acc)[K], int hf) {
+  constexpr int NH = Half<NB>::NH, K0 = Half<NB>::K0, H = Half<NB>::H, NT = Half<NB>::NT;
+  if constexpr (Half<NB>::HV == 1) {
+    T a[K][4];
 #pragma unroll
-  for (int k = 0; k < K; ++k) a[k][0] = a[k][1] = a[k][2] = a[k][3] = T(0);
+    for (int k = 0; k < K; ++k) a[k][0] = a[k][1] = a[k][2] = a[k][3] = T(0);
 #pragma unroll
-  for (int q = 0; q < NH; ++q) {
-    const T dq[4] = {(T)d.q[q][0], (T)d.q[q][1], (T)d.q[q][2], (T)d.q[q][3]};
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[k][i] = fmat(dq[i], vo[k * VW + K0 + 4 * q + i], a[k][i]);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-#pragma unroll
-  for (int e = 0; e < K0; ++e) {
-    const T de = (T)d.h[e];
-#pragma unroll
-    for (int k = 0; k < K; ++k) a[k][e] = fmat(de, vo[k * VW + e], a[k][e]);
-  }
-#pragma unroll
-  for (int g = 1; g <= H; g += 4) {
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int e = g; e < g + 4 && e <= H; ++e) {
-      const T de = (T)rot[e - 1];
+    for (int q = 0; q < NH; ++q) {
+      const T dq[4] = {(T)d.q[q][0], (T)d.q[q][1], (T)d.q[q][2], (T)d.q[q][3]};
 #pragma unroll
       for (int k = 0; k < K; ++k)
-        a[k][(e - 1) & 3] = fmat(de, vr[k * VW - e], a[k][(e - 1) & 3]);
-    }
-  }
 #pragma unroll
-  for (int k = 0; k < K; ++k) acc[k] = (a[k][0] + a[k][1]) + (a[k][2] + a[k][3]);
+        for (int i = 0; i < 4; ++i) a[k][i] = fmat(dq[i], vo[k * VW + K0 + 4 * q + i], a[k][i]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int e = 0; e < K0; ++e) {
+      const T de = (T)d.h[e];
+#pragma unroll
+      for (int k = 0; k < K; ++k) a[k][e] = fmat(de, vo[k * VW + e], a[k][e]);
+    }
+#pragma unroll
+    for (int g = 1; g <= H; g += 4) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int e = g; e < g + 4 && e <= H; ++e) {
+        const T de = (T)rot[e - 1];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+          a[k][(e - 1) & 3] = fmat(de, vr[k * VW - e], a[k][(e - 1) & 3]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc[k] = (a[k][0] + a[k][1]) + (a[k][2] + a[k][3]);
+  } else {
+    T a[K][2];
+#pragma unroll
+    for (int k = 0; k < K; ++k) a[k][0] = a[k][1] = T(0);
+#pragma unroll
+    for (int q = 0; q < NH; ++q) {
+      const T dq[2] = {(T)d.p[q][0], (T)d.p[q][1]};
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) a[k][e] = fmat(dq[e], vo[k * VW + K0 + 4 * q + e], a[k][e]);
+      if (q & 1) __builtin_amdgcn_sched_barrier(0);
+    }
+    const T s0 = (T)d.s[0], s1 = K0 == 3 ? (T)d.s[1] : T(0);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const T u = fmat(s0, vo[k * VW], a[k][0]);
+      if constexpr (K0 == 3) {
+        const T w = fmat(s1, vo[k * VW + 1], a[k][1]);
+        a[k][0] = u;
+        a[k][1] = hf ? a[k][1] : w;
+      } else {
+        a[k][0] = hf ? a[k][0] : u;
+      }
+    }
+    if constexpr (K0 == 3 && sizeof(T) == 8) {
+#pragma unroll
+      for (int q = 0; q < NH; ++q) {
+        if (q % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const T de = (T)rot[2 * q + e];
+#pragma unroll
+          for (int k = 0; k < K; ++k) a[k][e] = fmat(de, vr[k * VW - (3 + 4 * q + e)], a[k][e]);
+        }
+      }
+      const T de = (T)rot[2 * NH];
+#pragma unroll
+      for (int k = 0; k < K; ++k) a[k][1] = fmat(de, vr[k * VW + hf - 1], a[k][1]);
+    } else {
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        if (t % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const T de = (T)rot[2 * t + e];
+#pragma unroll
+          for (int k = 0; k < K; ++k) {
+            const T v = fmat(de, vr[k * VW - (4 * t + 1 + e)], a[k][e]);
+            a[k][e] = 4 * t + 3 + e <= H ? v : hf ? a[k][e] : v;
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc[k] = sum_halves(a[k][0] + a[k][1]);
+  }
 }
 
 // Completes this work-item's global stores before its later loads and makes
@@ -1439,119 +1740,151 @@ __device__ __forceinline__ void group_fence() {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
 }
 
-// Block LDL^T solves of one box for K right-hand sides by a group (the
-// recurrence of box_solve, K columns per step).  Row j of right-hand side k
-// is read at in[k] + j * istride (lane r: column r); the solution is built
-// in place at work[k] + j * wstride: the forward pass leaves u_j there and
-// the backward pass overwrites it with x_j.  The next step's rows are loaded
+// Block LDL^T solves of one box for K right-hand sides by the group
+// of one end (the recurrence of box_solve, K columns per step).  Row j of
+// right-hand side k
+// is read at in[k] + j * istride (row lane r: column r); the solution is built
+// in place at work[k] + j * wstride: the elimination leaves u_j there and
+// the substitution overwrites it with x_j.  The next step's rows are loaded
 // one step ahead.  vv holds the group's K vector slots (vec_words each,
-// zeroed), cp the couplings (LDS); g0 is the group's first lane in the wave;
-// pin zeroes b_0 in column 0 (a box fixed at its first cell); the backward
-// pass ends at row stop, as in box_solve.
-template <typename T, typename S, int NB, int GS, int K, typename In>
+// zeroed), other those of the box's other group; cp the couplings (LDS); live =
+// false writes nothing;
+// pin zeroes b_0 in column 0 (a box fixed at its first cell); the other
+// arguments as in box_solve.
+template <typename T, typename S, int NB, int K, typename In>
 __device__ __forceinline__ void box_solve_k(const In* const (&in)[K], long long istride,
                                             T* const (&work)[K], long long wstride, T* vv,
-                                            const S* cp, const S* __restrict__ Dinv, int bx,
-                                            int by, int bstride, int r, int g0, bool live,
-                                            bool pin, int stop) {
-  constexpr int H = Half<NB>::H, VW = vec_words<NB, GS>();
-  constexpr int DEPTH = reg_depth_k<S, NB, K>();
-  const bool act = live && r < bx;
+                                            const T* other, const S* cp,
+                                            const S* __restrict__ Dinv, int bx, int by,
+                                            int bstride, int r, int hf, int end,
+                                            bool live, bool pin, int lo, int hi) {
+  constexpr int H = Half<NB>::H, HV = Half<NB>::HV, ENDS = box_ends<S>();
+  constexpr int VW = vec_words<NB>(), DEPTH = reg_depth<S, NB>();
+  const EndSteps<ENDS> st(by, end, lo, hi);
   const int rc = r < bx ? r : bx - 1;
-  int src[(H + 3) / 4];
-  mirror_lanes<H>(src, g0, rc, bx);
-  const T* vo = vv + H + rc;
-  const T* vr = vv + H + rc + bx;
-  T carry[K], nxt[K];
+  const Mirror<NB, sizeof(T) == 8> mir(rc, hf, bx);
+  const T* vo = vv + H + rc + 2 * hf;
+  const T* vr = vv + H + rc + bx - 2 * hf;
+  T* put = vv + H + rc + hf * bx;
+  const S* cr = cp + rc;
+  const int dx = st.dir * bx;
+  const bool own = live && hf == 0 && r < bx;
+  T xh[K];
+  auto product = [&](const T (&y)[K], const HalfRow<S, NB>& d,
+                     const S (&rot)[Half<NB>::NM], T (&acc)[K]) {
 #pragma unroll
-  for (int k = 0; k < K; ++k) carry[k] = T(0);
-  auto in_row = [&](int s) {
-    const long long off = (long long)(s < by ? s : by - 1) * istride + rc;
-#pragma unroll
-    for (int k = 0; k < K; ++k) nxt[k] = (T)in[k][off];
+    for (int k = 0; k < K; ++k) {
+      put[k * VW] = y[k];
+      if constexpr (HV == 1) put[k * VW + bx] = y[k];
+    }
+    wave_sync();
+    half_dot_k<T, S, NB, K, VW>(d, rot, vo, vr, acc, hf);
+    wave_sync();
   };
-  in_row(0);
-  pipelined_sweep<S, NB, DEPTH>(
-      live ? by : 0, wave_steps<DEPTH>(live ? by : 0), [](int s) { return s; },
-      [&](int s, const HalfRow<S, NB>& d, bool valid) {
-        S rot[H];
-        mirror_rows<S, NB>(rot, d, src);
-        const int j = s < by ? s : by - 1;
-        const bool w = act && valid;
-        T b[K];
+  {
+    int row = st.first, ca = (st.top ? by : 0) * bx;
+    T carry[K], nxt[K], c = T(0);
+    auto fetch = [&]() {
 #pragma unroll
-        for (int k = 0; k < K; ++k) b[k] = (pin && j == 0 && rc == 0) ? T(0) : nxt[k];
-        in_row(s + 1);
-        const T cj = (T)cp[j * bx + rc];
-        if (r < bx)
+      for (int k = 0; k < K; ++k) nxt[k] = (T)in[k][row * istride + rc];
+      if (pin && row == 0 && rc == 0)
+#pragma unroll
+        for (int k = 0; k < K; ++k) nxt[k] = T(0);
+    };
+#pragma unroll
+    for (int k = 0; k < K; ++k) carry[k] = T(0);
+    fetch();
+    pipelined_sweep<S, NB, DEPTH>(
+        st.n, Dinv + st.first * bstride, st.dir * bstride,
+        [&](int s, const HalfRow<S, NB>& d) {
+          S rot[Half<NB>::NM];
+          mirror_rows<S, NB>(rot, d, mir, hf);
+          T b[K], y[K];
 #pragma unroll
           for (int k = 0; k < K; ++k) {
-            const T y = j > 0 ? fmat(cj, carry[k], b[k]) : b[k];
-            vv[k * VW + H + r] = vv[k * VW + H + bx + r] = w ? y : T(0);
+            b[k] = nxt[k];
+            y[k] = fmat(c, carry[k], b[k]);
           }
-        wave_sync();
-        T acc[K];
-        half_dot_k<T, S, NB, K, VW>(d, rot, vo, vr, acc);
-        wave_sync();
+          const int cur = row;
+          row += s + 1 < st.n ? st.dir : 0;
+          ca += s + 1 < st.n ? dx : 0;
+          fetch();
+          c = (T)cr[ca];
+          if (ENDS == 2 && s == st.n - 1) {
+            // both ends have reached the middle row: exchange the rows next to it
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-          if (w) work[k][(long long)j * wstride + r] = acc[k];
-          carry[k] = w ? acc[k] : carry[k];
-        }
-      },
-      Dinv, bstride, bx, rc);
+            for (int k = 0; k < K; ++k) vv[k * VW + H + rc] = carry[k];
+            pair_sync<ENDS>();
+            const T cl = (T)cr[st.h * bx], ch = (T)cr[(st.h + 1 < by ? st.h + 1 : st.h) * bx];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+              const T o = other[k * VW + H + rc];
+              y[k] = b[k];
+              if (st.h > 0) y[k] = fmat(cl, st.top ? o : carry[k], y[k]);
+              if (st.h + 1 < by) y[k] = fmat(ch, st.top ? carry[k] : o, y[k]);
+            }
+            pair_sync<ENDS>();
+          }
+          product(y, d, rot, carry);
+          if (own && !(st.top && s == st.n - 1))
+#pragma unroll
+            for (int k = 0; k < K; ++k) work[k][cur * wstride + r] = carry[k];
+        },
+        bx, rc, hf);
+#pragma unroll
+    for (int k = 0; k < K; ++k) xh[k] = carry[k];
+  }
+  group_fence();  // lanes of the wave read back the rows that others of it wrote
+  if (st.nb > 0) {
+    int row = st.h - st.dir, ca = (st.top ? row : st.h) * bx;
+    T carry[K], nxt[K], c = (T)cr[ca];
+    auto fetch = [&]() {
+#pragma unroll
+      for (int k = 0; k < K; ++k) nxt[k] = work[k][row * wstride + rc];
+    };
+#pragma unroll
+    for (int k = 0; k < K; ++k) carry[k] = xh[k];
+    fetch();
+    pipelined_sweep<S, NB, DEPTH>(
+        st.nb, Dinv + row * bstride, -st.dir * bstride,
+        [&](int s, const HalfRow<S, NB>& d) {
+          S rot[Half<NB>::NM];
+          mirror_rows<S, NB>(rot, d, mir, hf);
+          T u[K], y[K], acc[K];
+#pragma unroll
+          for (int k = 0; k < K; ++k) {
+            u[k] = nxt[k];
+            y[k] = c * carry[k];
+          }
+          const int cur = row;
+          row -= s + 1 < st.nb ? st.dir : 0;
+          ca -= s + 1 < st.nb ? dx : 0;
+          fetch();
+          c = (T)cr[ca];
+          product(y, d, rot, acc);
+#pragma unroll
+          for (int k = 0; k < K; ++k) carry[k] = u[k] + acc[k];
+          if (own)
+#pragma unroll
+            for (int k = 0; k < K; ++k) work[k][cur * wstride + r] = carry[k];
+        },
+        bx, rc, hf);
+  }
   group_fence();
-  // carry = x_{by-1} = u_{by-1}; rows by - 2 down to stop
-  const int nb = live && by - 1 - stop > 0 ? by - 1 - stop : 0;
-  auto u_row = [&](int s) {
-    int j = by - 2 - s;
-    j = j < 0 ? 0 : j;
-#pragma unroll
-    for (int k = 0; k < K; ++k) nxt[k] = work[k][(long long)j * wstride + rc];
-  };
-  u_row(0);
-  pipelined_sweep<S, NB, DEPTH>(
-      nb, wave_steps<DEPTH>(nb), [by](int s) { return by - 2 - s; },
-      [&](int s, const HalfRow<S, NB>& d, bool valid) {
-        S rot[H];
-        mirror_rows<S, NB>(rot, d, src);
-        int j = by - 2 - s;
-        j = j < 0 ? 0 : j;
-        const int jn = j + 1 < by ? j + 1 : by - 1;
-        const bool w = act && valid;
-        T u[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) u[k] = nxt[k];
-        u_row(s + 1);
-        const T cj = (T)cp[jn * bx + rc];
-        if (r < bx)
-#pragma unroll
-          for (int k = 0; k < K; ++k)
-            vv[k * VW + H + r] = vv[k * VW + H + bx + r] = w ? cj * carry[k] : T(0);
-        wave_sync();
-        T acc[K];
-        half_dot_k<T, S, NB, K, VW>(d, rot, vo, vr, acc);
-        wave_sync();
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          const T xj = u[k] + acc[k];
-          if (w) work[k][(long long)j * wstride + r] = xj;
-          carry[k] = w ? xj : carry[k];
-        }
-      },
-      Dinv, bstride, bx, rc);
-  group_fence();
+  pair_sync<ENDS>();
 }
 
-// LDS slot of one lane group for K right-hand sides:
-//   vv[K][vec_words] (T) | cp[max cells] (S).
-template <typename T, typename S, int NB, int GS, int K>
+// LDS slot of one box for K right-hand sides:
+//   vv[ends][K][vec_words] (T) | cp[max cells] (S, also the moments' buffer).
+template <typename T, typename S, int NB, int K>
 struct BoxSlotK {
-  T* vv;
+  T *vv, *other;
   S* cp;
-  __device__ BoxSlotK(char* base) {
-    vv = reinterpret_cast<T*>(base);
-    cp = reinterpret_cast<S*>(base + K * vec_words<NB, GS>() * sizeof(T));
+  __device__ BoxSlotK(char* base, int end) {
+    constexpr int W = K * vec_words<NB>(), ENDS = box_ends<S>();
+    vv = reinterpret_cast<T*>(base) + end * W;
+    other = reinterpret_cast<T*>(base) + (ENDS - 1 - end) * W;
+    cp = reinterpret_cast<S*>(base + ENDS * W * sizeof(T));
   }
 };
 
@@ -1560,7 +1893,7 @@ struct BoxSlotK {
 // stride bx), p_k = its restriction to Omega_i, and the trace moments of
 // every coarse dof of the subdomain for every k (mU[k * nc + dof], mP
 // likewise; the arithmetic of k_local per column).
-template <typename T, typename S, int NB, int K, int GS = (NB <= 16 ? 16 : NB <= 32 ? 32 : 64)>
+template <typename T, typename S, int NB, int K>
 __global__ void __launch_bounds__(kBoxThreads)
     k_local_k(const BoxDesc* __restrict__ boxes, int m, int group_bytes,
               const S* __restrict__ dinv, const S* __restrict__ coup, RhsPtrs<const double> r,
@@ -1569,12 +1902,10 @@ __global__ void __launch_bounds__(kBoxThreads)
               const int* __restrict__ dof_face0, const double* __restrict__ face_w,
               double* __restrict__ mU, double* __restrict__ mP, int nc) {
   extern __shared__ __align__(16) char smem_raw[];
-  const int grp = threadIdx.x / GS, lane = threadIdx.x % GS;
-  const int i0 = blockIdx.x * (blockDim.x / GS) + grp;
-  const bool live = i0 < m;
-  const int i = live ? i0 : m - 1;
-  BoxSlotK<T, S, NB, GS, K> L(smem_raw + (long long)grp * group_bytes);
-  const BoxDesc d = boxes[i];
+  typedef BoxThread<S, NB> BT;
+  const BT t(blockIdx.x, m);
+  BoxSlotK<T, S, NB, K> L(smem_raw + (long long)t.slot * group_bytes, t.end);
+  const BoxDesc d = boxes[t.i];
   const int bx = d.bx, by = d.by;
   const long long origin = (long long)d.y0 * nx + d.x0;
   const double* in[K];
@@ -1584,49 +1915,44 @@ __global__ void __launch_bounds__(kBoxThreads)
     in[k] = r.v[k] + origin;
     work[k] = e.v[k] + d.coff;
   }
-  words_to_lds<S, GS>(L.cp, coup + d.coff, bx * by, lane, live);
-  zero_slots<T, GS>(L.vv, K * vec_words<NB, GS>(), lane);
-  wave_sync();
-  box_solve_k<T, S, NB, GS, K, double>(in, nx, work, bx, L.vv, L.cp, dinv + d.doff, bx, by,
-                                       d.bs, lane, (threadIdx.x & 63) - lane, live,
-                                       live && d.pin, d.oy > 0 ? d.oy - 1 : 0);
-  if (!live) return;
-  if (lane >= d.ox && lane < d.ox + d.obx) {
+  words_to_lds<S, BT::NL>(L.cp, coup + d.coff, bx * by, t.lane);
+  zero_slots(L.vv, K * vec_words<NB>());
+  pair_sync<BT::ENDS>();
+  box_solve_k<T, S, NB, K, double>(in, nx, work, bx, L.vv, L.other, L.cp, dinv + d.doff, bx, by,
+                                   d.bs, t.r, t.hf, t.end, t.live, d.pin != 0,
+                                   trace_lo(d), trace_hi(d));
+  if (t.live && t.r >= d.ox && t.r < d.ox + d.obx) {
     const long long o2 = origin + (long long)d.oy * nx;
 #pragma unroll 1
     for (int k = 0; k < K; ++k)
-      for (int j = 0; j < d.oby; ++j)
-        p.v[k][o2 + (long long)j * nx + lane] = work[k][(long long)(d.oy + j) * bx + lane];
+      for (int j = t.set; j < d.oby; j += BT::NSET)
+        p.v[k][o2 + (long long)j * nx + t.r] = work[k][(long long)(d.oy + j) * bx + t.r];
   }
-  for (int kd = dof_off[i] + lane; kd < dof_off[i + 1]; kd += GS) {
-    const int side = dof_side[kd], q = dof_q[kd];
-    const double* fw = face_w + 4LL * dof_face0[kd];
+  const int k0 = dof_off[t.i], nd = dof_off[t.i + 1] - k0;
+  if (nd > 0)
 #pragma unroll 1
     for (int k = 0; k < K; ++k) {
-      const T* wk = work[k];
-      double su, sp;
-      trace_moments(d, side, q, fw, [&](int c) { return (double)wk[c]; }, su, sp);
-      mU[(long long)k * nc + kd] = su;
-      mP[(long long)k * nc + kd] = sp;
+      const T* wk = e.v[k] + d.coff;
+      trace_moments<BT::ENDS>(d, t.lane, t.live, dof_side, dof_q, dof_face0, k0, nd,
+                                      face_w, reinterpret_cast<double*>(L.cp),
+                                      [&](int c) { return (double)wk[c]; },
+                                      mU + (long long)k * nc, mP + (long long)k * nc);
     }
-  }
 }
 
 // k_patch for K right-hand sides: e_k = A[S_i]^-1 rho_k[S_i], built in the
 // patch's slice of the scratch vectors (offset coff, row stride bx), then
 // p_k += e_k on the owned cells.
-template <typename T, typename S, int NB, int K, int GS = (NB <= 16 ? 16 : NB <= 32 ? 32 : 64)>
+template <typename T, typename S, int NB, int K>
 __global__ void __launch_bounds__(kBoxThreads)
     k_patch_k(const BoxDesc* __restrict__ boxes, int m, int group_bytes,
               const S* __restrict__ dinv, const S* __restrict__ coup, RhsPtrs<const T> rho,
               RhsPtrs<T> p, RhsPtrs<T> e, int nx) {
   extern __shared__ __align__(16) char smem_raw[];
-  const int grp = threadIdx.x / GS, lane = threadIdx.x % GS;
-  const int i0 = blockIdx.x * (blockDim.x / GS) + grp;
-  const bool live = i0 < m;
-  const int i = live ? i0 : m - 1;
-  BoxSlotK<T, S, NB, GS, K> L(smem_raw + (long long)grp * group_bytes);
-  const BoxDesc d = boxes[i];
+  typedef BoxThread<S, NB> BT;
+  const BT t(blockIdx.x, m);
+  BoxSlotK<T, S, NB, K> L(smem_raw + (long long)t.slot * group_bytes, t.end);
+  const BoxDesc d = boxes[t.i];
   const int bx = d.bx, by = d.by;
   const long long origin = (long long)d.y0 * nx + d.x0;
   const T* in[K];
@@ -1636,21 +1962,24 @@ __global__ void __launch_bounds__(kBoxThreads)
     in[k] = rho.v[k] + origin;
     work[k] = e.v[k] + d.coff;
   }
-  words_to_lds<S, GS>(L.cp, coup + d.coff, bx * by, lane, live);
-  zero_slots<T, GS>(L.vv, K * vec_words<NB, GS>(), lane);
-  wave_sync();
-  box_solve_k<T, S, NB, GS, K, T>(in, nx, work, bx, L.vv, L.cp, dinv + d.doff, bx, by, d.bs,
-                                  lane, (threadIdx.x & 63) - lane, live, live && d.pin, d.oy);
-  // p += e on the owned cells, eight rows of read-modify-write in flight
-  const bool own = live && lane >= d.ox && lane < d.ox + d.obx;
-  const int col = own ? lane : d.ox;
+  words_to_lds<S, BT::NL>(L.cp, coup + d.coff, bx * by, t.lane);
+  zero_slots(L.vv, K * vec_words<NB>());
+  pair_sync<BT::ENDS>();
+  box_solve_k<T, S, NB, K, T>(in, nx, work, bx, L.vv, L.other, L.cp, dinv + d.doff, bx, by,
+                              d.bs, t.r, t.hf, t.end, t.live, d.pin != 0, d.oy,
+                              d.oy + d.oby - 1);
+  // p += e on the owned cells, each set of row lanes a run of eight rows in
+  // turn, all of a run's read-modify-writes in flight
+  const bool own = t.live && t.r >= d.ox && t.r < d.ox + d.obx;
+  const int col = own ? t.r : d.ox;
   const long long o2 = origin + (long long)d.oy * nx;
-  const int rows = wave_max(live ? d.oby : 0);
+  const int rows = d.oby;
 #pragma unroll 1
   for (int k = 0; k < K; ++k) {
     T* pk = p.v[k];
     const T* ek = work[k] + (long long)d.oy * bx;
-    for (int j0 = 0; j0 < rows; j0 += 8) {
+    for (int jj = 0; jj < rows; jj += 8 * BT::NSET) {
+      const int j0 = jj + 8 * t.set;
       T v[8], ev[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
@@ -1660,7 +1989,7 @@ __global__ void __launch_bounds__(kBoxThreads)
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        if (own && j0 + u < d.oby) pk[o2 + (long long)(j0 + u) * nx + lane] = v[u] + ev[u];
+        if (own && j0 + u < d.oby) pk[o2 + (long long)(j0 + u) * nx + t.r] = v[u] + ev[u];
     }
   }
 }
@@ -2038,64 +2367,97 @@ void launch_rhs(const double* tx, const double* ty, int nx, int ny, const int* b
                      bc[1], bc[2], bc[3], f, g, h, b);
 }
 
-// Column-buffer width (registers) and lane-group size for boxes up to max_bx
-// cells wide.
+// Column width (registers) for boxes up to max_bx cells wide, row lanes of a
+// group, and threads of one box (a wave per end of its factor: two where the
+// factors are FP64); w: bytes of the factor storage type.
 inline int col_width(int max_bx) { return box_cols(max_bx); }
-inline int group_size(int max_bx) { return max_bx <= 16 ? 16 : max_bx <= 32 ? 32 : 64; }
+inline int row_lanes(int max_bx) { return max_bx <= 32 ? 32 : 64; }
+inline int ends_of(size_t w) { return w == 8 ? 2 : 1; }
+inline int box_threads(size_t w) { return 64 * ends_of(w); }
 // Words of a group's vector slot (vec_words of the kernels).
 inline int vec_slot_words(int max_bx) {
-  return (col_width(max_bx) / 2 + 2 * group_size(max_bx) + 3) / 4 * 4;
+  return (col_width(max_bx) / 2 + 2 * row_lanes(max_bx) + 3) / 4 * 4;
 }
 // Words of S in 16 bytes; x rounded up to a multiple of them.
 inline int round16(long long x, size_t w) {
   const long long e = 16 / (long long)w;
   return (int)((x + e - 1) / e * e);
 }
-// LDS bytes of one lane group: broadcast slot and box (arithmetic words t)
-// and the couplings (storage words w), rounded to 16 bytes.
+// Words of a box's coupling area: the couplings, or the trace moments' buffer
+// (three FP64 words per thread of the box) where that is larger.
+inline int coupling_words(int max_cells, size_t w) {
+  const long long buf = 3LL * box_threads(w) * (8 / (long long)w);
+  return round16(max_cells > buf ? max_cells : buf, w);
+}
+// LDS bytes of one box: the vector slots of its groups and the box
+// (arithmetic words t) and the coupling area (storage words w), rounded to 16
+// bytes.
 inline size_t group_bytes(int max_bx, int max_cells, size_t t, size_t w) {
-  const size_t b = (size_t)vec_slot_words(max_bx) * t + (size_t)round16(max_cells, w) * w +
-                   (size_t)max_cells * t;
+  const size_t b = (size_t)ends_of(w) * vec_slot_words(max_bx) * t +
+                   (size_t)coupling_words(max_cells, w) * w + (size_t)max_cells * t;
   return (b + 15) / 16 * 16;
 }
-// Lane groups per workgroup: up to 256 threads, fewer when the boxes' LDS
-// would exceed 64 KB (0 when even one group does not fit).
+// Boxes are accepted up to this much LDS for one vector slot, the couplings and
+// the box; a launch may ask for more (second slot, moments' buffer).
+constexpr size_t kBoxLds = 64 * 1024, kBoxLdsMax = kBoxLds + 8192;
+inline bool box_fits(int max_bx, int max_cells, size_t t, size_t w) {
+  const size_t b = (size_t)vec_slot_words(max_bx) * t + (size_t)round16(max_cells, w) * w +
+                   (size_t)max_cells * t;
+  return (b + 15) / 16 * 16 <= kBoxLds;
+}
+// Boxes per workgroup: up to 256 threads, fewer when the boxes' LDS would
+// exceed 64 KB (0 when even one box does not fit).
 int box_groups(int max_bx, int max_cells, size_t t, size_t w) {
-  const int gs = group_size(max_bx);
-  for (int groups = kBoxThreads / gs; groups >= 1; groups /= 2)
-    if (groups * group_bytes(max_bx, max_cells, t, w) <= 64 * 1024) return groups;
-  return 0;
+  const int bt = box_threads(w);
+  for (int groups = kBoxThreads / bt; groups > 1; groups /= 2)
+    if (groups * group_bytes(max_bx, max_cells, t, w) <= kBoxLds) return groups;
+  return box_fits(max_bx, max_cells, t, w) ? 1 : 0;
 }
 size_t box_lds_bytes(int max_bx, int max_cells, size_t t, size_t w) {
-  const int groups = box_groups(max_bx, max_cells, t, w);
-  return groups ? groups * group_bytes(max_bx, max_cells, t, w) : ~(size_t)0;
+  return box_fits(max_bx, max_cells, t, w) ? box_groups(max_bx, max_cells, t, w) *
+                                                 group_bytes(max_bx, max_cells, t, w)
+                                           : ~(size_t)0;
 }
-#define MRCM_BOX_DISPATCH(KERNEL, T, S, max_bx, ...)                                      \
-  do {                                                                                   \
-    switch (col_width(max_bx)) {                                                         \
-      case 16: hipLaunchKernelGGL((KERNEL<T, S, 16>), __VA_ARGS__); break;               \
-      case 20: hipLaunchKernelGGL((KERNEL<T, S, 20>), __VA_ARGS__); break;               \
-      case 24: hipLaunchKernelGGL((KERNEL<T, S, 24>), __VA_ARGS__); break;               \
-      case 32: hipLaunchKernelGGL((KERNEL<T, S, 32>), __VA_ARGS__); break;               \
-      case 36: hipLaunchKernelGGL((KERNEL<T, S, 36>), __VA_ARGS__); break;               \
-      case 40: hipLaunchKernelGGL((KERNEL<T, S, 40>), __VA_ARGS__); break;               \
-      case 48: hipLaunchKernelGGL((KERNEL<T, S, 48>), __VA_ARGS__); break;               \
-      default: hipLaunchKernelGGL((KERNEL<T, S, 64>), __VA_ARGS__); break;               \
-    }                                                                                    \
+// Launch a box kernel with shm bytes of LDS (past 64 KB gfx950 has to be asked).
+template <typename... A, typename... B>
+void launch_box(void (*kernel)(A...), dim3 grid, dim3 block, size_t shm, hipStream_t s,
+                B... args) {
+  if (shm > kBoxLds)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBoxLdsMax);
+  hipLaunchKernelGGL(kernel, grid, block, shm, s, args...);
+}
+#define MRCM_BOX_DISPATCH(KERNEL, T, S, max_bx, ...)                     \
+  do {                                                                         \
+    switch (col_width(max_bx)) {                                               \
+      case 16: launch_box(KERNEL<T, S, 16>, __VA_ARGS__); break;               \
+      case 20: launch_box(KERNEL<T, S, 20>, __VA_ARGS__); break;               \
+      case 24: launch_box(KERNEL<T, S, 24>, __VA_ARGS__); break;               \
+      case 32: launch_box(KERNEL<T, S, 32>, __VA_ARGS__); break;               \
+      case 36: launch_box(KERNEL<T, S, 36>, __VA_ARGS__); break;               \
+      case 40: launch_box(KERNEL<T, S, 40>, __VA_ARGS__); break;               \
+      case 48: launch_box(KERNEL<T, S, 48>, __VA_ARGS__); break;               \
+      default: launch_box(KERNEL<T, S, 64>, __VA_ARGS__); break;               \
+    }                                                                          \
   } while (0)
+// Boxes per workgroup of a launch over m boxes: few boxes get a workgroup each, so
+// that they spread over the CUs (up to four waves per CU).
+inline int launch_groups(int m, int max_bx, int max_cells, size_t t, size_t w) {
+  if ((long long)m * box_threads(w) <= 4LL * 64 * 256) return 1;
+  return box_groups(max_bx, max_cells, t, w);
+}
 template <typename T, typename S>
 void launch_local(const BoxDesc* boxes, int m, int max_cells, int max_bx, const S* dinv,
                   const S* coup, const double* r, T* p, int nx, const int* dof_off,
                   const int* dof_side, const int* dof_q, const int* dof_face0,
                   const double* face_w, double* mU, double* mP, hipStream_t s, int groups_cap) {
-  int groups = box_groups(max_bx, max_cells, sizeof(T), sizeof(S));
+  int groups = launch_groups(m, max_bx, max_cells, sizeof(T), sizeof(S));
   if (groups_cap > 0 && groups_cap < groups) groups = groups_cap;
   const int gb = (int)group_bytes(max_bx, max_cells, sizeof(T), sizeof(S));
   const size_t shm = (size_t)groups * gb;
-  const int cp_words = round16(max_cells, sizeof(S));
-  const dim3 grid((m + groups - 1) / groups), block(groups * group_size(max_bx));
-  MRCM_BOX_DISPATCH(k_local, T, S, max_bx, grid, block, shm, s, boxes, m, gb, cp_words,
-                    dinv, coup, r, p, nx, dof_off, dof_side, dof_q, dof_face0, face_w, mU, mP);
+  const int cp_words = coupling_words(max_cells, sizeof(S));
+  const dim3 grid((m + groups - 1) / groups), block(groups * box_threads(sizeof(S)));
+  MRCM_BOX_DISPATCH(k_local, T, S, max_bx, grid, block, shm, s, boxes, m, gb, cp_words, dinv, coup, r, p, nx, dof_off, dof_side, dof_q, dof_face0, face_w, mU, mP);
 }
 
 void launch_coarse_rhs(const int4* gsrc, const double* gscale, const double* mU,
@@ -2160,14 +2522,13 @@ void launch_residual(const T* tx, const T* ty, int nx, int ny, const double* r, 
 template <typename T, typename S>
 void launch_patch(const BoxDesc* boxes, int m, int max_cells, int max_bx, const S* dinv,
                   const S* coup, const T* rho, T* p, int nx, hipStream_t s, int groups_cap) {
-  int groups = box_groups(max_bx, max_cells, sizeof(T), sizeof(S));
+  int groups = launch_groups(m, max_bx, max_cells, sizeof(T), sizeof(S));
   if (groups_cap > 0 && groups_cap < groups) groups = groups_cap;
   const int gb = (int)group_bytes(max_bx, max_cells, sizeof(T), sizeof(S));
   const size_t shm = (size_t)groups * gb;
-  const int cp_words = round16(max_cells, sizeof(S));
-  const dim3 grid((m + groups - 1) / groups), block(groups * group_size(max_bx));
-  MRCM_BOX_DISPATCH(k_patch, T, S, max_bx, grid, block, shm, s, boxes, m, gb, cp_words,
-                    dinv, coup, rho, p, nx);
+  const int cp_words = coupling_words(max_cells, sizeof(S));
+  const dim3 grid((m + groups - 1) / groups), block(groups * box_threads(sizeof(S)));
+  MRCM_BOX_DISPATCH(k_patch, T, S, max_bx, grid, block, shm, s, boxes, m, gb, cp_words, dinv, coup, rho, p, nx);
 }
 
 // ---- K right-hand sides per launch ----
@@ -2183,12 +2544,13 @@ void check_k(int k) {
     throw Error(MRCM_EINVAL, "multi-RHS launch of unsupported width");
 }
 inline size_t group_bytes_k(int k, int max_bx, int max_cells, size_t t, size_t w) {
-  const size_t b = (size_t)k * vec_slot_words(max_bx) * t + (size_t)round16(max_cells, w) * w;
+  const size_t b = (size_t)ends_of(w) * k * vec_slot_words(max_bx) * t +
+                   (size_t)coupling_words(max_cells, w) * w;
   return (b + 15) / 16 * 16;
 }
 int box_groups_k(int k, int max_bx, int max_cells, size_t t, size_t w) {
-  const int gs = group_size(max_bx);
-  for (int groups = kBoxThreads / gs; groups >= 1; groups /= 2)
+  const int bt = box_threads(w);
+  for (int groups = kBoxThreads / bt; groups >= 1; groups /= 2)
     if (groups * group_bytes_k(k, max_bx, max_cells, t, w) <= 64 * 1024) return groups;
   return 0;
 }
@@ -2255,7 +2617,7 @@ void launch_local_k(int k, const BoxDesc* boxes, int m, int max_cells, int max_b
     const int groups = box_groups_k(kk, max_bx, max_cells, sizeof(T), sizeof(S));
     const size_t shm = box_lds_bytes_k(kk, max_bx, max_cells, sizeof(T), sizeof(S));
     const int gb = (int)group_bytes_k(kk, max_bx, max_cells, sizeof(T), sizeof(S));
-    const dim3 grid((m + groups - 1) / groups), block(groups * group_size(max_bx));
+    const dim3 grid((m + groups - 1) / groups), block(groups * box_threads(sizeof(S)));
     const RhsPtrs<const double> rp = rhs_ptrs(kk, r + k0);
     const RhsPtrs<T> pp = rhs_ptrs(kk, p + k0), ep = rhs_ptrs(kk, e + k0);
     MRCM_BOX_DISPATCH_K(k_local_k, T, S, nb, kk, grid, block, shm, s, boxes, m, gb, dinv, coup,
@@ -2374,7 +2736,7 @@ void launch_patch_k(int k, const BoxDesc* boxes, int m, int max_cells, int max_b
     const int groups = box_groups_k(kk, max_bx, max_cells, sizeof(T), sizeof(S));
     const size_t shm = box_lds_bytes_k(kk, max_bx, max_cells, sizeof(T), sizeof(S));
     const int gb = (int)group_bytes_k(kk, max_bx, max_cells, sizeof(T), sizeof(S));
-    const dim3 grid((m + groups - 1) / groups), block(groups * group_size(max_bx));
+    const dim3 grid((m + groups - 1) / groups), block(groups * box_threads(sizeof(S)));
     const RhsPtrs<const T> rp = rhs_ptrs(kk, rho + k0);
     const RhsPtrs<T> pp = rhs_ptrs(kk, p + k0), ep = rhs_ptrs(kk, e + k0);
     MRCM_BOX_DISPATCH_K(k_patch_k, T, S, nb, kk, grid, block, shm, s, boxes, m, gb, dinv, coup,
@@ -2470,13 +2832,13 @@ __device__ __forceinline__ Blk many_blk(const int* __restrict__ pre, int c) {
   return Blk{(int)blockIdx.x - pre[c], pre[c + 1] - pre[c]};
 }
 
-template <typename T, typename S, int NB, int GS = (NB <= 16 ? 16 : NB <= 32 ? 32 : 64)>
+template <typename T, typename S, int NB>
 __global__ void __launch_bounds__(kBoxThreads)
     k_local_many(const ManyCol* __restrict__ cols, const int* __restrict__ pre, int ncol,
                  int group_bytes, int cp_words) {
   const int c = many_col(pre, ncol, blockIdx.x);
   const ManyCol& a = cols[c];
-  local_body<T, S, NB, GS>(many_blk(pre, c), a.lbox, a.m, group_bytes, cp_words,
+  local_body<T, S, NB>(many_blk(pre, c), a.lbox, a.m, group_bytes, cp_words,
                            static_cast<const S*>(a.ldinv), static_cast<const S*>(a.lcoup), a.r,
                            static_cast<T*>(a.p), a.nx, a.dof_off, a.dof_side, a.dof_q,
                            a.dof_face0, a.face_w, a.mU, a.mP);
@@ -2540,13 +2902,13 @@ __global__ void __launch_bounds__(kVecThreads)
                    a.nx, a.ny, a.r, static_cast<const T*>(a.p), static_cast<T*>(a.rho));
 }
 
-template <typename T, typename S, int NB, int GS = (NB <= 16 ? 16 : NB <= 32 ? 32 : 64)>
+template <typename T, typename S, int NB>
 __global__ void __launch_bounds__(kBoxThreads)
     k_patch_many(const ManyCol* __restrict__ cols, const int* __restrict__ pre, int ncol,
                  int group_bytes, int cp_words) {
   const int c = many_col(pre, ncol, blockIdx.x);
   const ManyCol& a = cols[c];
-  patch_body<T, S, NB, GS>(many_blk(pre, c), a.pbox, a.m, group_bytes, cp_words,
+  patch_body<T, S, NB>(many_blk(pre, c), a.pbox, a.m, group_bytes, cp_words,
                            static_cast<const S*>(a.pdinv), static_cast<const S*>(a.pcoup),
                            static_cast<const T*>(a.rho), static_cast<T*>(a.p), a.nx);
 }
@@ -2611,9 +2973,10 @@ void launch_local_many(const ManyCol* cols, const int* pre, int ncol, int blocks
   if (blocks <= 0) return;
   const int groups = box_groups(max_bx, max_cells, sizeof(T), sizeof(S));
   const int gb = (int)group_bytes(max_bx, max_cells, sizeof(T), sizeof(S));
-  const int cp_words = round16(max_cells, sizeof(S));
-  MRCM_BOX_DISPATCH(k_local_many, T, S, max_bx, dim3(blocks), dim3(groups * group_size(max_bx)),
-                    (size_t)groups * gb, s, cols, pre, ncol, gb, cp_words);
+  const int cp_words = coupling_words(max_cells, sizeof(S));
+  MRCM_BOX_DISPATCH(k_local_many, T, S, max_bx, dim3(blocks),
+                    dim3(groups * box_threads(sizeof(S))), (size_t)groups * gb, s, cols, pre, ncol,
+                    gb, cp_words);
 }
 void launch_coarse_rhs_many(const ManyCol* cols, const int* pre, int ncol, int blocks,
                             hipStream_t s) {
@@ -2663,9 +3026,10 @@ void launch_patch_many(const ManyCol* cols, const int* pre, int ncol, int blocks
   if (blocks <= 0) return;
   const int groups = box_groups(max_bx, max_cells, sizeof(T), sizeof(S));
   const int gb = (int)group_bytes(max_bx, max_cells, sizeof(T), sizeof(S));
-  const int cp_words = round16(max_cells, sizeof(S));
-  MRCM_BOX_DISPATCH(k_patch_many, T, S, max_bx, dim3(blocks), dim3(groups * group_size(max_bx)),
-                    (size_t)groups * gb, s, cols, pre, ncol, gb, cp_words);
+  const int cp_words = coupling_words(max_cells, sizeof(S));
+  MRCM_BOX_DISPATCH(k_patch_many, T, S, max_bx, dim3(blocks),
+                    dim3(groups * box_threads(sizeof(S))), (size_t)groups * gb, s, cols, pre, ncol,
+                    gb, cp_words);
 }
 template <typename T>
 void launch_sum_many(const ManyCol* cols, const int* pre, int ncol, int blocks, hipStream_t s) {

@@ -5,6 +5,16 @@
 
 namespace mrcm {
 
+// The factor of a cell box of by cell rows (all of its uses on the device): a
+// block LDL^T with the rows as blocks, eliminated from both ends towards a middle
+// row h, D_j^-1 of every row in row order and the couplings T_j
+// (diagonal, between rows j - 1 and j; T_0 = 0):
+//   D_j = A_j - T_j D_{j-1}^-1 T_j            for j < h,
+//   D_j = A_j - T_{j+1} D_{j+1}^-1 T_{j+1}    for j > h,
+// and both terms for j = h.  Factors kept in FP64 are two-ended, h = by / 2;
+// factors stored in FP32 are one-ended, h = by - 1: their rounding belongs to the
+// operator the FP32-storing modes define, which a solve sees.
+//
 // Half-block layout of the symmetric row blocks D_j^-1 (n x n, n <= cols).
 // Lane r of a box keeps the entries D(r, (r + k) mod n) for k = 0 .. cols / 2
 // (the "rows" k of the half block); the entries D(r, r - k) it needs as well
