@@ -6,19 +6,30 @@
 
 namespace mrcm3d {
 
-constexpr int kBox3Threads = 256;  // cells of a box plane, at most (a thread per cell)
+constexpr int kBox3Threads = 256;  // cells of a box plane, at most; threads of a
+                                   // reconstruction workgroup
+constexpr int kBox3MaxThreads = 512;  // threads of a box solve, at most
 constexpr int kMaxBox3Cells = 4096;
 
 // A cell box solved by one workgroup: origin lo and extents n (global),
 // the owned subdomain inside it (olo relative to lo, extents on), the plane
-// size P = n[0] n[1], and the offsets of its D_j^-1 blocks (bz P x P,
-// symmetric) and z-couplings (bz x P) in the factor buffers.
+// size P = n[0] n[1], and the offsets of its D_j^-1 blocks (bz, symmetric P x P,
+// block_words words each) and z-couplings (bz x P) in the factor buffers.
 struct Box3 {
   int lo[3], n[3];
   int olo[3], on[3];
   int P, pin;
   long long doff, coff;
 };
+
+// Words of a stored symmetric P x P block: the 16 x 16 tiles (I, J), J <= I, of its
+// lower triangle, tile row after tile row, the tiles of a row one after the other,
+// each row-major with 16 words a row; the last tile row holds only its P % 16 rows
+// (16 when it divides), columns past P are zero.
+__host__ __device__ constexpr int block_words(int P) {
+  const int nt = (P + 15) / 16, last = P - 16 * (nt - 1);
+  return 128 * (nt - 1) * nt + 16 * last * nt;
+}
 
 // A coarse dof's trace table: its side's faces f0 .. f0 + nf (n0 x n1,
 // lower tangential axis fastest) and its tensor Legendre indices (a, b).
@@ -31,7 +42,8 @@ struct Dof3 {
 // trace moments mU, mP of every dof of the box's subdomain; face tables:
 // box-local inside and outside cell, four weights per face).  max_cells and
 // max_plane: the most cells and plane cells of a box of the launch (its LDS
-// and threads, whole waves; at most kMaxBox3Cells and kBox3Threads).
+// and threads, whole waves; cells at most kMaxBox3Cells, plane cells at
+// most kBox3Threads).
 // S: the storage type of the plane blocks (double or float), FP64 arithmetic.
 template <typename S>
 void launch_local3(const Box3* boxes, int m, int max_cells, int max_plane, const S* dinv,

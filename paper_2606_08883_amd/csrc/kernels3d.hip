@@ -1,5 +1,5 @@
 // HIP kernels of the 3-D path (include/mrcm3d.h), FP64: plane-block LDL^T
-// box solves (one workgroup per box, one thread per cell of a plane), trace
+// box solves (one workgroup per box, tiled symmetric plane products), trace
 // moments with tensor Legendre test functions, reconstruction, and the
 // seven-point operator in its forms for smoothing and GMRES (the interface
 // solve runs the level kernels of the 2-D path on the 3-D factor).  Every
@@ -30,91 +30,173 @@ __device__ __forceinline__ long long global_cell(const Box3& d, int q, int nx, i
   return ((long long)(d.lo[2] + z) * ny + (d.lo[1] + y)) * nx + (d.lo[0] + x);
 }
 
-// sum_c D(t, c) v[c] for a block in cyclic-diagonal storage (word d P + t
-// holds D(t, (t + d) mod P), d < P / 2 + 1): diagonal d gives D(t, t + d)
-// v[t + d] from word d P + t and, unless 2 d = P, D(t - d, t) v[t - d] from
-// word d P + t - d, indices mod P.  Consecutive threads read consecutive
-// words of one diagonal in both terms, so each stored word comes from HBM
-// once.  Odd and even d in separate sums, added as (even up + odd up) +
-// (even down + odd down): the host solve's order.
-template <typename S>
-__device__ __forceinline__ double plane_dot(const S* __restrict__ D, const double* v, int P,
-                                            int t) {
-  const int H = P / 2 + 1;
-  double u0 = (double)D[t] * v[t], u1 = 0.0, w0 = 0.0, w1 = 0.0;
-  // kU diagonals per pass, every load of the pass issued before its
-  // multiply-adds (eight for FP32 blocks, which leave the loop latency-bound;
-  // two for FP64, where four and eight measured slower); d starts odd, so
-  // diagonal d + q is odd for even q.  Only the diagonal d = P / 2 of an
-  // even P has no second term, and it is the last: the passes stop before
-  // it, so their loop holds no branch (a branch there made every pass wait
-  // for all of its loads).
-  constexpr int kU = sizeof(S) == 4 ? 8 : 2;
-  const int Hd = P % 2 == 0 ? P / 2 : H;  // diagonals 1 .. Hd - 1 have both terms
-  int d = 1;
-  for (; d + kU <= Hd; d += kU) {
-    double a[kU], b[kU], x[kU], y[kU];
-#pragma unroll
-    for (int q = 0; q < kU; ++q) {
-      int up = t + d + q, dn = t - d - q;
-      if (up >= P) up -= P;
-      if (dn < 0) dn += P;
-      const S* row = D + (long long)(d + q) * P;
-      a[q] = row[t];
-      b[q] = row[dn];
-      x[q] = v[up];
-      y[q] = v[dn];
-    }
-#pragma unroll
-    for (int q = 0; q < kU; ++q) {
-      double& u = q & 1 ? u0 : u1;
-      double& w = q & 1 ? w0 : w1;
-      u = fma(a[q], x[q], u);
-      w = fma(b[q], y[q], w);
-    }
-  }
-  for (; d < H; ++d) {
-    int up = t + d, dn = t - d;
-    if (up >= P) up -= P;
-    if (dn < 0) dn += P;
-    const S* row = D + (long long)d * P;
-    double& u = d & 1 ? u1 : u0;
-    double& w = d & 1 ? w1 : w0;
-    u = fma((double)row[t], v[up], u);
-    if (2 * d != P) w = fma((double)row[dn], v[dn], w);
-  }
-  return (u0 + u1) + (w0 + w1);
+// Four consecutive words of a tile, in FP64.
+struct Quad3 {
+  double v[4];
+};
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void load_words(f64x2 (&d)[2], const double* p) {
+  d[0] = *reinterpret_cast<const f64x2*>(p);
+  d[1] = *reinterpret_cast<const f64x2*>(p + 2);
+}
+__device__ __forceinline__ void load_words(f32x4 (&d)[1], const float* p) {
+  d[0] = *reinterpret_cast<const f32x4*>(p);
+}
+__device__ __forceinline__ Quad3 words(const f64x2 (&d)[2]) {
+  return Quad3{{d[0][0], d[0][1], d[1][0], d[1][1]}};
+}
+__device__ __forceinline__ Quad3 words(const f32x4 (&d)[1]) {
+  return Quad3{{(double)d[0][0], (double)d[0][1], (double)d[0][2], (double)d[0][3]}};
+}
+template <typename S> struct TileRegs;
+template <> struct TileRegs<double> { f64x2 d[2]; };
+template <> struct TileRegs<float> { f32x4 d[1]; };
+
+// Sum of v over the four lanes of a quad, in every lane.
+template <int CTRL>
+__device__ __forceinline__ double quad_perm(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double quad_sum(double v) {
+  v += quad_perm<0xB1>(v);  // lanes 1 0 3 2
+  return v + quad_perm<0x4E>(v);  // lanes 2 3 0 1
 }
 
 // Block LDL^T solve of the box in LDS: us holds b on entry and x on exit in
 // planes stop .. bz - 1 (planes below keep their forward values).
+//
+// A plane's symmetric block D_j^-1 is stored as its 16 x 16 tiles (I, J), J <= I
+// (device3d.h).  One wave takes a tile: lane 4 r + c holds words 4 c .. 4 c + 3 of
+// row r, which give row r's part of D v (from v_J, summed over the quad of lanes)
+// and, off the diagonal, the columns' part (from v_I, summed over the rows once
+// per tile column).  Wave w takes the tile columns w and nt - 1 - w, together
+// nt + 1 tiles in every wave, so the waves of a box are evenly loaded; every part
+// goes to a slot of its own in LDS and row t's thread adds its parts in a fixed
+// order.  A wave has the next TR tiles of its stream (which runs on over the
+// planes and over the turn of the sweep) in flight in registers, across the
+// barriers: the HBM rate, not the latency of a plane step, is what this waits for.
+// One thread per row of the block over its cyclic diagonals, as before, read every
+// word twice through L1 and waited for each pass of loads (96^3 cube, FP64 / FP32
+// words: local 806 / 471 us, patch 737 / 418 us).
 template <typename S>
 __device__ __forceinline__ void plane_solve(double* us, double* v, const Box3& d,
                                             const S* __restrict__ dinv,
                                             const double* __restrict__ coup, int stop) {
-  const int P = d.P, bz = d.n[2], t = threadIdx.x;
-  const long long HP = (long long)(P / 2 + 1) * P;  // words of one stored block
+  constexpr int TR = sizeof(S) == 4 ? 10 : 5;
+  const int P = d.P, bz = d.n[2], t = threadIdx.x, lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int nt = (P + 15) / 16;                     // tile rows
+  const int rows_last = P - 16 * (nt - 1);
+  const int HP = block_words(P);
+  double* rp = v + 16 * nt;                         // [tile (I, J)][row]: row parts
+  double* cp = rp + 8 * nt * (nt + 1);              // [J][row]: column parts
   const S* D = dinv + d.doff;
   const double* T = coup + d.coff;
-  for (int j = 0; j < bz; ++j) {
-    if (t < P) v[t] = j > 0 ? fma(T[(long long)j * P + t], us[(j - 1) * P + t], us[j * P + t])
-                            : us[j * P + t];
+  const int na = nt - w, wb = nt - 1 - w;           // tiles of column w; the second column
+  const int mine = 2 * w > nt - 1 ? 0 : wb == w ? na : nt + 1;
+  const int np = bz + (bz - 1 - stop > 0 ? bz - 1 - stop : 0);
+  const int r = lane >> 2, c4 = 4 * (lane & 3);
+  auto tile = [&](int q, int& I, int& J) {
+    const bool first = q < na;
+    J = first ? w : wb;
+    I = first ? w + q : wb + (q - na);
+  };
+  auto plane = [&](int p) { return p < bz ? p : 2 * (bz - 1) - p; };
+  auto load = [&](TileRegs<S>& reg, int p, int q) {
+    int I, J;
+    tile(q < mine ? q : mine - 1, I, J);
+    const int nr = I == nt - 1 ? rows_last : 16;
+    const int off = 128 * I * (I + 1) + J * nr * 16;
+    const S* at = D + (long long)plane(p < np ? p : np - 1) * HP + off;
+    load_words(reg.d, at + (unsigned)((r < nr ? r : nr - 1) * 16 + c4));
+  };
+  TileRegs<S> reg[TR];
+  if (mine > 0)
+#pragma unroll
+    for (int u = 0; u < TR; ++u) load(reg[u], 0, u);
+  // v of plane 0 (rows past P stay zero)
+  if (t < 16 * nt) v[t] = t < P ? us[t] : 0.0;
+  __syncthreads();
+  for (int p = 0; p < np; ++p) {
+    const int j = plane(p);
+    double cs[4] = {0.0, 0.0, 0.0, 0.0}, x[4] = {0.0, 0.0, 0.0, 0.0};
+    // the sums over the rows of tile column J's words, into cp
+    auto flush = [&](int J) {
+      const bool b5 = lane & 32, b4 = lane & 16;
+      double k0 = b5 ? cs[2] : cs[0], k1 = b5 ? cs[3] : cs[1];
+      k0 += __shfl_xor(b5 ? cs[0] : cs[2], 32, 64);
+      k1 += __shfl_xor(b5 ? cs[1] : cs[3], 32, 64);
+      double k = b4 ? k1 : k0;
+      k += __shfl_xor(b4 ? k0 : k1, 16, 64);
+      k += __shfl_xor(k, 8, 64);
+      k += __shfl_xor(k, 4, 64);
+      if ((lane & 12) == 0) cp[16 * J + c4 + (b5 ? 2 : 0) + (b4 ? 1 : 0)] = k;
+    };
+    for (int q0 = 0; q0 < mine; q0 += TR) {
+#pragma unroll
+      for (int u = 0; u < TR; ++u) {
+        const int q = q0 + u;
+        if (q < mine) {
+          int I, J;
+          tile(q, I, J);
+          if (I == J) {
+            if (q > 0) flush(w);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              x[i] = v[16 * J + c4 + i];
+              cs[i] = 0.0;
+            }
+          }
+          const Quad3 m = words(reg[u].d);
+          double s = m.v[0] * x[0];
+#pragma unroll
+          for (int i = 1; i < 4; ++i) s = fma(m.v[i], x[i], s);
+          s = quad_sum(s);
+          if ((lane & 3) == 0) rp[8 * I * (I + 1) + 16 * J + r] = s;
+          if (I != J) {
+            const double vi = v[16 * I + r];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) cs[i] = fma(m.v[i], vi, cs[i]);
+          }
+        }
+        const bool wrap = q0 + TR >= mine;
+        load(reg[u], wrap ? p + 1 : p, wrap ? u : q + TR);
+      }
+    }
+    if (mine > 0) flush(mine > na ? wb : w);
     __syncthreads();
-    if (t < P) us[j * P + t] = plane_dot(D + j * HP, v, P, t);
-    __syncthreads();
-  }
-  for (int j = bz - 2; j >= stop; --j) {
-    if (t < P) v[t] = T[(long long)(j + 1) * P + t] * us[(j + 1) * P + t];
-    __syncthreads();
-    if (t < P) us[j * P + t] += plane_dot(D + j * HP, v, P, t);
+    if (t < P) {
+      const int I = t >> 4, rt = t & 15;
+      double s = I + 1 < nt ? cp[t] : 0.0;
+      const double* part = rp + 8 * I * (I + 1) + rt;
+      for (int J = 0; J <= I; J += 4) {
+        double e[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[i] = part[16 * (J + i <= I ? J + i : I)];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (J + i <= I) s += e[i];
+      }
+      const double xj = p < bz ? s : us[j * P + t] + s;
+      us[j * P + t] = xj;
+      if (p + 1 < np) {
+        const int jn = plane(p + 1);
+        v[t] = p + 1 < bz ? fma(T[(long long)jn * P + t], xj, us[jn * P + t])
+                          : T[(long long)(jn + 1) * P + t] * xj;
+      }
+    }
     __syncthreads();
   }
 }
 
-// LDS: us[cells] | v[P].  S: the storage type of the plane blocks (FP64 or
-// FP32); the arithmetic is FP64.
+// LDS: us[cells] | v, rp, cp of plane_solve.  S: the storage type of the plane
+// blocks (FP64 or FP32); the arithmetic is FP64.
 template <typename S>
-__global__ void __launch_bounds__(kBox3Threads)
+__global__ void __launch_bounds__(kBox3MaxThreads)
     k_local3(const Box3* __restrict__ boxes, const S* __restrict__ dinv,
              const double* __restrict__ coup, const double* __restrict__ r,
              double* __restrict__ p, int nx, int ny, const int* __restrict__ dof_off,
@@ -139,11 +221,16 @@ __global__ void __launch_bounds__(kBox3Threads)
     const int lq = ((d.olo[2] + z) * d.n[1] + d.olo[1] + y) * d.n[0] + d.olo[0] + x;
     p[global_cell(d, lq, nx, ny)] = us[lq];
   }
-  // trace moments of every dof of the subdomain
-  for (int k = dof_off[i] + threadIdx.x; k < dof_off[i + 1]; k += blockDim.x) {
-    const Dof3 q = dofs[k];
+  // trace moments of every dof of the subdomain, eight lanes to a dof (the 64
+  // faces of a dof one after the other, with a division or two each, took as long
+  // as the solve)
+  const int sub = threadIdx.x & 7;
+  for (int k0 = dof_off[i]; k0 < dof_off[i + 1]; k0 += blockDim.x / 8) {
+    const int k = k0 + (threadIdx.x >> 3);
+    const bool on = k < dof_off[i + 1];
+    const Dof3 q = dofs[on ? k : k0];
     double su = 0.0, sp = 0.0;
-    for (int f = 0; f < q.nf; ++f) {
+    for (int f = sub; f < q.nf; f += 8) {
       const int ff = q.f0 + f;
       const double pin = us[fin[ff]], pout = us[fout[ff]];
       const double bv = legendre_face3(q.a, f % q.n0, q.n0) * legendre_face3(q.b, f / q.n0, q.n1);
@@ -152,13 +239,20 @@ __global__ void __launch_bounds__(kBox3Threads)
       su = fma(bv, U, su);
       sp = fma(bv, Pi, sp);
     }
-    mU[k] = su;
-    mP[k] = sp;
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) {
+      su += __shfl_xor(su, off, 64);
+      sp += __shfl_xor(sp, off, 64);
+    }
+    if (on && sub == 0) {
+      mU[k] = su;
+      mP[k] = sp;
+    }
   }
 }
 
 template <typename S>
-__global__ void __launch_bounds__(kBox3Threads)
+__global__ void __launch_bounds__(kBox3MaxThreads)
     k_patch3(const Box3* __restrict__ boxes, const S* __restrict__ dinv,
              const double* __restrict__ coup, const double* __restrict__ rho,
              double* __restrict__ p, int nx, int ny) {
@@ -317,8 +411,14 @@ inline int grid3(long long n) {
 
 }  // namespace
 
-// Threads of a box launch: one per cell of the widest plane, whole waves.
-inline int box3_threads(int max_plane) { return (max_plane + 63) / 64 * 64; }
+// Threads of a box launch: a wave per two tile columns of the largest plane
+// (which is at least one thread per cell of it), and the LDS of its boxes.
+inline int tile_rows(int max_plane) { return (max_plane + 15) / 16; }
+inline int box3_threads(int max_plane) { return 64 * ((tile_rows(max_plane) + 1) / 2); }
+inline size_t box3_lds(int max_cells, int max_plane) {
+  const int nt = tile_rows(max_plane);
+  return sizeof(double) * ((size_t)max_cells + 16 * nt + 8 * nt * (nt + 1) + 16 * nt);
+}
 
 template <typename S>
 void launch_local3(const Box3* boxes, int m, int max_cells, int max_plane, const S* dinv,
@@ -326,7 +426,7 @@ void launch_local3(const Box3* boxes, int m, int max_cells, int max_plane, const
                    const int* dof_off, const Dof3* dofs, const int* fin, const int* fout,
                    const double* fw, double* mU, double* mP, hipStream_t s) {
   if (m <= 0) return;
-  const size_t shm = sizeof(double) * (max_cells + max_plane);
+  const size_t shm = box3_lds(max_cells, max_plane);
   hipLaunchKernelGGL(k_local3<S>, dim3(m), dim3(box3_threads(max_plane)), shm, s, boxes, dinv,
                      coup, r, p, nx, ny, dof_off, dofs, fin, fout, fw, mU, mP);
 }
@@ -335,7 +435,7 @@ void launch_patch3(const Box3* boxes, int m, int max_cells, int max_plane, const
                    const double* coup, const double* rho, double* p, int nx, int ny,
                    hipStream_t s) {
   if (m <= 0) return;
-  const size_t shm = sizeof(double) * (max_cells + max_plane);
+  const size_t shm = box3_lds(max_cells, max_plane);
   hipLaunchKernelGGL(k_patch3<S>, dim3(m), dim3(box3_threads(max_plane)), shm, s, boxes, dinv,
                      coup, rho, p, nx, ny);
 }

@@ -203,8 +203,8 @@ PlaneFactor factor_box(const Setup& S, const Box& b, bool robin, bool keep_full)
   const int dims[3] = {S.nx, S.ny, S.nz};
   for (int a = 0; a < 3; ++a) whole = whole && b.lo[a] == 0 && b.hi[a] == dims[a];
   F.pin = S.noflow && whole ? 1 : 0;
-  const int H = half_rows(P);
-  F.dinv.assign((size_t)bz * H * P, 0.0);
+  const size_t words = plane_words(P);
+  F.dinv.assign(bz * words, 0.0);
   F.coup.assign((size_t)bz * P, 0.0);
   std::vector<double> D((size_t)P * P), Dp((size_t)P * P);
   for (int j = 0; j < bz; ++j) {
@@ -252,9 +252,14 @@ PlaneFactor factor_box(const Setup& S, const Box& b, bool robin, bool keep_full)
     }
     if (!spd_inverse(D.data(), P))
       throw Error(MRCM_ESINGULAR, "non-positive pivot in a local factorisation");
-    double* Dh = &F.dinv[(size_t)j * H * P];
-    for (int d = 0; d < H; ++d)
-      for (int t = 0; t < P; ++t) Dh[(size_t)d * P + t] = D[(size_t)t * P + (t + d) % P];
+    double* Dh = &F.dinv[j * words];
+    for (int I = 0; I < tile_rows(P); ++I)
+      for (int J = 0; J <= I; ++J) {
+        double* tile = Dh + block_offset(P, I, J);
+        for (int r = 0; r < tile_height(P, I); ++r)
+          for (int c = 0; c < 16 && 16 * J + c < P; ++c)
+            tile[16 * r + c] = D[(size_t)(16 * I + r) * P + 16 * J + c];
+      }
     if (keep_full) F.full.insert(F.full.end(), D.begin(), D.end());
     std::swap(D, Dp);
   }
@@ -291,20 +296,22 @@ long long cell_of(const Setup& S, int x, int y, int z) {
   return ((long long)z * S.ny + y) * S.nx + x;
 }
 
-double plane_dot(const double* D, const double* v, int P, int t) {
-  const int H = half_rows(P);
-  double u0 = D[t] * v[t], u1 = 0.0, w0 = 0.0, w1 = 0.0;
-  int up = t, dn = t;
-  for (int d = 1; d < H; ++d) {
-    up = up + 1 == P ? 0 : up + 1;
-    dn = dn == 0 ? P - 1 : dn - 1;
-    const double* row = D + (size_t)d * P;
-    double& u = d & 1 ? u1 : u0;
-    double& w = d & 1 ? w1 : w0;
-    u = std::fma(row[t], v[up], u);
-    if (2 * d != P) w = std::fma(row[dn], v[dn], w);
-  }
-  return (u0 + u1) + (w0 + w1);
+void block_product(const double* D, const double* v, int P, double* out) {
+  std::fill(out, out + P, 0.0);
+  for (int I = 0; I < tile_rows(P); ++I)
+    for (int J = 0; J <= I; ++J) {
+      const double* tile = D + block_offset(P, I, J);
+      const int nc = std::min(16, P - 16 * J);
+      for (int r = 0; r < tile_height(P, I); ++r) {
+        const double* row = tile + 16 * r;
+        double s = 0.0;
+        for (int c = 0; c < nc; ++c) s = std::fma(row[c], v[16 * J + c], s);
+        out[16 * I + r] += s;
+        if (J < I)
+          for (int c = 0; c < nc; ++c)
+            out[16 * J + c] = std::fma(row[c], v[16 * I + r], out[16 * J + c]);
+      }
+    }
 }
 
 void box_solve_full(const PlaneFactor& F, double* x) {
@@ -332,22 +339,22 @@ void box_solve_full(const PlaneFactor& F, double* x) {
 }
 
 void box_solve(const PlaneFactor& F, double* x) {
-  const int P = F.P, bz = F.bz, H = half_rows(P);
+  const int P = F.P, bz = F.bz;
+  const size_t words = plane_words(P);
   if (F.pin) x[0] = 0.0;
-  std::vector<double> v(P);
+  std::vector<double> v(P), u(P);
   for (int j = 0; j < bz; ++j) {
     double* xj = x + (size_t)j * P;
     for (int c = 0; c < P; ++c)
       v[c] = j > 0 ? std::fma(F.coup[(size_t)j * P + c], x[(size_t)(j - 1) * P + c], xj[c]) : xj[c];
-    const double* D = &F.dinv[(size_t)j * H * P];
-    for (int a = 0; a < P; ++a) xj[a] = plane_dot(D, v.data(), P, a);
+    block_product(&F.dinv[j * words], v.data(), P, xj);
   }
   for (int j = bz - 2; j >= 0; --j) {
     double* xj = x + (size_t)j * P;
     const double* xn = x + (size_t)(j + 1) * P;
     for (int c = 0; c < P; ++c) v[c] = F.coup[(size_t)(j + 1) * P + c] * xn[c];
-    const double* D = &F.dinv[(size_t)j * H * P];
-    for (int a = 0; a < P; ++a) xj[a] += plane_dot(D, v.data(), P, a);
+    block_product(&F.dinv[j * words], v.data(), P, u.data());
+    for (int a = 0; a < P; ++a) xj[a] += u[a];
   }
 }
 
