@@ -1001,21 +1001,12 @@ void ensure_krylov(mrcm_ctx* c, mrcm_ctx::Lane& L, mrcm_ctx::Slot& S, int restar
   S.krylov_cap = restart;
 }
 
-// The rest of Arnoldi step j of a slot after z_j = T v_j: w = A z_j,
+// Step j of a slot after z_j = T v_j, for launch_tail: w = A z_j,
 // modified Gram-Schmidt against v_0..v_j, h_{j+1,j} = ||w||, v_{j+1} =
 // w / h_{j+1,j}; the Hessenberg column is left in S.hcol (j + 2 values).
-void arnoldi_tail(mrcm_ctx* c, mrcm_ctx::Slot& S, int j, int nb, hipStream_t s) {
-  const long long n = c->n;
-  double* zj = S.Z + (size_t)j * n;
-  double* w = S.V + (size_t)(j + 1) * n;
-  mrcm::launch_arnoldi_start(c->tx, c->ty, c->nx, c->ny, zj, w, S.V, S.parts, nb, s);
-  for (int i = 0; i <= j; ++i)
-    mrcm::launch_mgs_step(S.parts + (i % 2) * mrcm::kMaxVecBlocks,
-                          S.parts + ((i + 1) % 2) * mrcm::kMaxVecBlocks, nb, S.hcol, i, w,
-                          S.V + (size_t)i * n, i < j ? S.V + (size_t)(i + 1) * n : nullptr, n,
-                          s);
-  mrcm::launch_norm_scale(S.parts + ((j + 1) % 2) * mrcm::kMaxVecBlocks, nb, S.hcol, j + 1, w,
-                          n, s);
+mrcm::TailCol tail_col(const mrcm_ctx* c, const mrcm_ctx::Slot& S, int j, int nb) {
+  return mrcm::TailCol{c->tx, c->ty, S.Z + (size_t)j * c->n, S.V, S.parts, S.hcol, c->n,
+                       c->nx, c->ny, nb,  j};
 }
 
 // One Arnoldi step of Algorithm 1 for slot 0 of a lane: z_j = T v_j, then
@@ -1023,7 +1014,9 @@ void arnoldi_tail(mrcm_ctx* c, mrcm_ctx::Slot& S, int j, int nb, hipStream_t s) 
 void arnoldi_step(mrcm_ctx* c, mrcm_ctx::Lane& L, int j, int nb, hipStream_t s) {
   mrcm_ctx::Slot& S = L.slots[0];
   apply_dispatch(c, L, S.V + (size_t)j * c->n, S.Z + (size_t)j * c->n, s);
-  arnoldi_tail(c, S, j, nb, s);
+  mrcm::TailCols cols{};
+  cols.c[0] = tail_col(c, S, j, nb);
+  mrcm::launch_tail(cols, 1, s);
 }
 
 // The captured graph of Arnoldi step j of a lane (captured on first use, on
@@ -1196,7 +1189,7 @@ inline int grid_blocks(long long n) {
 // z = T r for every column of one family, each phase one launch over all
 // columns (the steps and per-column arithmetic of apply_one); with tails
 // also the Arnoldi tail of every column at its step j (w = A z_j,
-// Gram-Schmidt, normalisation; the work of arnoldi_tail).
+// Gram-Schmidt, normalisation; the work of launch_tail).
 template <typename T, typename S>
 void apply_family(const std::vector<ManyRef>& refs, ManyTables& tb, hipStream_t s,
                   bool tails) {
@@ -1899,9 +1892,9 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
       fetch(L, S, S.parts, nb);
       R.phase = kBeta;
     };
-    // The lane's Arnoldi steps of this tick: one application of T for all
-    // stepping slots (a captured step when the lane has one slot), then
-    // each slot's tail and the copy of its Hessenberg column.
+    // The lane's Arnoldi steps of this tick: one application of T and one
+    // tail for all stepping slots (a captured step when the lane has one
+    // slot), then the copies of their Hessenberg columns.
     std::vector<const double*> vr(w);
     std::vector<double*> zr(w);
     auto launch_steps = [&](int l) {
@@ -1928,12 +1921,15 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
         return;
       }
       apply_columns(c, L, vr.data(), zr.data(), cnt, L.st);
+      mrcm::TailCols cols{};
+      int k = 0;
+      for (int q = 0; q < w; ++q)
+        if (runs[l][q].step) cols.c[k++] = tail_col(c, L.slots[q], runs[l][q].j, nb);
+      mrcm::launch_tail(cols, k, L.st);
       for (int q = 0; q < w; ++q) {
         Run& R = runs[l][q];
         if (!R.step) continue;
-        mrcm_ctx::Slot& S = L.slots[q];
-        arnoldi_tail(c, S, R.j, nb, L.st);
-        fetch(L, S, S.hcol, R.j + 2);
+        fetch(L, L.slots[q], L.slots[q].hcol, R.j + 2);
         R.step = false;
       }
     };

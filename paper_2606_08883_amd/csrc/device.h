@@ -252,9 +252,21 @@ void launch_resid_norm(const double* tx, const double* ty, int nx, int ny, const
 void launch_scale(double* v, long long n, double alpha, hipStream_t s);
 // v = 0 (a kernel, so that it can be captured in a graph)
 void launch_zero(double* v, long long n, hipStream_t s);
-// w = A z, partials = w . v0
-void launch_arnoldi_start(const double* tx, const double* ty, int nx, int ny, const double* z,
-                          double* w, const double* v0, double* partials, int nb, hipStream_t s);
+// One Arnoldi step of a column after z = T v_j: w = A z in V_{j+1}, modified
+// Gram-Schmidt against v_0 .. v_j, the Hessenberg column in hcol (j + 2 values),
+// v_{j+1} = w / ||w||.  parts: two halves of kMaxVecBlocks partials; nb =
+// vec_blocks(n).
+struct TailCol {
+  const double *tx, *ty, *z;
+  double *V, *parts, *hcol;
+  long long n;
+  int nx, ny, nb, j;
+};
+struct TailCols {
+  TailCol c[kMaxRhs];
+};
+// The step of k <= kMaxRhs columns of one context (one n, each column at its own j).
+void launch_tail(const TailCols& cols, int k, hipStream_t s);
 // h = sum(part_in); hcol[i] = h; w -= h vi; part_out = w . vnext (or w . w when vnext NULL)
 void launch_mgs_step(const double* part_in, double* part_out, int nb, double* hcol, int i,
                      double* w, const double* vi, const double* vnext, long long n,

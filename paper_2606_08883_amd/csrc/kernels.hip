@@ -1481,13 +1481,6 @@ __device__ __forceinline__ void arnoldi_start_body(const Blk blk, const double* 
   s = block_sum(s, red);
   if (threadIdx.x == 0) partials[blk.id] = s;
 }
-__global__ void __launch_bounds__(kVecThreads)
-    k_arnoldi_start(const double* __restrict__ tx, const double* __restrict__ ty, int nx, int ny,
-                    const double* __restrict__ z, double* __restrict__ w,
-                    const double* __restrict__ v0, double* __restrict__ partials) {
-  arnoldi_start_body(hw_blk(), tx, ty, nx, ny, z, w, v0, partials);
-}
-
 // h = sum(part_in) (= w . v_i); hcol[i] = h; w -= h v_i; partial sums of
 // w . v_next, or of w . w when vnext is null.  The vectors' loads do not
 // depend on h: every thread issues its first round before the reduction
@@ -1578,6 +1571,27 @@ __global__ void __launch_bounds__(kVecThreads)
     k_norm_scale(const double* __restrict__ part_in, int nb, double* __restrict__ hcol, int j,
                  double* __restrict__ w, long long n) {
   norm_scale_body(hw_blk(), part_in, nb, hcol, j, w, n);
+}
+
+// The Arnoldi step after z_j = T v_j for the columns of one context (blockIdx.y):
+// each phase one launch over all of them.
+__global__ void __launch_bounds__(kVecThreads) k_tail_start(const TailCols cols) {
+  const TailCol& c = cols.c[blockIdx.y];
+  arnoldi_start_body(hw_blk(), c.tx, c.ty, c.nx, c.ny, c.z, c.V + (long long)(c.j + 1) * c.n, c.V,
+                     c.parts);
+}
+__global__ void __launch_bounds__(kVecThreads) k_tail_mgs(const TailCols cols, int i) {
+  const TailCol& c = cols.c[blockIdx.y];
+  if (i > c.j) return;
+  mgs_step_body(hw_blk(), c.parts + (i % 2) * kMaxVecBlocks,
+                c.parts + ((i + 1) % 2) * kMaxVecBlocks, c.nb, c.hcol, i,
+                c.V + (long long)(c.j + 1) * c.n, c.V + (long long)i * c.n,
+                i < c.j ? c.V + (long long)(i + 1) * c.n : (const double*)nullptr, c.n);
+}
+__global__ void __launch_bounds__(kVecThreads) k_tail_norm(const TailCols cols) {
+  const TailCol& c = cols.c[blockIdx.y];
+  norm_scale_body(hw_blk(), c.parts + ((c.j + 1) % 2) * kMaxVecBlocks, c.nb, c.hcol, c.j + 1,
+                  c.V + (long long)(c.j + 1) * c.n, c.n);
 }
 
 // p += sum_{i < k} y_i Z_i (k <= kMaxUpdate per launch).
@@ -2784,10 +2798,14 @@ void launch_scale(double* v, long long n, double alpha, hipStream_t s) {
   hipLaunchKernelGGL(k_scale, dim3(grid_for(n)), dim3(kVecThreads), 0, s, v, n, alpha);
 }
 
-void launch_arnoldi_start(const double* tx, const double* ty, int nx, int ny, const double* z,
-                          double* w, const double* v0, double* partials, int nb, hipStream_t s) {
-  hipLaunchKernelGGL(k_arnoldi_start, dim3(nb), dim3(kVecThreads), 0, s, tx, ty, nx, ny, z, w, v0,
-                     partials);
+void launch_tail(const TailCols& cols, int k, hipStream_t s) {
+  if (k < 1 || k > kMaxRhs) throw Error(MRCM_EINVAL, "launch of unsupported width");
+  int maxj = 0;
+  for (int i = 0; i < k; ++i) maxj = cols.c[i].j > maxj ? cols.c[i].j : maxj;
+  const dim3 grid(cols.c[0].nb, k), block(kVecThreads);
+  hipLaunchKernelGGL(k_tail_start, grid, block, 0, s, cols);
+  for (int i = 0; i <= maxj; ++i) hipLaunchKernelGGL(k_tail_mgs, grid, block, 0, s, cols, i);
+  hipLaunchKernelGGL(k_tail_norm, grid, block, 0, s, cols);
 }
 
 void launch_mgs_step(const double* part_in, double* part_out, int nb, double* hcol, int i,
