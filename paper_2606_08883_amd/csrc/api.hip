@@ -19,6 +19,7 @@
 #include "coarse.h"
 #include "device.h"
 #include "internal.h"
+#include "mailbox.h"
 #include "setup.h"
 
 namespace {
@@ -247,11 +248,11 @@ struct mrcm_ctx {
     double *contrib = nullptr, *partials = nullptr;
   };
   // One right-hand side in flight in GMRES: its Krylov space (V, Z), the
-  // Hessenberg column and reduction partials, and pinned host buffers.
+  // Hessenberg column and reduction partials, and the scalars for the host.
   struct Slot {
     int krylov_cap = 0;
-    double *V = nullptr, *Z = nullptr, *hcol = nullptr, *parts = nullptr, *yd = nullptr;
-    double *h_fetch = nullptr, *h_y = nullptr;
+    double *V = nullptr, *Z = nullptr, *hcol = nullptr, *parts = nullptr;
+    mrcm::Mailbox mail;
   };
   // A lane: a stream with the work space of one-column and multi-column
   // applications of T and the slots it advances together (one multi-column
@@ -267,6 +268,7 @@ struct mrcm_ctx {
     Batch batch;
     std::vector<Slot> slots;
     std::vector<StepGraph> graphs;  // captured steps of slot 0 (lanes of one slot)
+    bool open = false;  // a solve left the lane before its last scalars arrived
   };
   std::vector<Lane> lanes;
   int max_lanes = 4, batch_width = 4;
@@ -284,7 +286,8 @@ struct mrcm_ctx {
   struct RunSpace {
     Column w;
     int restart = 0;
-    double *V = nullptr, *Z = nullptr, *hcol = nullptr, *parts = nullptr, *yd = nullptr;
+    double *V = nullptr, *Z = nullptr, *hcol = nullptr, *parts = nullptr;
+    mrcm::Mailbox mail;
   };
   std::vector<RunSpace> run_pool;
   // Column tables of the mrcm_apply_many calls this context leads.
@@ -391,11 +394,9 @@ struct mrcm_ctx {
     for (auto& L : lanes) {
       drop_graphs(L);
       if (L.st) (void)hipStreamDestroy(L.st);
-      for (auto& S : L.slots) {
-        if (S.h_fetch) (void)hipHostFree(S.h_fetch);
-        if (S.h_y) (void)hipHostFree(S.h_y);
-      }
+      for (auto& S : L.slots) S.mail.destroy();
     }
+    for (auto& q : run_pool) q.mail.destroy();
     if (ws_in) (void)hipEventDestroy(ws_in);
     if (ws_out) (void)hipEventDestroy(ws_out);
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
@@ -835,18 +836,13 @@ void apply_columns(mrcm_ctx* c, mrcm_ctx::Lane& L, const double* const* r, doubl
   }
 }
 
-// Slots 0 .. count - 1 of a lane exist (reduction partials and pinned host
-// buffers; the Krylov space is sized by ensure_krylov).
+// Slots 0 .. count - 1 of a lane exist (reduction partials and mailboxes; the Krylov space is sized by ensure_krylov).
 void ensure_slots(mrcm_ctx* c, mrcm_ctx::Lane& L, int count) {
   while ((int)L.slots.size() < count) {
     L.slots.emplace_back();
     mrcm_ctx::Slot& S = L.slots.back();
     S.parts = c->alloc<double>(2 * mrcm::kMaxVecBlocks);
-    hip_check(hipHostMalloc((void**)&S.h_fetch, sizeof(double) * (mrcm::kMaxVecBlocks + 256),
-                            hipHostMallocDefault),
-              "hipHostMalloc");
-    hip_check(hipHostMalloc((void**)&S.h_y, sizeof(double) * 256, hipHostMallocDefault),
-              "hipHostMalloc");
+    S.mail.create();
   }
 }
 
@@ -997,16 +993,15 @@ void ensure_krylov(mrcm_ctx* c, mrcm_ctx::Lane& L, mrcm_ctx::Slot& S, int restar
   S.V = c->alloc<double>((size_t)(restart + 1) * c->n);
   S.Z = c->alloc<double>((size_t)restart * c->n);
   S.hcol = c->alloc<double>(restart + 2);
-  S.yd = c->alloc<double>(restart + 1);
   S.krylov_cap = restart;
 }
 
 // Step j of a slot after z_j = T v_j, for launch_tail: w = A z_j,
 // modified Gram-Schmidt against v_0..v_j, h_{j+1,j} = ||w||, v_{j+1} =
-// w / h_{j+1,j}; the Hessenberg column is left in S.hcol (j + 2 values).
+// w / h_{j+1,j}; the Hessenberg column (j + 2 values) goes to the slot's mailbox.
 mrcm::TailCol tail_col(const mrcm_ctx* c, const mrcm_ctx::Slot& S, int j, int nb) {
-  return mrcm::TailCol{c->tx, c->ty, S.Z + (size_t)j * c->n, S.V, S.parts, S.hcol, c->n,
-                       c->nx, c->ny, nb,  j};
+  return mrcm::TailCol{c->tx, c->ty, S.Z + (size_t)j * c->n, S.V, S.parts, S.hcol,
+                       S.mail.h, c->n, c->nx, c->ny, nb, j};
 }
 
 // One Arnoldi step of Algorithm 1 for slot 0 of a lane: z_j = T v_j, then
@@ -1109,7 +1104,7 @@ struct ManyRef {
   const mrcm_ctx::Column* w = nullptr;
   const double* r = nullptr;
   double* z = nullptr;
-  double *V = nullptr, *Z = nullptr, *parts = nullptr, *hcol = nullptr;
+  double *V = nullptr, *Z = nullptr, *parts = nullptr, *hcol = nullptr, *mail = nullptr;
   int j = 0;
 };
 
@@ -1177,6 +1172,7 @@ mrcm::ManyCol many_col_of(const ManyRef& f) {
   a.Z = f.Z;
   a.parts = f.parts;
   a.hcol = f.hcol;
+  a.mail = f.mail;
   a.j = f.j;
   return a;
 }
@@ -1745,9 +1741,9 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
     // Right-hand sides in flight: nl lanes (streams) of w slots each, all
     // ordered after the work the caller's stream holds.  A lane advances its
     // slots in ticks: one multi-column application of T for every slot that
-    // is on an Arnoldi step, then each slot's Gram-Schmidt and the copies of
-    // the scalars the host needs; one synchronisation per tick, after which
-    // the host advances every slot (Givens rotations, restarts, the next
+    // is on an Arnoldi step, then the slots' Gram-Schmidt, whose last kernel
+    // sends the scalars the host needs to the slots' mailboxes; one wait per
+    // tick, after which the host advances every slot (Givens rotations, restarts, the next
     // right-hand side).  One host thread serves the lanes round robin, so
     // while it serves one the others compute.  A right-hand side runs the
     // same kernels in the same order (and the multi-column applications give
@@ -1761,6 +1757,8 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
       mrcm_ctx::Lane& L = c->lanes[l];
       ensure_slots(c, L, w);
       for (int q = 0; q < w; ++q) ensure_krylov(c, L, L.slots[q], restart);
+      if (L.open) hip_check(hipStreamSynchronize(L.st), "hipStreamSynchronize");
+      L.open = true;
       hip_check(hipStreamWaitEvent(L.st, c->ws_in, 0), "hipStreamWaitEvent");
     }
     const long long n = c->n;
@@ -1781,10 +1779,6 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
       std::vector<double> H, cs, sn, gv, y;
     };
     std::vector<std::vector<Run>> runs(nl, std::vector<Run>(w));
-    auto fetch = [&](mrcm_ctx::Lane& L, mrcm_ctx::Slot& S, const double* src, int cnt) {
-      hip_check(hipMemcpyAsync(S.h_fetch, src, sizeof(double) * cnt, hipMemcpyDeviceToHost, L.st),
-                "hipMemcpyAsync");
-    };
     auto finish = [&](Run& R) {
       total_it += R.it;
       all_conv &= R.conv ? 1 : 0;
@@ -1803,16 +1797,15 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
       R.y.assign(restart, 0.0);
       double* pk = p + (size_t)R.k * n;
       hip_check(hipMemsetAsync(pk, 0, sizeof(double) * n, L.st), "hipMemsetAsync");
-      mrcm::launch_sumsq(b + (size_t)R.k * n, n, S.parts, nb, L.st);
-      fetch(L, S, S.parts, nb);
+      mrcm::launch_sumsq(b + (size_t)R.k * n, n, S.mail.post(nb), nb, L.st);
       R.phase = kNormB;
     };
-    // Consume a slot's fetched scalars and launch its next work other than
+    // Consume a slot's scalars and launch its next work other than
     // the application of T (R.step asks for that).
     auto advance = [&](Run& R, mrcm_ctx::Lane& L, mrcm_ctx::Slot& S) {
       const double* bk = b + (size_t)R.k * n;
       double* pk = p + (size_t)R.k * n;
-      const double* hh = S.h_fetch;
+      const double* hh = S.mail.wait(L.st);
       if (R.phase == kNormB) {
         R.bnorm = std::sqrt(host_sum(hh, nb));
         if (R.bnorm == 0.0) {  // p = 0 is exact
@@ -1822,8 +1815,8 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
           return;
         }
         R.tol = rtol * R.bnorm;
-        mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, bk, nullptr, S.V, S.parts, nb, L.st);
-        fetch(L, S, S.parts, nb);
+        mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, bk, nullptr, S.V, S.mail.post(nb), nb,
+                                L.st);
         R.phase = kBeta;
         return;
       }
@@ -1884,17 +1877,13 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
         for (int q = i + 1; q < jj; ++q) sum -= H[(size_t)i * restart + q] * R.y[q];
         R.y[i] = sum / H[(size_t)i * restart + i];
       }
-      std::memcpy(S.h_y, R.y.data(), sizeof(double) * jj);
-      hip_check(hipMemcpyAsync(S.yd, S.h_y, sizeof(double) * jj, hipMemcpyHostToDevice, L.st),
-                "hipMemcpyAsync");
-      mrcm::launch_update(pk, S.Z, S.yd, jj, n, L.st);
-      mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, bk, pk, S.V, S.parts, nb, L.st);
-      fetch(L, S, S.parts, nb);
+      mrcm::launch_update(pk, S.Z, R.y.data(), jj, n, L.st);
+      mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, bk, pk, S.V, S.mail.post(nb), nb, L.st);
       R.phase = kBeta;
     };
     // The lane's Arnoldi steps of this tick: one application of T and one
     // tail for all stepping slots (a captured step when the lane has one
-    // slot), then the copies of their Hessenberg columns.
+    // slot).
     std::vector<const double*> vr(w);
     std::vector<double*> zr(w);
     auto launch_steps = [&](int l) {
@@ -1912,26 +1901,25 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
       if (w == 1) {
         Run& R = runs[l][0];
         mrcm_ctx::StepGraph* sg = step_graph(c, L, R.j, nb);
+        L.slots[0].mail.post(R.j + 2);
         if (sg)
           hip_check(hipGraphLaunch(sg->exec, L.st), "hipGraphLaunch");
         else
           arnoldi_step(c, L, R.j, nb, L.st);
-        fetch(L, L.slots[0], L.slots[0].hcol, R.j + 2);
         R.step = false;
         return;
       }
       apply_columns(c, L, vr.data(), zr.data(), cnt, L.st);
       mrcm::TailCols cols{};
       int k = 0;
-      for (int q = 0; q < w; ++q)
-        if (runs[l][q].step) cols.c[k++] = tail_col(c, L.slots[q], runs[l][q].j, nb);
-      mrcm::launch_tail(cols, k, L.st);
       for (int q = 0; q < w; ++q) {
         Run& R = runs[l][q];
         if (!R.step) continue;
-        fetch(L, L.slots[q], L.slots[q].hcol, R.j + 2);
+        cols.c[k++] = tail_col(c, L.slots[q], R.j, nb);
+        L.slots[q].mail.post(R.j + 2);
         R.step = false;
       }
+      mrcm::launch_tail(cols, k, L.st);
     };
     for (int l = 0; l < nl; ++l) {
       for (int q = 0; q < w && next < nrhs; ++q)
@@ -1945,8 +1933,10 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
         for (const Run& R : runs[l]) live |= R.phase != kIdle;
         if (!live) continue;
         busy = true;
-        hip_check(hipStreamSynchronize(L.st), "hipStreamSynchronize");
-        if (c->timing) c->fold_timing();
+        if (c->timing) {
+          hip_check(hipStreamSynchronize(L.st), "hipStreamSynchronize");
+          c->fold_timing();
+        }
         for (int q = 0; q < w; ++q) {
           Run& R = runs[l][q];
           if (R.phase == kIdle) continue;
@@ -1956,6 +1946,10 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
         launch_steps(l);
       }
       if (!busy) break;
+    }
+    for (int l = 0; l < nl; ++l) {
+      hip_check(hipStreamSynchronize(c->lanes[l].st), "hipStreamSynchronize");
+      c->lanes[l].open = false;
     }
     check_launch();
     if (st) {
@@ -1980,13 +1974,12 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
 
 // ---- batched GMRES over several contexts -----------------------------------
 // Right-hand sides of any number of contexts advance together in ticks.  A
-// tick consumes the scalars the previous tick fetched (norms, Hessenberg
+// tick waits for the scalars of the previous tick (norms, Hessenberg
 // columns), advances every right-hand side on the host exactly as
 // gmres_solve does (Givens rotations, cycle ends, restarts), launches the
 // Arnoldi steps of all of them at once (one launch per phase of T and of the
-// Arnoldi tail over every stepping column, per family of kernel templates),
-// gathers the scalars the host needs next into one staging vector and copies
-// it to the host with one transfer.  Each right-hand side runs the kernels
+// Arnoldi tail over every stepping column, per family of kernel templates); the
+// scalars the host needs next go to each right-hand side's mailbox.  Each right-hand side runs the kernels
 // and arithmetic of gmres_solve in the same order, so its iterates are the
 // same bit for bit.
 struct mrcm_batch {
@@ -1994,10 +1987,6 @@ struct mrcm_batch {
   hipStream_t st = nullptr;
   hipEvent_t ev_in = nullptr;
   ManyTables tables;
-  mrcm::GatherItem *d_items = nullptr, *h_items = nullptr;
-  size_t cap_items = 0;
-  double *d_stage = nullptr, *h_stage = nullptr;
-  size_t cap_stage = 0;
   enum Phase { kNew, kNormB, kBeta, kStep, kDone };
   struct Run {
     mrcm_ctx* c = nullptr;
@@ -2005,17 +1994,14 @@ struct mrcm_batch {
     const double* b = nullptr;
     double* p = nullptr;
     mrcm_ctx::Column w;
-    double *V = nullptr, *Z = nullptr, *hcol = nullptr, *parts = nullptr, *yd = nullptr;
-    double* h_y = nullptr;  // pinned
+    double *V = nullptr, *Z = nullptr, *hcol = nullptr, *parts = nullptr;
+    mrcm::Mailbox mail;
     Phase phase = kNew;
     bool step = false;
     double rtol = 0.0, bnorm = 0.0, tol = 0.0, relres = 1.0;
     int maxit = 0, it = 0, j = 0, cycles = 0, nb = 1;
     bool conv = false;
     std::vector<double> H, cs, sn, gv, y;
-    const double* fsrc = nullptr;  // scalars to fetch this tick
-    int fcnt = 0;
-    long long foff = 0;  // their place in the staging vector
   };
   struct Tag {
     std::vector<Run*> runs;
@@ -2026,12 +2012,7 @@ struct mrcm_batch {
   int next_tag = 1;
   ~mrcm_batch() {
     if (st) (void)hipStreamSynchronize(st);
-    for (auto& R : runs)
-      if (R->h_y) (void)hipHostFree(R->h_y);
-    if (d_items) (void)hipFree(d_items);
-    if (h_items) (void)hipHostFree(h_items);
-    if (d_stage) (void)hipFree(d_stage);
-    if (h_stage) (void)hipHostFree(h_stage);
+    for (auto& R : runs) R->mail.destroy();
     if (ev_in) (void)hipEventDestroy(ev_in);
     if (st) (void)hipStreamDestroy(st);
   }
@@ -2041,15 +2022,9 @@ namespace {
 
 using Run = mrcm_batch::Run;
 
-void batch_fetch(Run& R, const double* src, int cnt) {
-  R.fsrc = src;
-  R.fcnt = cnt;
-}
-
 void batch_finish(mrcm_batch* B, Run& R) {
   R.phase = mrcm_batch::kDone;
   R.step = false;
-  R.fcnt = 0;
   B->tags[R.tag].remaining -= 1;
 }
 
@@ -2061,18 +2036,17 @@ void batch_start(mrcm_batch* B, Run& R) {
   R.gv.assign(B->restart + 1, 0.0);
   R.y.assign(B->restart, 0.0);
   mrcm::launch_zero(R.p, n, B->st);
-  mrcm::launch_sumsq(R.b, n, R.parts, R.nb, B->st);
-  batch_fetch(R, R.parts, R.nb);
+  mrcm::launch_sumsq(R.b, n, R.mail.post(R.nb), R.nb, B->st);
   R.phase = mrcm_batch::kNormB;
 }
 
 // The host part of a tick for one right-hand side (gmres_solve's advance).
-void batch_advance(mrcm_batch* B, Run& R, const double* hh) {
+void batch_advance(mrcm_batch* B, Run& R) {
   mrcm_ctx* c = R.c;
   const long long n = c->n;
   const int restart = B->restart;
   hipStream_t s = B->st;
-  R.fcnt = 0;
+  const double* hh = R.mail.wait(s);
   if (R.phase == mrcm_batch::kNormB) {
     R.bnorm = std::sqrt(host_sum(hh, R.nb));
     if (R.bnorm == 0.0) {  // p = 0 is exact
@@ -2082,8 +2056,8 @@ void batch_advance(mrcm_batch* B, Run& R, const double* hh) {
       return;
     }
     R.tol = R.rtol * R.bnorm;
-    mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, R.b, nullptr, R.V, R.parts, R.nb, s);
-    batch_fetch(R, R.parts, R.nb);
+    mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, R.b, nullptr, R.V, R.mail.post(R.nb), R.nb,
+                            s);
     R.phase = mrcm_batch::kBeta;
     return;
   }
@@ -2140,12 +2114,8 @@ void batch_advance(mrcm_batch* B, Run& R, const double* hh) {
     for (int q = i + 1; q < jj; ++q) sum -= H[(size_t)i * restart + q] * R.y[q];
     R.y[i] = sum / H[(size_t)i * restart + i];
   }
-  std::memcpy(R.h_y, R.y.data(), sizeof(double) * jj);
-  hip_check(hipMemcpyAsync(R.yd, R.h_y, sizeof(double) * jj, hipMemcpyHostToDevice, s),
-            "hipMemcpyAsync");
-  mrcm::launch_update(R.p, R.Z, R.yd, jj, n, s);
-  mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, R.b, R.p, R.V, R.parts, R.nb, s);
-  batch_fetch(R, R.parts, R.nb);
+  mrcm::launch_update(R.p, R.Z, R.y.data(), jj, n, s);
+  mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, R.b, R.p, R.V, R.mail.post(R.nb), R.nb, s);
   R.phase = mrcm_batch::kBeta;
 }
 
@@ -2195,7 +2165,7 @@ int gmres_batch_add(mrcm_batch* B, mrcm_ctx* c, const double* b, double* p, int3
         R->Z = pooled->Z;
         R->hcol = pooled->hcol;
         R->parts = pooled->parts;
-        R->yd = pooled->yd;
+        R->mail = pooled->mail;
         c->run_pool.erase(pooled);
       } else {
         R->w = make_column(c, B->st);
@@ -2203,11 +2173,8 @@ int gmres_batch_add(mrcm_batch* B, mrcm_ctx* c, const double* b, double* p, int3
         R->Z = c->alloc<double>((size_t)B->restart * n);
         R->hcol = c->alloc<double>(B->restart + 2);
         R->parts = c->alloc<double>(2 * mrcm::kMaxVecBlocks);
-        R->yd = c->alloc<double>(B->restart + 1);
+        R->mail.create();
       }
-      hip_check(hipHostMalloc((void**)&R->h_y, sizeof(double) * (B->restart + 1),
-                              hipHostMallocDefault),
-                "hipHostMalloc");
       R->rtol = rtol;
       R->maxit = maxit;
       R->nb = mrcm::vec_blocks(n);
@@ -2228,8 +2195,7 @@ int gmres_batch_add(mrcm_batch* B, mrcm_ctx* c, const double* b, double* p, int3
 int gmres_batch_tick(mrcm_batch* B, int32_t* active) {
   try {
     if (!B) throw mrcm::Error(MRCM_EINVAL, "invalid argument");
-    hip_check(hipStreamSynchronize(B->st), "hipStreamSynchronize");
-    // consume the fetched scalars; start the new right-hand sides
+    // consume the scalars of the last tick; start the new right-hand sides
     for (auto& up : B->runs) {
       Run& R = *up;
       if (R.phase == mrcm_batch::kDone) continue;
@@ -2237,7 +2203,7 @@ int gmres_batch_tick(mrcm_batch* B, int32_t* active) {
         batch_start(B, R);
         continue;
       }
-      batch_advance(B, R, B->h_stage + R.foff);
+      batch_advance(B, R);
     }
     // the Arnoldi steps of every stepping right-hand side
     std::vector<ManyRef> refs;
@@ -2253,53 +2219,14 @@ int gmres_batch_tick(mrcm_batch* B, int32_t* active) {
       f.Z = R.Z;
       f.parts = R.parts;
       f.hcol = R.hcol;
+      f.mail = R.mail.post(R.j + 2);
       f.j = R.j;
       refs.push_back(f);
-      batch_fetch(R, R.hcol, R.j + 2);
       R.step = false;
     }
     if (!refs.empty()) apply_families(refs, B->tables, B->st, true);
-    // gather the scalars of every right-hand side and copy them to the host
-    std::vector<mrcm::GatherItem> items;
-    long long total = 0;
     int live = 0;
-    for (auto& up : B->runs) {
-      Run& R = *up;
-      if (R.phase == mrcm_batch::kDone) continue;
-      ++live;
-      if (R.fcnt <= 0) continue;
-      R.foff = total;
-      items.push_back(mrcm::GatherItem{R.fsrc, total, R.fcnt, 0});
-      total += R.fcnt;
-    }
-    if (!items.empty()) {
-      if (items.size() > B->cap_items) {
-        if (B->d_items) (void)hipFree(B->d_items);
-        if (B->h_items) (void)hipHostFree(B->h_items);
-        B->cap_items = std::max(items.size(), 2 * B->cap_items);
-        hip_check(hipMalloc(&B->d_items, B->cap_items * sizeof(mrcm::GatherItem)), "hipMalloc");
-        hip_check(hipHostMalloc((void**)&B->h_items, B->cap_items * sizeof(mrcm::GatherItem),
-                                hipHostMallocDefault),
-                  "hipHostMalloc");
-      }
-      if ((size_t)total > B->cap_stage) {
-        if (B->d_stage) (void)hipFree(B->d_stage);
-        if (B->h_stage) (void)hipHostFree(B->h_stage);
-        B->cap_stage = std::max((size_t)total, 2 * B->cap_stage);
-        hip_check(hipMalloc(&B->d_stage, B->cap_stage * sizeof(double)), "hipMalloc");
-        hip_check(hipHostMalloc((void**)&B->h_stage, B->cap_stage * sizeof(double),
-                                hipHostMallocDefault),
-                  "hipHostMalloc");
-      }
-      std::memcpy(B->h_items, items.data(), items.size() * sizeof(mrcm::GatherItem));
-      hip_check(hipMemcpyAsync(B->d_items, B->h_items, items.size() * sizeof(mrcm::GatherItem),
-                               hipMemcpyHostToDevice, B->st),
-                "hipMemcpyAsync");
-      mrcm::launch_gather(B->d_items, (int)items.size(), B->d_stage, B->st);
-      hip_check(hipMemcpyAsync(B->h_stage, B->d_stage, total * sizeof(double),
-                               hipMemcpyDeviceToHost, B->st),
-                "hipMemcpyAsync");
-    }
+    for (auto& up : B->runs) live += up->phase != mrcm_batch::kDone;
     check_launch();
     if (active) *active = live;
     return MRCM_OK;
@@ -2353,7 +2280,6 @@ int gmres_batch_remove(mrcm_batch* B, int32_t tag) {
     for (auto r = runs.begin(); r != runs.end();) {
       if ((*r)->tag == tag) {
         Run& R = **r;
-        if (R.h_y) (void)hipHostFree(R.h_y);
         // the buffers go back to the context for its next tags
         mrcm_ctx::RunSpace q;
         q.w = R.w;
@@ -2362,7 +2288,7 @@ int gmres_batch_remove(mrcm_batch* B, int32_t tag) {
         q.Z = R.Z;
         q.hcol = R.hcol;
         q.parts = R.parts;
-        q.yd = R.yd;
+        q.mail = R.mail;
         R.c->run_pool.push_back(q);
         r = runs.erase(r);
       } else {

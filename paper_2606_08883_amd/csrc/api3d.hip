@@ -18,6 +18,7 @@
 
 #include "device.h"
 #include "device3d.h"
+#include "mailbox.h"
 #include "setup3d.h"
 
 namespace {
@@ -68,8 +69,8 @@ struct mrcm3d_ctx {
   double *x = nullptr, *rnd = nullptr, *dx = nullptr, *ybuf = nullptr, *contrib = nullptr;
   double* partials = nullptr;
   int krylov_cap = 0;
-  double *V = nullptr, *Z = nullptr, *hcol = nullptr, *parts = nullptr, *yd = nullptr;
-  double *h_fetch = nullptr, *h_y = nullptr;  // pinned
+  double *V = nullptr, *Z = nullptr, *hcol = nullptr, *parts = nullptr;
+  mrcm::Mailbox mail;  // the scalars of GMRES for the host
   hipStream_t st = nullptr;
   hipEvent_t ev_in = nullptr;
   // per-phase timing: (phase, start, end)
@@ -139,8 +140,7 @@ struct mrcm3d_ctx {
       else
         (void)hipFree(q);
     }
-    if (h_fetch) (void)hipHostFree(h_fetch);
-    if (h_y) (void)hipHostFree(h_y);
+    mail.destroy();
     if (ev_in) (void)hipEventDestroy(ev_in);
     if (st) (void)hipStreamDestroy(st);
   }
@@ -404,11 +404,7 @@ int mrcm3d_setup(const mrcm3d_grid* grid, const mrcm3d_params* params, const dou
            "hipMemsetAsync");
     c->partials = c->alloc<double>(2 * mrcm::kMaxVecBlocks);
     c->parts = c->alloc<double>(2 * mrcm::kMaxVecBlocks);
-    check3(hipHostMalloc((void**)&c->h_fetch, sizeof(double) * (mrcm::kMaxVecBlocks + 256),
-                         hipHostMallocDefault),
-           "hipHostMalloc");
-    check3(hipHostMalloc((void**)&c->h_y, sizeof(double) * 256, hipHostMallocDefault),
-           "hipHostMalloc");
+    c->mail.create();
     check3(hipStreamSynchronize(c->st), "hipStreamSynchronize");
     c->setup_seconds =
         std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -487,15 +483,16 @@ int mrcm3d_gmres_solve(mrcm3d_ctx* c, const double* b, double* p, double rtol, i
       c->V = c->alloc<double>((size_t)(restart + 1) * n);
       c->Z = c->alloc<double>((size_t)restart * n);
       c->hcol = c->alloc<double>(restart + 2);
-      c->yd = c->alloc<double>(restart + 1);
       c->krylov_cap = restart;
     }
     const int nb = mrcm::vec_blocks(n);
-    auto fetch = [&](const double* src, int cnt) {
-      check3(hipMemcpyAsync(c->h_fetch, src, sizeof(double) * cnt, hipMemcpyDeviceToHost, s),
-             "hipMemcpyAsync");
-      check3(hipStreamSynchronize(s), "hipStreamSynchronize");
-      if (c->timing) c->fold();
+    auto fetch = [&]() {
+      const double* h = c->mail.wait(s);
+      if (c->timing) {
+        check3(hipStreamSynchronize(s), "hipStreamSynchronize");
+        c->fold();
+      }
+      return h;
     };
     std::vector<double> H((size_t)(restart + 1) * restart), cs(restart), sn(restart),
         gv(restart + 1), y(restart);
@@ -503,9 +500,8 @@ int mrcm3d_gmres_solve(mrcm3d_ctx* c, const double* b, double* p, double rtol, i
     bool conv = false;
     double relres = 1.0;
     mrcm::launch_zero(p, n, s);
-    mrcm::launch_sumsq(b, n, c->parts, nb, s);
-    fetch(c->parts, nb);
-    const double bnorm = std::sqrt(host_sum3(c->h_fetch, nb));
+    mrcm::launch_sumsq(b, n, c->mail.post(nb), nb, s);
+    const double bnorm = std::sqrt(host_sum3(fetch(), nb));
     if (bnorm == 0.0) {
       conv = true;
       relres = 0.0;
@@ -514,10 +510,9 @@ int mrcm3d_gmres_solve(mrcm3d_ctx* c, const double* b, double* p, double rtol, i
       bool first = true;
       for (;;) {
         mrcm3d::launch_resid_norm3(c->tx, c->ty, c->tz, c->nx, c->ny, c->nz, b,
-                                   first ? nullptr : p, c->V, c->parts, nb, s);
+                                   first ? nullptr : p, c->V, c->mail.post(nb), nb, s);
         first = false;
-        fetch(c->parts, nb);
-        const double beta = std::sqrt(host_sum3(c->h_fetch, nb));
+        const double beta = std::sqrt(host_sum3(fetch(), nb));
         relres = beta / bnorm;
         if (beta <= tol) {
           conv = true;
@@ -543,9 +538,8 @@ int mrcm3d_gmres_solve(mrcm3d_ctx* c, const double* b, double* p, double rtol, i
                                   w, c->V + (size_t)i * n,
                                   i < j ? c->V + (size_t)(i + 1) * n : nullptr, n, s);
           mrcm::launch_norm_scale(c->parts + ((j + 1) % 2) * mrcm::kMaxVecBlocks, nb, c->hcol,
-                                  j + 1, w, n, s);
-          fetch(c->hcol, j + 2);
-          const double* hh = c->h_fetch;
+                                  c->mail.post(j + 2), j + 1, w, n, s);
+          const double* hh = fetch();
           ++it;
           for (int i = 0; i <= j + 1; ++i) H[(size_t)i * restart + j] = hh[i];
           const double hnext = hh[j + 1];
@@ -572,10 +566,7 @@ int mrcm3d_gmres_solve(mrcm3d_ctx* c, const double* b, double* p, double rtol, i
             for (int q = i + 1; q < jj; ++q) sum -= H[(size_t)i * restart + q] * y[q];
             y[i] = sum / H[(size_t)i * restart + i];
           }
-          std::memcpy(c->h_y, y.data(), sizeof(double) * jj);
-          check3(hipMemcpyAsync(c->yd, c->h_y, sizeof(double) * jj, hipMemcpyHostToDevice, s),
-                 "hipMemcpyAsync");
-          mrcm::launch_update(p, c->Z, c->yd, jj, n, s);
+          mrcm::launch_update(p, c->Z, y.data(), jj, n, s);
           break;
         }
       }

@@ -179,15 +179,9 @@ struct ManyCol {
   double *mU, *mP, *xc, *g_nd, *ybuf, *rnd, *dx, *contrib, *partials;
   // GMRES state of the column (batched solves): the Krylov basis V (restart
   // + 1 vectors), Z, the two halves of the reduction partials, the
-  // Hessenberg column and the step j.
-  double *V, *Z, *parts, *hcol;
+  // Hessenberg column, its copy for the host (mailbox.h) and the step j.
+  double *V, *Z, *parts, *hcol, *mail;
   int j, pad;
-};
-// A copy of count doubles from src into a staging vector at dst.
-struct GatherItem {
-  const double* src;
-  long long dst;
-  int count, pad;
 };
 template <typename T, typename S>
 void launch_local_many(const ManyCol* cols, const int* pre, int ncol, int blocks, int max_cells,
@@ -227,7 +221,6 @@ void launch_mgs_step_many(const ManyCol* cols, const int* pre, int ncol, int blo
                           hipStream_t s);
 void launch_norm_scale_many(const ManyCol* cols, const int* pre, int ncol, int blocks,
                             hipStream_t s);
-void launch_gather(const GatherItem* items, int count, double* stage, hipStream_t s);
 
 // ---- set-up on the device (FP64; one wave per box or subdomain) ------------
 // Factor the boxes of `jobs` (LDS: two maxn x maxn blocks); status[0] = 1
@@ -245,20 +238,20 @@ void launch_over_mbf(const SubJob* subs, int m, const OverRhs* rhs, const GamFac
                      S* mbf, double* colU, double* colP, hipStream_t s);
 
 // ---- GMRES vector kernels (FP64) -------------------------------------------
-// r = b - A p (p may be NULL for p = 0); partials[block] = sum r^2
+// r = b - A p (p may be NULL for p = 0); mail[block] = sum r^2, for the host (mailbox.h)
 void launch_resid_norm(const double* tx, const double* ty, int nx, int ny, const double* b,
-                       const double* p, double* r, double* partials, int nb, hipStream_t s);
+                       const double* p, double* r, double* mail, int nb, hipStream_t s);
 // v = alpha * v
 void launch_scale(double* v, long long n, double alpha, hipStream_t s);
 // v = 0 (a kernel, so that it can be captured in a graph)
 void launch_zero(double* v, long long n, hipStream_t s);
 // One Arnoldi step of a column after z = T v_j: w = A z in V_{j+1}, modified
-// Gram-Schmidt against v_0 .. v_j, the Hessenberg column in hcol (j + 2 values),
-// v_{j+1} = w / ||w||.  parts: two halves of kMaxVecBlocks partials; nb =
+// Gram-Schmidt against v_0 .. v_j, the Hessenberg column in hcol and, for the host
+// (mailbox.h), in mail (j + 2 values), v_{j+1} = w / ||w||.  parts: two halves of kMaxVecBlocks partials; nb =
 // vec_blocks(n).
 struct TailCol {
   const double *tx, *ty, *z;
-  double *V, *parts, *hcol;
+  double *V, *parts, *hcol, *mail;
   long long n;
   int nx, ny, nb, j;
 };
@@ -271,13 +264,13 @@ void launch_tail(const TailCols& cols, int k, hipStream_t s);
 void launch_mgs_step(const double* part_in, double* part_out, int nb, double* hcol, int i,
                      double* w, const double* vi, const double* vnext, long long n,
                      hipStream_t s);
-// hn = sqrt(sum(part_in)); hcol[j] = hn; w /= hn (if hn > 0)
-void launch_norm_scale(const double* part_in, int nb, double* hcol, int j, double* w,
-                       long long n, hipStream_t s);
-// p += sum_i y[i] Z_i
+// hn = sqrt(sum(part_in)); mail[i] = hcol[i] (i < j), mail[j] = hn; w /= hn (if hn > 0)
+void launch_norm_scale(const double* part_in, int nb, const double* hcol, double* mail, int j,
+                       double* w, long long n, hipStream_t s);
+// p += sum_i y[i] Z_i (y: k values on the host, read before the call returns)
 void launch_update(double* p, const double* Z, const double* y, int k, long long n,
                    hipStream_t s);
-// partials = sum of squares of x
-void launch_sumsq(const double* x, long long n, double* partials, int nb, hipStream_t s);
+// mail[block] = sum of squares of x, for the host (mailbox.h)
+void launch_sumsq(const double* x, long long n, double* mail, int nb, hipStream_t s);
 
 }  // namespace mrcm

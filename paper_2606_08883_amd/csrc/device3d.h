@@ -74,7 +74,7 @@ void launch_arnoldi_start3(const double* tx, const double* ty, const double* tz,
                            int nz, const double* z, double* w, const double* v0,
                            double* partials, int nb, hipStream_t s);
 void launch_resid_norm3(const double* tx, const double* ty, const double* tz, int nx, int ny,
-                        int nz, const double* b, const double* p, double* r, double* partials,
+                        int nz, const double* b, const double* p, double* r, double* mail,
                         int nb, hipStream_t s);
 
 }  // namespace mrcm3d

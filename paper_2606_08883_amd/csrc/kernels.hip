@@ -31,6 +31,11 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   return s;
 }
 
+// Store a value where the host waits for it (mailbox.h).
+__device__ __forceinline__ void publish(double* place, double v) {
+  __hip_atomic_store(place, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Sum of nb partials, identical order in every block.
 // Elements a thread handles per round of a grid-stride loop: the loads of a
 // round are all issued (indices clamped into range) before any is used, so
@@ -1411,7 +1416,7 @@ __global__ void k_convert(const double* __restrict__ s, float* __restrict__ d, l
 __global__ void __launch_bounds__(kVecThreads)
     k_resid_norm(const double* __restrict__ tx, const double* __restrict__ ty, int nx, int ny,
                  const double* __restrict__ b, const double* __restrict__ p,
-                 double* __restrict__ r, double* __restrict__ partials) {
+                 double* __restrict__ r, double* __restrict__ mail) {
   __shared__ double red[kVecThreads / 64];
   const long long n = (long long)nx * ny, st = (long long)gridDim.x * blockDim.x;
   double s = 0.0;
@@ -1434,7 +1439,7 @@ __global__ void __launch_bounds__(kVecThreads)
     }
   }
   s = block_sum(s, red);
-  if (threadIdx.x == 0) partials[blockIdx.x] = s;
+  if (threadIdx.x == 0) publish(mail + blockIdx.x, s);
 }
 
 __global__ void k_zero(double* __restrict__ v, long long n) {
@@ -1537,10 +1542,12 @@ __global__ void __launch_bounds__(kVecThreads)
   mgs_step_body(hw_blk(), part_in, part_out, nb, hcol, i, w, vi, vnext, n);
 }
 
-// hn = sqrt(sum(part_in)); hcol[j] = hn; w /= hn (if hn > 0).  First round
+// hn = sqrt(sum(part_in)); w /= hn (if hn > 0); block 0 sends the Hessenberg column
+// (hcol[0 .. j), hn) to the host as soon as hn is known.  First round
 // loaded before the reduction, as in k_mgs_step.
 __device__ __forceinline__ void norm_scale_body(const Blk blk, const double* __restrict__ part_in,
-                                                int nb, double* __restrict__ hcol, int j,
+                                                int nb, const double* __restrict__ hcol,
+                                                double* __restrict__ mail, int j,
                                                 double* __restrict__ w, long long n) {
   __shared__ double red[kVecThreads / 64];
   const long long st = (long long)blk.n * blockDim.x;
@@ -1555,7 +1562,10 @@ __device__ __forceinline__ void norm_scale_body(const Blk blk, const double* __r
   const long long start = blk.id * (long long)blockDim.x + threadIdx.x;
   load(start);
   const double hn = sqrt(reduce_partials(part_in, nb, red));
-  if (blk.id == 0 && threadIdx.x == 0) hcol[j] = hn;
+  if (blk.id == 0) {
+    for (int i = threadIdx.x; i < j; i += blockDim.x) publish(mail + i, hcol[i]);
+    if (threadIdx.x == 0) publish(mail + j, hn);
+  }
   if (!(hn > 0.0)) return;
   const double inv = 1.0 / hn;
   for (long long c0 = start; c0 < n; c0 += kRound * st) {
@@ -1568,9 +1578,9 @@ __device__ __forceinline__ void norm_scale_body(const Blk blk, const double* __r
   }
 }
 __global__ void __launch_bounds__(kVecThreads)
-    k_norm_scale(const double* __restrict__ part_in, int nb, double* __restrict__ hcol, int j,
-                 double* __restrict__ w, long long n) {
-  norm_scale_body(hw_blk(), part_in, nb, hcol, j, w, n);
+    k_norm_scale(const double* __restrict__ part_in, int nb, const double* __restrict__ hcol,
+                 double* __restrict__ mail, int j, double* __restrict__ w, long long n) {
+  norm_scale_body(hw_blk(), part_in, nb, hcol, mail, j, w, n);
 }
 
 // The Arnoldi step after z_j = T v_j for the columns of one context (blockIdx.y):
@@ -1590,14 +1600,17 @@ __global__ void __launch_bounds__(kVecThreads) k_tail_mgs(const TailCols cols, i
 }
 __global__ void __launch_bounds__(kVecThreads) k_tail_norm(const TailCols cols) {
   const TailCol& c = cols.c[blockIdx.y];
-  norm_scale_body(hw_blk(), c.parts + ((c.j + 1) % 2) * kMaxVecBlocks, c.nb, c.hcol, c.j + 1,
-                  c.V + (long long)(c.j + 1) * c.n, c.n);
+  norm_scale_body(hw_blk(), c.parts + ((c.j + 1) % 2) * kMaxVecBlocks, c.nb, c.hcol, c.mail,
+                  c.j + 1, c.V + (long long)(c.j + 1) * c.n, c.n);
 }
 
-// p += sum_{i < k} y_i Z_i (k <= kMaxUpdate per launch).
+// p += sum_{i < k} y_i Z_i (k <= kMaxUpdate per launch; y travels with the launch).
 constexpr int kMaxUpdate = 16;
+struct UpdateY {
+  double v[kMaxUpdate];
+};
 __global__ void k_update(double* __restrict__ p, const double* __restrict__ Z,
-                         const double* __restrict__ y, int k, long long n) {
+                         const UpdateY y, int k, long long n) {
   for (long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x; c < n;
        c += (long long)gridDim.x * blockDim.x) {
     double z[kMaxUpdate];
@@ -1606,14 +1619,14 @@ __global__ void k_update(double* __restrict__ p, const double* __restrict__ Z,
     double s = p[c];
 #pragma unroll
     for (int i = 0; i < kMaxUpdate; ++i)
-      if (i < k) s += y[i] * z[i];
+      if (i < k) s += y.v[i] * z[i];
     p[c] = s;
   }
 }
 
 // partial sums of x^2.
 __global__ void __launch_bounds__(kVecThreads)
-    k_sumsq(const double* __restrict__ x, long long n, double* __restrict__ partials) {
+    k_sumsq(const double* __restrict__ x, long long n, double* __restrict__ mail) {
   __shared__ double red[kVecThreads / 64];
   const long long st = (long long)gridDim.x * blockDim.x;
   double s = 0.0;
@@ -1630,7 +1643,7 @@ __global__ void __launch_bounds__(kVecThreads)
       if (c0 + u * st < n) s += a[u] * a[u];
   }
   s = block_sum(s, red);
-  if (threadIdx.x == 0) partials[blockIdx.x] = s;
+  if (threadIdx.x == 0) publish(mail + blockIdx.x, s);
 }
 
 // ---- several right-hand sides per launch ----------------------------------
@@ -2784,9 +2797,9 @@ void launch_convert(const double* src, float* dst, long long n, hipStream_t s) {
 }
 
 void launch_resid_norm(const double* tx, const double* ty, int nx, int ny, const double* b,
-                       const double* p, double* r, double* partials, int nb, hipStream_t s) {
+                       const double* p, double* r, double* mail, int nb, hipStream_t s) {
   hipLaunchKernelGGL(k_resid_norm, dim3(nb), dim3(kVecThreads), 0, s, tx, ty, nx, ny, b, p, r,
-                     partials);
+                     mail);
 }
 
 void launch_zero(double* v, long long n, hipStream_t s) {
@@ -2815,21 +2828,26 @@ void launch_mgs_step(const double* part_in, double* part_out, int nb, double* hc
                      w, vi, vnext, n);
 }
 
-void launch_norm_scale(const double* part_in, int nb, double* hcol, int j, double* w,
-                       long long n, hipStream_t s) {
-  hipLaunchKernelGGL(k_norm_scale, dim3(nb), dim3(kVecThreads), 0, s, part_in, nb, hcol, j, w, n);
+void launch_norm_scale(const double* part_in, int nb, const double* hcol, double* mail, int j,
+                       double* w, long long n, hipStream_t s) {
+  hipLaunchKernelGGL(k_norm_scale, dim3(nb), dim3(kVecThreads), 0, s, part_in, nb, hcol, mail, j,
+                     w, n);
 }
 
 void launch_update(double* p, const double* Z, const double* y, int k, long long n,
                    hipStream_t s) {
   // in slices of kMaxUpdate vectors: p is updated in the same order
-  for (int i0 = 0; i0 < k; i0 += kMaxUpdate)
+  for (int i0 = 0; i0 < k; i0 += kMaxUpdate) {
+    const int ki = k - i0 < kMaxUpdate ? k - i0 : kMaxUpdate;
+    UpdateY u{};
+    for (int i = 0; i < ki; ++i) u.v[i] = y[i0 + i];
     hipLaunchKernelGGL(k_update, dim3(grid_for(n)), dim3(kVecThreads), 0, s, p,
-                       Z + (long long)i0 * n, y + i0, k - i0 < kMaxUpdate ? k - i0 : kMaxUpdate, n);
+                       Z + (long long)i0 * n, u, ki, n);
+  }
 }
 
-void launch_sumsq(const double* x, long long n, double* partials, int nb, hipStream_t s) {
-  hipLaunchKernelGGL(k_sumsq, dim3(nb), dim3(kVecThreads), 0, s, x, n, partials);
+void launch_sumsq(const double* x, long long n, double* mail, int nb, hipStream_t s) {
+  hipLaunchKernelGGL(k_sumsq, dim3(nb), dim3(kVecThreads), 0, s, x, n, mail);
 }
 
 // ---- launches over several contexts ----------------------------------------
@@ -2974,13 +2992,7 @@ __global__ void __launch_bounds__(kVecThreads)
   const int c = many_col(pre, ncol, blockIdx.x);
   const ManyCol& a = cols[c];
   norm_scale_body(many_blk(pre, c), a.parts + ((a.j + 1) % 2) * kMaxVecBlocks, a.nb, a.hcol,
-                  a.j + 1, a.V + (long long)(a.j + 1) * a.n, a.n);
-}
-
-// One workgroup per item.
-__global__ void k_gather(const GatherItem* __restrict__ items, double* __restrict__ stage) {
-  const GatherItem g = items[blockIdx.x];
-  for (int e = threadIdx.x; e < g.count; e += blockDim.x) stage[g.dst + e] = g.src[e];
+                  a.mail, a.j + 1, a.V + (long long)(a.j + 1) * a.n, a.n);
 }
 
 }  // namespace
@@ -3076,11 +3088,6 @@ void launch_norm_scale_many(const ManyCol* cols, const int* pre, int ncol, int b
   if (blocks <= 0) return;
   hipLaunchKernelGGL(k_norm_scale_many, dim3(blocks), dim3(kVecThreads), 0, s, cols, pre, ncol);
 }
-void launch_gather(const GatherItem* items, int count, double* stage, hipStream_t s) {
-  if (count <= 0) return;
-  hipLaunchKernelGGL(k_gather, dim3(count), dim3(64), 0, s, items, stage);
-}
-
 #define MRCM_INSTANTIATE_TS(T, S)                                                              \
   template void launch_local<T, S>(const BoxDesc*, int, int, int, const S*, const S*,          \
                                    const double*, T*, int, const int*, const int*, const int*,   \

@@ -347,7 +347,7 @@ __device__ __forceinline__ double block_sum3(double v, double* red) {
 }
 
 // mode 0: w = A z, partials of w . v0 (v0 = aux); mode 1: r = b - A p (b when
-// p is NULL; b = aux), partials of r^2.
+// p is NULL; b = aux), partials of r^2, which the host waits for (mailbox.h).
 __global__ void __launch_bounds__(kVec3Threads)
     k_op_reduce3(const double* __restrict__ tx, const double* __restrict__ ty,
                  const double* __restrict__ tz, int nx, int ny, int nz,
@@ -369,7 +369,12 @@ __global__ void __launch_bounds__(kVec3Threads)
     }
   }
   s = block_sum3(s, red);
-  if (threadIdx.x == 0) partials[blockIdx.x] = s;
+  if (threadIdx.x == 0) {
+    if (mode == 0)
+      partials[blockIdx.x] = s;
+    else
+      __hip_atomic_store(partials + blockIdx.x, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 // b = f h^2 plus t_f g_f on every Dirichlet boundary face (t_f = 2 K_c
@@ -479,10 +484,10 @@ void launch_arnoldi_start3(const double* tx, const double* ty, const double* tz,
                      w, v0, partials, 0);
 }
 void launch_resid_norm3(const double* tx, const double* ty, const double* tz, int nx, int ny,
-                        int nz, const double* b, const double* p, double* r, double* partials,
+                        int nz, const double* b, const double* p, double* r, double* mail,
                         int nb, hipStream_t s) {
   hipLaunchKernelGGL(k_op_reduce3, dim3(nb), dim3(kVec3Threads), 0, s, tx, ty, tz, nx, ny, nz, p,
-                     r, b, partials, 1);
+                     r, b, mail, 1);
 }
 
 }  // namespace mrcm3d

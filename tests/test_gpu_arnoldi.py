@@ -57,3 +57,42 @@ def test_arnoldi_step_forms(case):
     print(f"  rel L2 {err:.2e} gate {gate:.2e}", flush=True)
     assert err <= gate
     ctx.close()
+
+
+# a quiet NaN, and the signalling NaN that marks a scalar as not yet written
+NANS = {"quiet": 0x7FF8000000000000, "unset-mark": 0x7FF4A5C3E1D2B697}
+
+
+@pytest.mark.parametrize("kind", NANS)
+def test_nan_right_hand_sides_end(kind):
+    """A right-hand side of NaN runs its steps and ends unconverged: no scalar the host
+    waits for looks as if it had not arrived."""
+    print(f"NaN right-hand side ({kind})", flush=True)
+    dev = torch.device("cuda:0")
+
+    def rhs(k, n):
+        return torch.tensor(np.full((k, n), NANS[kind], dtype=np.uint64).view(np.int64),
+                            device=dev).view(torch.float64)
+
+    ctx = B.Context(B.Config(36, 32, (1, 1, 0, 0), 16, 16, 2, 10.0, 0, 1, 2, 1, 0),
+                    torch.ones(36 * 32, dtype=torch.float64, device=dev))
+    for k in (1, 3):
+        b = rhs(k, ctx.n)
+        p = torch.zeros_like(b)
+        st = ctx.gmres(b, p, rtol=1e-8, restart=2, maxit=3, raise_on_noconv=False)
+        assert not st.converged and st.iterations == 3 * k
+        batch = B.Batch(2)
+        tag = batch.add(ctx, b, p, rtol=1e-8, maxit=3)
+        ticks = 0
+        while batch.tick():
+            ticks += 1
+            assert ticks < 20
+        batch.remove(tag)
+        batch.close()
+    ctx.close()
+    ctx3 = B.Context3(B.Config3(12, 12, 8, (1, 1, 0, 0, 0, 0), 4, 4, 4, 1, 10.0, 0, 1, 1, 1, 0),
+                      torch.ones(12 * 12 * 8, dtype=torch.float64, device=dev))
+    b = rhs(1, ctx3.n)[0]
+    st = ctx3.gmres(b, torch.zeros_like(b), rtol=1e-8, restart=2, maxit=3, raise_on_noconv=False)
+    assert not st.converged and st.iterations == 3
+    ctx3.close()
