@@ -1694,9 +1694,7 @@ int op_apply(mrcm_ctx* c, const double* x, double* y, int32_t nrhs, void* stream
     if (nrhs == 0) return MRCM_OK;
     if (!x || !y) throw mrcm::Error(MRCM_EINVAL, "null vector");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    for (int k = 0; k < nrhs; ++k)
-      mrcm::launch_op_apply(c->tx, c->ty, c->nx, c->ny, x + (size_t)k * c->n,
-                            y + (size_t)k * c->n, s);
+    mrcm::launch_op_apply(c->tx, c->ty, c->nx, c->ny, x, y, nrhs, s);
     check_launch();
     return MRCM_OK;
   } catch (const mrcm::Error& e) {

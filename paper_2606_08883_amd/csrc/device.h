@@ -36,7 +36,7 @@ inline int vec_blocks(long long n) {
 
 // ---- fine operator --------------------------------------------------------
 void launch_op_apply(const double* tx, const double* ty, int nx, int ny, const double* x,
-                     double* y, hipStream_t s);
+                     double* y, int nrhs, hipStream_t s);
 void launch_rhs(const double* tx, const double* ty, int nx, int ny, const int* bc,
                 const double* f, const double* g, double h, double* b, hipStream_t s);
 
