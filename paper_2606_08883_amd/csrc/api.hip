@@ -666,7 +666,8 @@ void autotune(mrcm_ctx* c, hipStream_t s) {
 }
 
 // One application of T with arithmetic / work-vector type T and factor
-// storage type S.
+// storage type S; with z null the result stays in the work vector, its mean not yet
+// taken (launch_tail_finish does the rest).
 template <typename T, typename S>
 void apply_one(mrcm_ctx* c, mrcm_ctx::Lane& L, const double* r, double* z, hipStream_t s) {
   T* p = static_cast<T*>(L.pT);
@@ -707,6 +708,7 @@ void apply_one(mrcm_ctx* c, mrcm_ctx::Lane& L, const double* r, double* z, hipSt
                              c->patch_groups);
     end(4);
   }
+  if (!z) return;
   begin();
   mrcm::launch_finalize<T>(p, c->n, c->noflow, z, L.partials, s);
   end(5);
@@ -1008,10 +1010,21 @@ mrcm::TailCol tail_col(const mrcm_ctx* c, const mrcm_ctx::Slot& S, int j, int nb
 // the tail.
 void arnoldi_step(mrcm_ctx* c, mrcm_ctx::Lane& L, int j, int nb, hipStream_t s) {
   mrcm_ctx::Slot& S = L.slots[0];
-  apply_dispatch(c, L, S.V + (size_t)j * c->n, S.Z + (size_t)j * c->n, s);
-  mrcm::TailCols cols{};
-  cols.c[0] = tail_col(c, S, j, nb);
-  mrcm::launch_tail(cols, 1, s);
+  const double* v = S.V + (size_t)j * c->n;
+  double* z = S.Z + (size_t)j * c->n;
+  const mrcm::TailCol col = tail_col(c, S, j, nb);
+  if (c->timing) {  // the mean is a phase of its own
+    apply_dispatch(c, L, v, z, s);
+    mrcm::TailCols cols{};
+    cols.c[0] = col;
+    mrcm::launch_tail(cols, 1, s);
+    return;
+  }
+  apply_dispatch(c, L, v, nullptr, s);
+  if (c->precision == 1)
+    mrcm::launch_tail_finish(col, static_cast<const float*>(L.pT), c->noflow, z, L.partials, s);
+  else
+    mrcm::launch_tail_finish(col, static_cast<const double*>(L.pT), c->noflow, z, L.partials, s);
 }
 
 // The captured graph of Arnoldi step j of a lane (captured on first use, on

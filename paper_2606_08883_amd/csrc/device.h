@@ -260,6 +260,11 @@ struct TailCols {
 };
 // The step of k <= kMaxRhs columns of one context (one n, each column at its own j).
 void launch_tail(const TailCols& cols, int k, hipStream_t s);
+// The step of one column from T's work vector p (before launch_finalize, whose z it
+// stores; partials: kMaxVecBlocks values).
+template <typename T>
+void launch_tail_finish(const TailCol& col, const T* p, int noflow, double* z, double* partials,
+                        hipStream_t s);
 // h = sum(part_in); hcol[i] = h; w -= h vi; part_out = w . vnext (or w . w when vnext NULL)
 void launch_mgs_step(const double* part_in, double* part_out, int nb, double* hcol, int i,
                      double* w, const double* vi, const double* vnext, long long n,
