@@ -42,6 +42,7 @@ struct mrcm3d_ctx {
   mrcm3d::Box3 *lbox = nullptr, *pbox = nullptr;
   int lmax_cells = 1, pmax_cells = 1;  // the most cells of a box of each list
   int lmax_plane = 1, pmax_plane = 1;  // and the most cells of a plane
+  int own_cells = 1;                   // the most cells of a subdomain
   // plane blocks: double, or float with precision 2
   void *ldinv = nullptr, *pdinv = nullptr;
   double *lcoup = nullptr, *pcoup = nullptr;
@@ -253,8 +254,8 @@ void apply3(mrcm3d_ctx* c, const double* r, double* z) {
     }
     if (e) mark(c, 1, e);
     e = start_mark(c);
-    mrcm3d::launch_reconstruct3(c->lbox, c->m, c->mbf, c->mbf_off, c->dof_off, c->x, c->p, c->nx,
-                                c->ny, s);
+    mrcm3d::launch_reconstruct3(c->lbox, c->m, c->own_cells, c->mbf, c->mbf_off, c->dof_off, c->x,
+                                c->p, c->nx, c->ny, s);
     if (e) mark(c, 2, e);
   }
   for (int k = 0; k < c->sweeps; ++k) {
@@ -326,6 +327,7 @@ int mrcm3d_setup(const mrcm3d_grid* grid, const mrcm3d_params* params, const dou
     if (S.sweeps > 0)
       upload_boxes(c, S, S.pboxes, S.patch, c->pbox, c->pdinv, c->pcoup, c->pmax_cells,
                    c->pmax_plane);
+    for (const auto& b : S.boxes) c->own_cells = std::max(c->own_cells, (int)b.cells());
     // multiscale basis functions
     std::vector<double> mbf;
     std::vector<long long> mbf_off(S.m);

@@ -55,10 +55,10 @@ template <typename S>
 void launch_patch3(const Box3* boxes, int m, int max_cells, int max_plane, const S* dinv,
                    const double* coup, const double* rho, double* p, int nx, int ny,
                    hipStream_t s);
-// p[Omega_i] += P_i x_i (one workgroup per subdomain; mbf_off per subdomain).
-void launch_reconstruct3(const Box3* boxes, int m, const double* mbf, const long long* mbf_off,
-                         const int* dof_off, const double* x, double* p, int nx, int ny,
-                         hipStream_t s);
+// p[Omega_i] += P_i x_i (mbf_off per subdomain; max_owned: the most cells of one).
+void launch_reconstruct3(const Box3* boxes, int m, int max_owned, const double* mbf,
+                         const long long* mbf_off, const int* dof_off, const double* x, double* p,
+                         int nx, int ny, hipStream_t s);
 // Seven-point operator: y = A x; rho = r - A p; w = A z with partial sums of
 // w . v0; r = b - A p (b when p is NULL) with partial sums of r^2.
 void launch_op3(const double* tx, const double* ty, const double* tz, int nx, int ny, int nz,
