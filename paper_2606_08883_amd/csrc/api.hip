@@ -838,7 +838,8 @@ void apply_columns(mrcm_ctx* c, mrcm_ctx::Lane& L, const double* const* r, doubl
   }
 }
 
-// Slots 0 .. count - 1 of a lane exist (reduction partials and mailboxes; the Krylov space is sized by ensure_krylov).
+// Slots 0 .. count - 1 of a lane exist (reduction partials and mailboxes; the
+// Krylov space is sized by ensure_krylov).
 void ensure_slots(mrcm_ctx* c, mrcm_ctx::Lane& L, int count) {
   while ((int)L.slots.size() < count) {
     L.slots.emplace_back();

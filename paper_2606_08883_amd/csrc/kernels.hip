@@ -291,6 +291,21 @@ constexpr int block_regs() {
   return (int)sizeof(S) / 4 *
          (Half<NB>::HV == 1 ? half_rows(NB) : 2 * Half<NB>::NH + (Half<NB>::K0 == 3 ? 2 : 1));
 }
+// Waves per SIMD the compiler may aim for in the one-column box kernels.  Left
+// alone it gives up loads in flight for one wave more: with FP32 factors in FP64
+// arithmetic it held 36- to 64-wide boxes to 110 to 149 registers and waited for
+// each block (T on 512 x 512 in 32-wide subdomains, 64-wide oversampled boxes: 271 us, at
+// two waves 184; 40- and 36-wide boxes with two sweeps 212, 182; 1500 x 1500, one
+// sweep, 429, 410).  The others lose where many boxes share a CU (24-wide FP64 at 1024 x
+// 1024: 75.2 us, at three waves 77.3, at two 84.5; 32-wide FP64 gains 1.5 of
+// 16.6 us for 33 boxes and loses 0.7% of T for 2500).
+template <typename T, typename S, int NB>
+constexpr int box_waves() {
+  return sizeof(T) == 8 && sizeof(S) == 4 && NB >= 36 ? 2 : 8;
+}
+#define MRCM_BOX_KERNEL(T, S, NB)    \
+  __launch_bounds__(kBoxThreads) \
+      __attribute__((amdgpu_waves_per_eu(1, box_waves<T, S, NB>())))
 // Blocks in flight per lane, 2 or 4: as many as about 64 VGPRs of rows hold (more
 // would cost waves per SIMD; 36-wide FP32 patches with four in flight instead
 // of two were a third slower).
@@ -897,7 +912,7 @@ __device__ __forceinline__ void local_body(
                                     [&](int c) { return (double)L.us[c]; }, mU, mP);
 }
 template <typename T, typename S, int NB>
-__global__ void __launch_bounds__(kBoxThreads)
+__global__ void MRCM_BOX_KERNEL(T, S, NB)
     k_local(const BoxDesc* __restrict__ boxes, int m, int group_bytes, int cp_words,
             const S* __restrict__ dinv, const S* __restrict__ coup,
             const double* __restrict__ r, T* __restrict__ p, int nx,
@@ -1390,7 +1405,7 @@ __device__ __forceinline__ void patch_body(const Blk blk, const BoxDesc* __restr
   }
 }
 template <typename T, typename S, int NB>
-__global__ void __launch_bounds__(kBoxThreads)
+__global__ void MRCM_BOX_KERNEL(T, S, NB)
     k_patch(const BoxDesc* __restrict__ boxes, int m, int group_bytes, int cp_words,
             const S* __restrict__ dinv, const S* __restrict__ coup, const T* __restrict__ rho,
             T* __restrict__ p, int nx) {
@@ -2985,7 +3000,7 @@ __device__ __forceinline__ Blk many_blk(const int* __restrict__ pre, int c) {
 }
 
 template <typename T, typename S, int NB>
-__global__ void __launch_bounds__(kBoxThreads)
+__global__ void MRCM_BOX_KERNEL(T, S, NB)
     k_local_many(const ManyCol* __restrict__ cols, const int* __restrict__ pre, int ncol,
                  int group_bytes, int cp_words) {
   const int c = many_col(pre, ncol, blockIdx.x);
@@ -3055,7 +3070,7 @@ __global__ void __launch_bounds__(kVecThreads)
 }
 
 template <typename T, typename S, int NB>
-__global__ void __launch_bounds__(kBoxThreads)
+__global__ void MRCM_BOX_KERNEL(T, S, NB)
     k_patch_many(const ManyCol* __restrict__ cols, const int* __restrict__ pre, int ncol,
                  int group_bytes, int cp_words) {
   const int c = many_col(pre, ncol, blockIdx.x);
