@@ -346,9 +346,9 @@ def boxes3(w, grow: int) -> np.ndarray:
 
 def algorithmic_bytes3(w, coarse_bytes: float) -> dict:
     """Algorithmic bytes of one instance of every phase of the 3-D apply
-    (FP64 throughout).  A box of bx x by x bz cells (plane P = bx by) stores
-    bz symmetric P x P plane blocks by their P / 2 + 1 cyclic diagonals and
-    bz x P couplings; the count reads them once.
+    (FP64 throughout).  A box of bx x by x bz cells (plane P = bx by) has bz
+    symmetric P x P plane blocks, counted as the (P / 2 + 1) P words such a
+    block needs, and bz x P couplings; the count reads them once.
       local       per subdomain on its oversampled box: factor and couplings,
                   r on the box, p written on the owned cells; per trace face
                   its two box-local cells (8 B) and four weights (32 B); per
