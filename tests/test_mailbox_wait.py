@@ -1,0 +1,126 @@
+"""The host's wait for a kernel's scalars (csrc/mailbox.h), compiled here against a stream
+that the test answers for: a waiting thread gives its core to the thread it waits for,
+asks the stream rarely, and ends with an error when the stream's work is done and a
+scalar is missing.
+"""
+import subprocess
+
+import pytest
+
+from paper_2606_08883_amd import build_lib
+
+SOURCE = r"""
+#include <sched.h>
+
+#include <algorithm>
+#include <atomic>
+#include <chrono>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <thread>
+#include <vector>
+
+#include "mailbox.h"
+
+static std::atomic<int> asked{0};
+static std::atomic<int> answer{hipErrorNotReady};
+extern "C" {
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  *p = std::calloc(1, n);
+  return hipSuccess;
+}
+hipError_t hipHostFree(void* p) {
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipStreamQuery(hipStream_t) {
+  ++asked;
+  return (hipError_t)answer.load();
+}
+const char* hipGetErrorString(hipError_t) { return "error"; }
+}
+
+int main(int argc, char** argv) {
+  cpu_set_t one;
+  CPU_ZERO(&one);
+  CPU_SET(sched_getcpu(), &one);
+  if (sched_setaffinity(0, sizeof(one), &one) != 0) return 3;
+  mrcm::Mailbox box;
+  box.create();
+  if (!std::strcmp(argv[1], "missing")) {
+    answer = hipSuccess;
+    box.post(3)[1] = 1.0;
+    try {
+      box.wait(nullptr);
+      std::puts("arrived");
+    } catch (const mrcm::Error& e) {
+      std::printf("error %d\n", e.code);
+    }
+    return 0;
+  }
+  // rounds of scalars from a second thread of the same core
+  const int rounds = 200;
+  std::atomic<int> posted{0};
+  std::thread sender([&] {
+    for (int k = 1; k <= rounds; ++k) {
+      while (posted.load() < k) std::this_thread::yield();
+      for (int i = 0; i < 5; ++i)
+        __atomic_store_n(reinterpret_cast<uint64_t*>(box.h) + i, (uint64_t)(k * 8 + i),
+                         __ATOMIC_RELAXED);
+    }
+  });
+  using clock = std::chrono::steady_clock;
+  auto ms = [](clock::duration d) { return std::chrono::duration<double, std::milli>(d).count(); };
+  const auto t0 = clock::now();
+  std::vector<double> took;
+  bool right = true;
+  for (int k = 1; k <= rounds; ++k) {
+    const auto began = clock::now();
+    box.post(5);
+    posted = k;
+    const double* h = box.wait(nullptr);
+    for (int i = 0; i < 5; ++i) {
+      uint64_t v;
+      std::memcpy(&v, h + i, 8);
+      right = right && v == (uint64_t)(k * 8 + i);
+    }
+    took.push_back(ms(clock::now() - began));
+  }
+  const double all = ms(clock::now() - t0);
+  sender.join();
+  box.destroy();
+  std::sort(took.begin(), took.end());
+  std::printf("right %d median_ms %.4f total_ms %.3f asked %d\n", right ? 1 : 0,
+              took[rounds / 2], all, asked.load());
+  return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("mailbox")
+    src, exe = d / "wait.cpp", d / "wait"
+    src.write_text(SOURCE)
+    r = subprocess.run([build_lib.CXX, "-O2", "-std=c++17", "-D__HIP_PLATFORM_AMD__",
+                        "-I/opt/rocm/include", "-I" + build_lib.CSRC, str(src), "-pthread", "-o",
+                        str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return str(exe)
+
+
+def test_wait_gives_the_core_away(program):
+    r = subprocess.run([program, "rounds"], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0
+    f = r.stdout.split()
+    assert f[1] == "1"
+    # a thread that holds the core is taken off it after a time slice (milliseconds); one
+    # that gives it away waits for a switch (microseconds)
+    assert float(f[3]) < 0.5
+    assert int(f[7]) <= 2 + 2 * float(f[5])
+
+
+def test_wait_ends_with_the_stream(program):
+    r = subprocess.run([program, "missing"], capture_output=True, text=True, timeout=60)
+    assert r.stdout.split() == ["error", "-5"]
