@@ -897,7 +897,7 @@ void device_setup(mrcm_ctx* c, mrcm::HostSetup& S, const double* K_dev, hipStrea
       throw mrcm::Error(MRCM_EINVAL,
                         "oversampled subdomains and smoothing patches must be at most 64 cells "
                         "wide");
-    if (mrcm::box_lds_bytes(max_bx, max_cells, sizeof(W), sizeof(X)) > 64 * 1024)
+    if (mrcm::box_groups(max_bx, max_cells, sizeof(W), sizeof(X)) <= 0)
       throw mrcm::Error(MRCM_EINVAL,
                         "oversampled subdomain or patch too large for the LDS of one workgroup");
   };

@@ -42,12 +42,9 @@ void launch_rhs(const double* tx, const double* ty, int nx, int ny, const int* b
 
 // ---- preconditioner apply (arithmetic T, factor storage S) ------------------
 // A box (at most 64 cells wide) is solved by one lane group per end of its
-// factor; LDS per workgroup: box_lds_bytes() (all ones when a
-// single box is too large).  t, w: bytes of the arithmetic type T and of
-// the factor storage type S.
-size_t box_lds_bytes(int max_bx, int max_cells, size_t t, size_t w);
-// Boxes per workgroup of the box kernels (the most that fit; a launch
-// may take fewer, groups_cap > 0, which changes no result).
+// factor.  Boxes per workgroup of the box kernels (the most that fit; a launch
+// may take fewer, groups_cap > 0, which changes no result); 0 when the boxes are too
+// large.  t, w: bytes of the arithmetic type T and of the factor storage type S.
 int box_groups(int max_bx, int max_cells, size_t t, size_t w);
 // Source-driven solves on the oversampled boxes (boxes[i]: hat-Omega_i with
 // Omega_i as its owned part): p = the solutions restricted to Omega_i, and

@@ -2533,34 +2533,33 @@ inline size_t group_bytes(int max_bx, int max_cells, size_t t, size_t w) {
                    (size_t)coupling_words(max_cells, w) * w + (size_t)max_cells * t;
   return (b + 15) / 16 * 16;
 }
-// Boxes are accepted up to this much LDS for one vector slot, the couplings and
-// the box; a launch may ask for more (second slot, moments' buffer).
+// Boxes are accepted up to kBoxLds bytes for one vector slot of whole lane groups (16
+// lanes for boxes of up to 16 columns), the couplings and the box, which is not what a
+// launch takes: with the second slot, wider slots and the moments' buffer the largest
+// accepted boxes ask for up to kBoxLdsMax (16 x 254 in FP64: 66 176 bytes).
 constexpr size_t kBoxLds = 64 * 1024, kBoxLdsMax = kBoxLds + 8192;
 inline bool box_fits(int max_bx, int max_cells, size_t t, size_t w) {
-  const size_t b = (size_t)vec_slot_words(max_bx) * t + (size_t)round16(max_cells, w) * w +
-                   (size_t)max_cells * t;
+  const int lanes = max_bx <= 16 ? 16 : row_lanes(max_bx);
+  const size_t slot = (col_width(max_bx) / 2 + 2 * lanes + 3) / 4 * 4;
+  const size_t b = slot * t + (size_t)round16(max_cells, w) * w + (size_t)max_cells * t;
   return (b + 15) / 16 * 16 <= kBoxLds;
 }
 // Boxes per workgroup: up to 256 threads, fewer when the boxes' LDS would
-// exceed 64 KB (0 when even one box does not fit).
+// exceed 64 KB (0 when a box is not accepted).
 int box_groups(int max_bx, int max_cells, size_t t, size_t w) {
   const int bt = box_threads(w);
   for (int groups = kBoxThreads / bt; groups > 1; groups /= 2)
     if (groups * group_bytes(max_bx, max_cells, t, w) <= kBoxLds) return groups;
   return box_fits(max_bx, max_cells, t, w) ? 1 : 0;
 }
-size_t box_lds_bytes(int max_bx, int max_cells, size_t t, size_t w) {
-  return box_fits(max_bx, max_cells, t, w) ? box_groups(max_bx, max_cells, t, w) *
-                                                 group_bytes(max_bx, max_cells, t, w)
-                                           : ~(size_t)0;
-}
 // Launch a box kernel with shm bytes of LDS (past 64 KB gfx950 has to be asked).
 template <typename... A, typename... B>
 void launch_box(void (*kernel)(A...), dim3 grid, dim3 block, size_t shm, hipStream_t s,
                 B... args) {
-  if (shm > kBoxLds)
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBoxLdsMax);
+  if (shm > kBoxLds &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBoxLdsMax) != hipSuccess)
+    throw Error(MRCM_EDEVICE, "no workgroup with the LDS of a box");
   hipLaunchKernelGGL(kernel, grid, block, shm, s, args...);
 }
 #define MRCM_BOX_DISPATCH(KERNEL, T, S, max_bx, ...)                     \

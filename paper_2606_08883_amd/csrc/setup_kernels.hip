@@ -348,9 +348,10 @@ void launch_factor_boxes(const FactorJob* jobs, int njobs, int maxn, const doubl
   if (njobs <= 0) return;
   const int waves = sizeof(S) == 8 ? 2 : 1;
   const size_t shm = waves * sizeof(double) * ((size_t)maxn * maxn + 4 * (size_t)maxn);
-  if (shm > 64 * 1024)  // boxes wider than 62 cells: ask for the larger LDS of gfx950
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&k_factor_boxes<S>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+  if (shm > 64 * 1024 &&  // boxes wider than 62 cells: ask for the larger LDS of gfx950
+      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_factor_boxes<S>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
+    throw Error(MRCM_EDEVICE, "no workgroup with the LDS of a box factorisation");
   hipLaunchKernelGGL(k_factor_boxes<S>, dim3(njobs), dim3(64 * waves), shm, s, jobs, maxn, K, tx, ty, nx,
                      ny, aL, dS, cS, d64, c64, status);
 }
