@@ -556,7 +556,9 @@ __device__ __forceinline__ void zero_slots(T* v, int count) {
   for (int i = threadIdx.x & 63; i < count; i += 64) v[i] = T(0);
 }
 
-// Meet the other group of the box, if it has two.
+// Meet the other group of the box, if it has two.  The meeting is the workgroup's: every
+// wave of a launch has to pass the same number of them (two in a box solve, one where the
+// middle row is reached and one when it has been read, whatever the box's rows).
 template <int ENDS>
 __device__ __forceinline__ void pair_sync() {
   if constexpr (ENDS == 2)
@@ -761,6 +763,18 @@ struct BoxThread {
     live = i0 < m;
     i = live ? i0 : m - 1;
   }
+  // The most faces of a subdomain among the workgroup's boxes (the same in every
+  // thread, so that loops with workgroup barriers run the same rounds in all waves).
+  __device__ int faces(const BoxDesc* __restrict__ boxes, int block, int m) const {
+    const int n = ENDS == 2 ? (int)(blockDim.x / NL) : 1, i0 = ENDS == 2 ? block * n : i;
+    int most = 0;
+    for (int q = 0; q < n; ++q) {
+      const BoxDesc& d = boxes[i0 + q < m ? i0 + q : m - 1];
+      const int f = 2 * (d.obx + d.oby);
+      most = f > most ? f : most;
+    }
+    return most;
+  }
 };
 // First and last row of the box that the owned rows' traces read: one beyond
 // the owned rows on either side, inside the box.
@@ -811,9 +825,11 @@ __device__ __forceinline__ void face_cells(const BoxDesc& d, int side, int j, in
 // 3 NL words of LDS), then one thread per dof adds its side's faces in order:
 // the divisions, weights and cells of all faces cost one pass instead of one per
 // face and dof (14 of k_local's 89 us at 1024^2 in FP64, 8 of 33 us at 505 x 387,
-// were this serial).
+// were this serial).  The rounds over the faces go to `span`, the workgroup's most
+// (BoxThread::faces): all its waves meet at the same barriers, whatever their boxes' sides.
+// A subdomain has at most 36 dofs (four sides, degree 8): one per thread.
 template <int ENDS, typename V>
-__device__ __forceinline__ void trace_moments(const BoxDesc& d, int lane, bool live,
+__device__ __forceinline__ void trace_moments(const BoxDesc& d, int lane, bool live, int span,
                                               const int* __restrict__ dof_side,
                                               const int* __restrict__ dof_q,
                                               const int* __restrict__ dof_face0, int k0, int nd,
@@ -824,50 +840,48 @@ __device__ __forceinline__ void trace_moments(const BoxDesc& d, int lane, bool l
   const int f0 = dof_face0[k0];
   const int last = dof_face0[k0 + nd - 1] - f0 +
                    (dof_side[k0 + nd - 1] <= 1 ? d.oby : d.obx);  // faces of the subdomain
-  for (int kb = 0; kb < nd; kb += NL) {
-    const bool mine = kb + lane < nd;
-    const int k = k0 + (mine ? kb + lane : 0);
-    const int side = dof_side[k], q = dof_q[k], len = side <= 1 ? d.oby : d.obx;
-    const int fa = dof_face0[k] - f0;
-    double su = 0.0, sp = 0.0;
-    for (int base = 0; base < last; base += NL) {
-      const int f = base + lane;
-      if (f < last) {
-        // the face's side: the last dof whose faces start at or before it
-        int fs = 0, fb = 0;
-        for (int e = 0; e < nd; ++e) {
-          const int b = dof_face0[k0 + e] - f0;
-          if (b <= f) {
-            fs = dof_side[k0 + e];
-            fb = b;
-          }
-        }
-        const f64x2* w = reinterpret_cast<const f64x2*>(face_w + 4LL * (f0 + f));
-        const f64x2 wu = w[0], wp = w[1];
-        const int j = f - fb;
-        int ci, co;
-        face_cells(d, fs, j, ci, co);
-        const double pin = v(ci), pout = v(co);
-        buf[lane] = fmat(wu[1], pout, wu[0] * pin);
-        buf[NL + lane] = fmat(wp[1], pout, wp[0] * pin);
-        buf[2 * NL + lane] = (2.0 * j + 1.0) / (fs <= 1 ? d.oby : d.obx) - 1.0;
-      }
-      pair_sync<ENDS>();
-      if (mine) {
-        const int a = fa > base ? fa : base;
-        const int b = fa + len < base + NL ? fa + len : base + NL;
-        for (int t = a; t < b; ++t) {
-          const double lw = legendre_at(q, buf[2 * NL + t - base]);
-          su = fmat(lw, buf[t - base], su);
-          sp = fmat(lw, buf[NL + t - base], sp);
+  const bool mine = lane < nd;
+  const int k = k0 + (mine ? lane : 0);
+  const int side = dof_side[k], q = dof_q[k], len = side <= 1 ? d.oby : d.obx;
+  const int fa = dof_face0[k] - f0;
+  double su = 0.0, sp = 0.0;
+  for (int base = 0; base < span; base += NL) {
+    const int f = base + lane;
+    if (f < last) {
+      // the face's side: the last dof whose faces start at or before it
+      int fs = 0, fb = 0;
+      for (int e = 0; e < nd; ++e) {
+        const int b = dof_face0[k0 + e] - f0;
+        if (b <= f) {
+          fs = dof_side[k0 + e];
+          fb = b;
         }
       }
-      pair_sync<ENDS>();
+      const f64x2* w = reinterpret_cast<const f64x2*>(face_w + 4LL * (f0 + f));
+      const f64x2 wu = w[0], wp = w[1];
+      const int j = f - fb;
+      int ci, co;
+      face_cells(d, fs, j, ci, co);
+      const double pin = v(ci), pout = v(co);
+      buf[lane] = fmat(wu[1], pout, wu[0] * pin);
+      buf[NL + lane] = fmat(wp[1], pout, wp[0] * pin);
+      buf[2 * NL + lane] = (2.0 * j + 1.0) / (fs <= 1 ? d.oby : d.obx) - 1.0;
     }
-    if (mine && live) {
-      mU[k] = su;
-      mP[k] = sp;
+    pair_sync<ENDS>();
+    if (mine) {
+      const int a = fa > base ? fa : base;
+      const int b = fa + len < base + NL ? fa + len : base + NL;
+      for (int t = a; t < b; ++t) {
+        const double lw = legendre_at(q, buf[2 * NL + t - base]);
+        su = fmat(lw, buf[t - base], su);
+        sp = fmat(lw, buf[NL + t - base], sp);
+      }
     }
+    pair_sync<ENDS>();
+  }
+  if (mine && live) {
+    mU[k] = su;
+    mP[k] = sp;
   }
 }
 
@@ -906,9 +920,9 @@ __device__ __forceinline__ void local_body(
       p[o2 + (long long)j * nx + t.r] = L.us[(d.oy + j) * bx + t.r];
   }
   const int k0 = dof_off[t.i], nd = dof_off[t.i + 1] - k0;
-  if (nd > 0)
-    trace_moments<BT::ENDS>(d, t.lane, t.live, dof_side, dof_q, dof_face0, k0, nd,
-                                    face_w, reinterpret_cast<double*>(L.cp),
+  if (nd > 0)  // none where one subdomain is the grid, the only box then
+    trace_moments<BT::ENDS>(d, t.lane, t.live, t.faces(boxes, blk.id, m), dof_side, dof_q,
+                                    dof_face0, k0, nd, face_w, reinterpret_cast<double*>(L.cp),
                                     [&](int c) { return (double)L.us[c]; }, mU, mP);
 }
 template <typename T, typename S, int NB>
@@ -2053,11 +2067,12 @@ __global__ void __launch_bounds__(kBoxThreads)
         p.v[k][o2 + (long long)j * nx + t.r] = work[k][(long long)(d.oy + j) * bx + t.r];
   }
   const int k0 = dof_off[t.i], nd = dof_off[t.i + 1] - k0;
-  if (nd > 0)
+  const int span = t.faces(boxes, blockIdx.x, m);
+  if (nd > 0)  // as in local_body
 #pragma unroll 1
     for (int k = 0; k < K; ++k) {
       const T* wk = e.v[k] + d.coff;
-      trace_moments<BT::ENDS>(d, t.lane, t.live, dof_side, dof_q, dof_face0, k0, nd,
+      trace_moments<BT::ENDS>(d, t.lane, t.live, span, dof_side, dof_q, dof_face0, k0, nd,
                                       face_w, reinterpret_cast<double*>(L.cp),
                                       [&](int c) { return (double)wk[c]; },
                                       mU + (long long)k * nc, mP + (long long)k * nc);
