@@ -254,7 +254,12 @@ struct Half {
   static constexpr int HV = 64 / R;
   static constexpr int NT = (H + 3) / 4;          // steps of four mirrored entries
   static constexpr int NM = HV == 2 ? 2 * NT : H;  // mirrored entries a lane fetches, at most
+  // Place of v in the vector slot: H words hold what lies before it; one more where half
+  // 1's last mirrored step, which it discards, reaches beyond them (a one-cell row and
+  // three words too many: column width 20).
+  static constexpr int V0 = HV == 2 && 4 * NT > H + 1 ? H + 1 : H;
   static_assert(HV == 1 || K0 == 1 || K0 == 3, "halves of a row: one or three single words");
+  static_assert(HV == 1 || V0 + 1 >= 4 * NT, "mirrored reads stay in the vector slot");
 };
 // Ends of the factors of storage type S (groups per box).
 template <typename S>
@@ -545,10 +550,10 @@ __device__ __forceinline__ void pipelined_sweep(int n, const S* __restrict__ blk
 }
 
 // Words of the group's copy of the step vector for column width NB:
-// v at [H, H + n) and again at [H + n, H + 2 n), zeros around it
+// v at [V0, V0 + n) and again at [V0 + n, V0 + 2 n), zeros around it
 // (the lane's rows past the box meet finite values).
 template <int NB>
-constexpr int vec_words() { return (NB / 2 + 2 * Half<NB>::R + 3) / 4 * 4; }
+constexpr int vec_words() { return (Half<NB>::V0 + 2 * Half<NB>::R + 3) / 4 * 4; }
 
 // Zero the group's vector slots (count words) before the first step.
 template <typename T>
@@ -597,14 +602,14 @@ template <typename T, typename S, int NB>
 __device__ __forceinline__ void box_solve(T* us, T* vv, const S* cp, const S* __restrict__ Dinv,
                                           int bx, int by, int bstride, int r, int hf, int end,
                                           int lo, int hi) {
-  constexpr int H = Half<NB>::H, HV = Half<NB>::HV, ENDS = box_ends<S>();
+  constexpr int V0 = Half<NB>::V0, HV = Half<NB>::HV, ENDS = box_ends<S>();
   constexpr int DEPTH = reg_depth<S, NB>();
   const EndSteps<ENDS> st(by, end, lo, hi);
   const int rc = r < bx ? r : bx - 1;
   const Mirror<NB, sizeof(T) == 8> mir(rc, hf, bx);
-  const T* vo = vv + H + rc + 2 * hf;
-  const T* vr = vv + H + rc + bx - 2 * hf;
-  T* put = vv + H + rc + hf * bx;
+  const T* vo = vv + V0 + rc + 2 * hf;
+  const T* vr = vv + V0 + rc + bx - 2 * hf;
+  T* put = vv + V0 + rc + hf * bx;
   T* ur = us + rc;
   const S* cr = cp + rc;
   const int dx = st.dir * bx;
@@ -1896,14 +1901,14 @@ __device__ __forceinline__ void box_solve_k(const In* const (&in)[K], long long 
                                             const S* __restrict__ Dinv, int bx, int by,
                                             int bstride, int r, int hf, int end,
                                             bool live, bool pin, int lo, int hi) {
-  constexpr int H = Half<NB>::H, HV = Half<NB>::HV, ENDS = box_ends<S>();
+  constexpr int V0 = Half<NB>::V0, HV = Half<NB>::HV, ENDS = box_ends<S>();
   constexpr int VW = vec_words<NB>(), DEPTH = reg_depth<S, NB>();
   const EndSteps<ENDS> st(by, end, lo, hi);
   const int rc = r < bx ? r : bx - 1;
   const Mirror<NB, sizeof(T) == 8> mir(rc, hf, bx);
-  const T* vo = vv + H + rc + 2 * hf;
-  const T* vr = vv + H + rc + bx - 2 * hf;
-  T* put = vv + H + rc + hf * bx;
+  const T* vo = vv + V0 + rc + 2 * hf;
+  const T* vr = vv + V0 + rc + bx - 2 * hf;
+  T* put = vv + V0 + rc + hf * bx;
   const S* cr = cp + rc;
   const int dx = st.dir * bx;
   const bool own = live && hf == 0 && r < bx;
@@ -1951,12 +1956,12 @@ __device__ __forceinline__ void box_solve_k(const In* const (&in)[K], long long 
           if (ENDS == 2 && s == st.n - 1) {
             // both ends have reached the middle row: exchange the rows next to it
 #pragma unroll
-            for (int k = 0; k < K; ++k) vv[k * VW + H + rc] = carry[k];
+            for (int k = 0; k < K; ++k) vv[k * VW + V0 + rc] = carry[k];
             pair_sync<ENDS>();
             const T cl = (T)cr[st.h * bx], ch = (T)cr[(st.h + 1 < by ? st.h + 1 : st.h) * bx];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-              const T o = other[k * VW + H + rc];
+              const T o = other[k * VW + V0 + rc];
               y[k] = b[k];
               if (st.h > 0) y[k] = fmat(cl, st.top ? o : carry[k], y[k]);
               if (st.h + 1 < by) y[k] = fmat(ch, st.top ? carry[k] : o, y[k]);
@@ -2527,7 +2532,16 @@ inline int ends_of(size_t w) { return w == 8 ? 2 : 1; }
 inline int box_threads(size_t w) { return 64 * ends_of(w); }
 // Words of a group's vector slot (vec_words of the kernels).
 inline int vec_slot_words(int max_bx) {
-  return (col_width(max_bx) / 2 + 2 * row_lanes(max_bx) + 3) / 4 * 4;
+  switch (col_width(max_bx)) {
+    case 16: return vec_words<16>();
+    case 20: return vec_words<20>();
+    case 24: return vec_words<24>();
+    case 32: return vec_words<32>();
+    case 36: return vec_words<36>();
+    case 40: return vec_words<40>();
+    case 48: return vec_words<48>();
+    default: return vec_words<64>();
+  }
 }
 // Words of S in 16 bytes; x rounded up to a multiple of them.
 inline int round16(long long x, size_t w) {
