@@ -268,7 +268,6 @@ struct mrcm_ctx {
     Batch batch;
     std::vector<Slot> slots;
     std::vector<StepGraph> graphs;  // captured steps of slot 0 (lanes of one slot)
-    bool open = false;  // a solve left the lane before its last scalars arrived
   };
   std::vector<Lane> lanes;
   int max_lanes = 4, batch_width = 4;
@@ -1769,8 +1768,6 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
       mrcm_ctx::Lane& L = c->lanes[l];
       ensure_slots(c, L, w);
       for (int q = 0; q < w; ++q) ensure_krylov(c, L, L.slots[q], restart);
-      if (L.open) hip_check(hipStreamSynchronize(L.st), "hipStreamSynchronize");
-      L.open = true;
       hip_check(hipStreamWaitEvent(L.st, c->ws_in, 0), "hipStreamWaitEvent");
     }
     const long long n = c->n;
@@ -1809,7 +1806,7 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
       R.y.assign(restart, 0.0);
       double* pk = p + (size_t)R.k * n;
       hip_check(hipMemsetAsync(pk, 0, sizeof(double) * n, L.st), "hipMemsetAsync");
-      mrcm::launch_sumsq(b + (size_t)R.k * n, n, S.mail.post(nb), nb, L.st);
+      mrcm::launch_sumsq(b + (size_t)R.k * n, n, S.mail.post(nb, L.st), nb, L.st);
       R.phase = kNormB;
     };
     // Consume a slot's scalars and launch its next work other than
@@ -1827,8 +1824,8 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
           return;
         }
         R.tol = rtol * R.bnorm;
-        mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, bk, nullptr, S.V, S.mail.post(nb), nb,
-                                L.st);
+        mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, bk, nullptr, S.V,
+                                S.mail.post(nb, L.st), nb, L.st);
         R.phase = kBeta;
         return;
       }
@@ -1890,7 +1887,8 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
         R.y[i] = sum / H[(size_t)i * restart + i];
       }
       mrcm::launch_update(pk, S.Z, R.y.data(), jj, n, L.st);
-      mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, bk, pk, S.V, S.mail.post(nb), nb, L.st);
+      mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, bk, pk, S.V, S.mail.post(nb, L.st), nb,
+                              L.st);
       R.phase = kBeta;
     };
     // The lane's Arnoldi steps of this tick: one application of T and one
@@ -1913,7 +1911,7 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
       if (w == 1) {
         Run& R = runs[l][0];
         mrcm_ctx::StepGraph* sg = step_graph(c, L, R.j, nb);
-        L.slots[0].mail.post(R.j + 2);
+        L.slots[0].mail.post(R.j + 2, L.st);
         if (sg)
           hip_check(hipGraphLaunch(sg->exec, L.st), "hipGraphLaunch");
         else
@@ -1928,7 +1926,7 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
         Run& R = runs[l][q];
         if (!R.step) continue;
         cols.c[k++] = tail_col(c, L.slots[q], R.j, nb);
-        L.slots[q].mail.post(R.j + 2);
+        L.slots[q].mail.post(R.j + 2, L.st);
         R.step = false;
       }
       mrcm::launch_tail(cols, k, L.st);
@@ -1959,10 +1957,8 @@ int gmres_solve(mrcm_ctx* c, const double* b, double* p, int32_t nrhs, double rt
       }
       if (!busy) break;
     }
-    for (int l = 0; l < nl; ++l) {
+    for (int l = 0; l < nl; ++l)
       hip_check(hipStreamSynchronize(c->lanes[l].st), "hipStreamSynchronize");
-      c->lanes[l].open = false;
-    }
     check_launch();
     if (st) {
       st->iterations = total_it;
@@ -2048,7 +2044,7 @@ void batch_start(mrcm_batch* B, Run& R) {
   R.gv.assign(B->restart + 1, 0.0);
   R.y.assign(B->restart, 0.0);
   mrcm::launch_zero(R.p, n, B->st);
-  mrcm::launch_sumsq(R.b, n, R.mail.post(R.nb), R.nb, B->st);
+  mrcm::launch_sumsq(R.b, n, R.mail.post(R.nb, B->st), R.nb, B->st);
   R.phase = mrcm_batch::kNormB;
 }
 
@@ -2068,8 +2064,8 @@ void batch_advance(mrcm_batch* B, Run& R) {
       return;
     }
     R.tol = R.rtol * R.bnorm;
-    mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, R.b, nullptr, R.V, R.mail.post(R.nb), R.nb,
-                            s);
+    mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, R.b, nullptr, R.V, R.mail.post(R.nb, s),
+                            R.nb, s);
     R.phase = mrcm_batch::kBeta;
     return;
   }
@@ -2127,7 +2123,7 @@ void batch_advance(mrcm_batch* B, Run& R) {
     R.y[i] = sum / H[(size_t)i * restart + i];
   }
   mrcm::launch_update(R.p, R.Z, R.y.data(), jj, n, s);
-  mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, R.b, R.p, R.V, R.mail.post(R.nb), R.nb, s);
+  mrcm::launch_resid_norm(c->tx, c->ty, c->nx, c->ny, R.b, R.p, R.V, R.mail.post(R.nb, s), R.nb, s);
   R.phase = mrcm_batch::kBeta;
 }
 
@@ -2231,7 +2227,7 @@ int gmres_batch_tick(mrcm_batch* B, int32_t* active) {
       f.Z = R.Z;
       f.parts = R.parts;
       f.hcol = R.hcol;
-      f.mail = R.mail.post(R.j + 2);
+      f.mail = R.mail.post(R.j + 2, B->st);
       f.j = R.j;
       refs.push_back(f);
       R.step = false;

@@ -502,7 +502,7 @@ int mrcm3d_gmres_solve(mrcm3d_ctx* c, const double* b, double* p, double rtol, i
     bool conv = false;
     double relres = 1.0;
     mrcm::launch_zero(p, n, s);
-    mrcm::launch_sumsq(b, n, c->mail.post(nb), nb, s);
+    mrcm::launch_sumsq(b, n, c->mail.post(nb, s), nb, s);
     const double bnorm = std::sqrt(host_sum3(fetch(), nb));
     if (bnorm == 0.0) {
       conv = true;
@@ -512,7 +512,7 @@ int mrcm3d_gmres_solve(mrcm3d_ctx* c, const double* b, double* p, double rtol, i
       bool first = true;
       for (;;) {
         mrcm3d::launch_resid_norm3(c->tx, c->ty, c->tz, c->nx, c->ny, c->nz, b,
-                                   first ? nullptr : p, c->V, c->mail.post(nb), nb, s);
+                                   first ? nullptr : p, c->V, c->mail.post(nb, s), nb, s);
         first = false;
         const double beta = std::sqrt(host_sum3(fetch(), nb));
         relres = beta / bnorm;
@@ -540,7 +540,7 @@ int mrcm3d_gmres_solve(mrcm3d_ctx* c, const double* b, double* p, double rtol, i
                                   w, c->V + (size_t)i * n,
                                   i < j ? c->V + (size_t)(i + 1) * n : nullptr, n, s);
           mrcm::launch_norm_scale(c->parts + ((j + 1) % 2) * mrcm::kMaxVecBlocks, nb, c->hcol,
-                                  c->mail.post(j + 2), j + 1, w, n, s);
+                                  c->mail.post(j + 2, s), j + 1, w, n, s);
           const double* hh = fetch();
           ++it;
           for (int i = 0; i <= j + 1; ++i) H[(size_t)i * restart + j] = hh[i];

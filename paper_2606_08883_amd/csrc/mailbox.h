@@ -15,8 +15,8 @@
 namespace mrcm {
 
 // A pinned buffer that kernels store into (publish) and one host thread watches:
-// post(n) marks the first n places unset before the kernels that write them are
-// launched, wait returns once all of them are set.  A copy to the host and a
+// post(n, s) marks the first n places unset before the kernels that write them are
+// launched on stream s, wait returns once all of them are set.  A copy to the host and a
 // stream synchronisation take 14.7 us from the launch of a 2 us kernel, stores from
 // the device and a watch 11.1 us, and those are stores of the step's last kernel, not a
 // launch more (the host waits once per Arnoldi step, for j + 2 values; eight
@@ -53,7 +53,10 @@ struct Mailbox {
     if (h) (void)hipHostFree(h);
     h = nullptr;
   }
-  double* post(int n) {
+  // A post that nobody waited for (the caller left by an error) may still be answered:
+  // the stream is drained first, so that the old scalars are not taken for the new ones.
+  double* post(int n, hipStream_t s) {
+    if (posted > 0) check(hipStreamSynchronize(s), "hipStreamSynchronize");
     uint64_t* q = reinterpret_cast<uint64_t*>(h);
     for (int i = 0; i < n; ++i) __atomic_store_n(q + i, kUnset, __ATOMIC_RELAXED);
     __atomic_thread_fence(__ATOMIC_SEQ_CST);
@@ -62,6 +65,7 @@ struct Mailbox {
   }
   const double* wait(hipStream_t s) {
     using clock = std::chrono::steady_clock;
+    if (posted == 0) throw Error(MRCM_EDEVICE, "no scalars to wait for");
     const uint64_t* q = reinterpret_cast<const uint64_t*>(h);
     int i = 0;
     auto set = [&]() {

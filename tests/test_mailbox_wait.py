@@ -1,7 +1,7 @@
 """The host's wait for a kernel's scalars (csrc/mailbox.h), compiled here against a stream
 that the test answers for: a waiting thread gives its core to the thread it waits for,
 asks the stream rarely, and ends with an error when the stream's work is done and a
-scalar is missing.
+scalar is missing; a post after one that nobody waited for drains the stream first.
 """
 import subprocess
 
@@ -23,7 +23,7 @@ SOURCE = r"""
 
 #include "mailbox.h"
 
-static std::atomic<int> asked{0};
+static std::atomic<int> asked{0}, drained{0};
 static std::atomic<int> answer{hipErrorNotReady};
 extern "C" {
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
@@ -32,6 +32,10 @@ hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
 }
 hipError_t hipHostFree(void* p) {
   std::free(p);
+  return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) {
+  ++drained;
   return hipSuccess;
 }
 hipError_t hipStreamQuery(hipStream_t) {
@@ -50,12 +54,29 @@ int main(int argc, char** argv) {
   box.create();
   if (!std::strcmp(argv[1], "missing")) {
     answer = hipSuccess;
-    box.post(3)[1] = 1.0;
+    box.post(3, nullptr)[1] = 1.0;
     try {
       box.wait(nullptr);
       std::puts("arrived");
     } catch (const mrcm::Error& e) {
       std::printf("error %d\n", e.code);
+    }
+    return 0;
+  }
+  if (!std::strcmp(argv[1], "abandoned")) {
+    double* h = box.post(1, nullptr);
+    h[0] = 1.0;
+    box.wait(nullptr);
+    int before = drained;
+    h = box.post(2, nullptr);  // every post so far was waited for
+    before = drained - before;
+    box.post(1, nullptr);
+    h[0] = 2.0;
+    std::printf("%d %d %g", before, drained.load(), box.wait(nullptr)[0]);
+    try {
+      box.wait(nullptr);
+    } catch (const mrcm::Error& e) {
+      std::printf(" error %d\n", e.code);
     }
     return 0;
   }
@@ -77,7 +98,7 @@ int main(int argc, char** argv) {
   bool right = true;
   for (int k = 1; k <= rounds; ++k) {
     const auto began = clock::now();
-    box.post(5);
+    box.post(5, nullptr);
     posted = k;
     const double* h = box.wait(nullptr);
     for (int i = 0; i < 5; ++i) {
@@ -124,3 +145,8 @@ def test_wait_gives_the_core_away(program):
 def test_wait_ends_with_the_stream(program):
     r = subprocess.run([program, "missing"], capture_output=True, text=True, timeout=60)
     assert r.stdout.split() == ["error", "-5"]
+
+
+def test_post_after_an_abandoned_one(program):
+    r = subprocess.run([program, "abandoned"], capture_output=True, text=True, timeout=60)
+    assert r.stdout.split() == ["0", "1", "2", "error", "-5"]
