@@ -393,9 +393,7 @@ struct mrcm_ctx {
     for (auto& L : lanes) {
       drop_graphs(L);
       if (L.st) (void)hipStreamDestroy(L.st);
-      for (auto& S : L.slots) S.mail.destroy();
     }
-    for (auto& q : run_pool) q.mail.destroy();
     if (ws_in) (void)hipEventDestroy(ws_in);
     if (ws_out) (void)hipEventDestroy(ws_out);
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
@@ -2020,7 +2018,6 @@ struct mrcm_batch {
   int next_tag = 1;
   ~mrcm_batch() {
     if (st) (void)hipStreamSynchronize(st);
-    for (auto& R : runs) R->mail.destroy();
     if (ev_in) (void)hipEventDestroy(ev_in);
     if (st) (void)hipStreamDestroy(st);
   }
@@ -2173,7 +2170,7 @@ int gmres_batch_add(mrcm_batch* B, mrcm_ctx* c, const double* b, double* p, int3
         R->Z = pooled->Z;
         R->hcol = pooled->hcol;
         R->parts = pooled->parts;
-        R->mail = pooled->mail;
+        R->mail = std::move(pooled->mail);
         c->run_pool.erase(pooled);
       } else {
         R->w = make_column(c, B->st);
@@ -2296,8 +2293,8 @@ int gmres_batch_remove(mrcm_batch* B, int32_t tag) {
         q.Z = R.Z;
         q.hcol = R.hcol;
         q.parts = R.parts;
-        q.mail = R.mail;
-        R.c->run_pool.push_back(q);
+        q.mail = std::move(R.mail);
+        R.c->run_pool.push_back(std::move(q));
         r = runs.erase(r);
       } else {
         ++r;

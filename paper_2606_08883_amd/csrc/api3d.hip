@@ -141,7 +141,6 @@ struct mrcm3d_ctx {
       else
         (void)hipFree(q);
     }
-    mail.destroy();
     if (ev_in) (void)hipEventDestroy(ev_in);
     if (st) (void)hipStreamDestroy(st);
   }

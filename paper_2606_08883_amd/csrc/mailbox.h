@@ -7,6 +7,7 @@
 #include <cstdint>
 #include <string>
 #include <thread>
+#include <utility>
 
 #include "../../include/mrcm.h"
 #include "device.h"
@@ -35,8 +36,22 @@ struct Mailbox {
   static constexpr uint64_t kUnset = 0x7ff4a5c3e1d2b697ull;
     static constexpr unsigned kSpins = 64;
   static constexpr std::chrono::microseconds kAskEvery{1000};
-  double* h = nullptr;  // the same address on the host and the device
+  double* h = nullptr;  // the same address on the host and the device; owned
   int posted = 0;
+
+  Mailbox() = default;
+  Mailbox(Mailbox&& o) noexcept : h(o.h), posted(o.posted) {
+    o.h = nullptr;
+    o.posted = 0;
+  }
+  Mailbox& operator=(Mailbox&& o) noexcept {
+    std::swap(h, o.h);
+    std::swap(posted, o.posted);
+    return *this;
+  }
+  ~Mailbox() {
+    if (h) (void)hipHostFree(h);
+  }
 
   static void check(hipError_t e, const char* what) {
     if (e != hipSuccess)
@@ -48,10 +63,6 @@ struct Mailbox {
     check(hipHostMalloc((void**)&h, sizeof(double) * kPlaces,
                         hipHostMallocMapped | hipHostMallocCoherent),
           "hipHostMalloc");
-  }
-  void destroy() {
-    if (h) (void)hipHostFree(h);
-    h = nullptr;
   }
   // A post that nobody waited for (the caller left by an error) may still be answered:
   // the stream is drained first, so that the old scalars are not taken for the new ones.

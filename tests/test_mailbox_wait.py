@@ -1,7 +1,7 @@
 """The host's wait for a kernel's scalars (csrc/mailbox.h), compiled here against a stream
 that the test answers for: a waiting thread gives its core to the thread it waits for,
 asks the stream rarely, and ends with an error when the stream's work is done and a
-scalar is missing; a post after one that nobody waited for drains the stream first.
+scalar is missing; a post after one that nobody waited for drains the stream first; its memory has one owner.
 """
 import subprocess
 
@@ -19,19 +19,23 @@ SOURCE = r"""
 #include <cstdlib>
 #include <cstring>
 #include <thread>
+#include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "mailbox.h"
 
-static std::atomic<int> asked{0}, drained{0};
+static std::atomic<int> asked{0}, drained{0}, held{0};
 static std::atomic<int> answer{hipErrorNotReady};
 extern "C" {
 hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
   *p = std::calloc(1, n);
+  ++held;
   return hipSuccess;
 }
 hipError_t hipHostFree(void* p) {
   std::free(p);
+  --held;
   return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) {
@@ -61,6 +65,24 @@ int main(int argc, char** argv) {
     } catch (const mrcm::Error& e) {
       std::printf("error %d\n", e.code);
     }
+    return 0;
+  }
+  if (!std::strcmp(argv[1], "owned")) {
+    static_assert(!std::is_copy_constructible<mrcm::Mailbox>::value, "one owner");
+    {
+      std::vector<mrcm::Mailbox> pool(3);  // growing moves them
+      for (int i = 0; i < 5; ++i) {
+        mrcm::Mailbox b;
+        b.create();
+        b.create();
+        pool.push_back(std::move(b));
+      }
+      box = std::move(pool.back());
+      pool.pop_back();
+      mrcm::Mailbox lost;  // dropped without reaching an owner
+      lost.create();
+    }
+    std::printf("%d\n", held.load());
     return 0;
   }
   if (!std::strcmp(argv[1], "abandoned")) {
@@ -110,7 +132,6 @@ int main(int argc, char** argv) {
   }
   const double all = ms(clock::now() - t0);
   sender.join();
-  box.destroy();
   std::sort(took.begin(), took.end());
   std::printf("right %d median_ms %.4f total_ms %.3f asked %d\n", right ? 1 : 0,
               took[rounds / 2], all, asked.load());
@@ -150,3 +171,8 @@ def test_wait_ends_with_the_stream(program):
 def test_post_after_an_abandoned_one(program):
     r = subprocess.run([program, "abandoned"], capture_output=True, text=True, timeout=60)
     assert r.stdout.split() == ["0", "1", "2", "error", "-5"]
+
+
+def test_one_owner(program):
+    r = subprocess.run([program, "owned"], capture_output=True, text=True, timeout=60)
+    assert r.stdout.split() == ["1"]
