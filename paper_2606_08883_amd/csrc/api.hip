@@ -602,9 +602,9 @@ void autotune(mrcm_ctx* c, hipStream_t s) {
       return best;
     };
     auto group_opts = [&](int max_bx, int max_cells) {
-      const int g = mrcm::box_groups(max_bx, max_cells, sizeof(T), sizeof(S));
-      std::vector<int> o{g};
-      for (int h = g / 2; h >= 1 && (int)o.size() < 3; h /= 2) o.push_back(h);
+      const mrcm::BoxGrid g = mrcm::box_grid(c->m, max_bx, max_cells, sizeof(T), sizeof(S), true);
+      std::vector<int> o{g.groups};
+      for (int h = g.groups / 2; h >= g.least && (int)o.size() < 3; h /= 2) o.push_back(h);
       return o;
     };
     if (c->m > 0) {
@@ -894,7 +894,7 @@ void device_setup(mrcm_ctx* c, mrcm::HostSetup& S, const double* K_dev, hipStrea
       throw mrcm::Error(MRCM_EINVAL,
                         "oversampled subdomains and smoothing patches must be at most 64 cells "
                         "wide");
-    if (mrcm::box_groups(max_bx, max_cells, sizeof(W), sizeof(X)) <= 0)
+    if (!mrcm::box_fits(max_bx, max_cells, sizeof(W), sizeof(X)))
       throw mrcm::Error(MRCM_EINVAL,
                         "oversampled subdomain or patch too large for the LDS of one workgroup");
   };
@@ -1204,8 +1204,10 @@ void apply_family(const std::vector<ManyRef>& refs, ManyTables& tb, hipStream_t 
   if (nc == 0) return;
   int mcl = 0, mbl = 0, mcp = 0, mbp = 0, mnf = 0, mnu = 0, nfwd = 0, nbwd = 0, nref = 0,
       nsw = 0, maxj = 0;
+  long long nboxes = 0;
   for (const ManyRef& f : refs) {
     const mrcm_ctx* c = f.c;
+    nboxes += c->m;
     mcl = std::max(mcl, c->max_cells_local);
     mbl = std::max(mbl, c->max_bx_local);
     if (c->sweeps > 0) {
@@ -1222,10 +1224,11 @@ void apply_family(const std::vector<ManyRef>& refs, ManyTables& tb, hipStream_t 
     nsw = std::max(nsw, c->sweeps);
     maxj = std::max(maxj, f.j);
   }
-  const int gl = mrcm::box_groups(mbl, mcl, sizeof(T), sizeof(S));
-  const int gp = nsw > 0 ? mrcm::box_groups(mbp, mcp, sizeof(T), sizeof(S)) : 1;
-  if (gl <= 0 || gp <= 0)
+  if (!mrcm::box_fits(mbl, mcl, sizeof(T), sizeof(S)) ||
+      (nsw > 0 && !mrcm::box_fits(mbp, mcp, sizeof(T), sizeof(S))))
     throw mrcm::Error(MRCM_EINVAL, "boxes too large for a launch over several contexts");
+  const mrcm::BoxGrid gl = mrcm::box_grid(nboxes, mbl, mcl, sizeof(T), sizeof(S), false);
+  const mrcm::BoxGrid gp = mrcm::box_grid(nboxes, mbp, mcp, sizeof(T), sizeof(S), false);
   // workgroup ranges: prefix sums of per-column counts (and first chunks)
   std::vector<int> ints;
   struct Seg {
@@ -1247,7 +1250,9 @@ void apply_family(const std::vector<ManyRef>& refs, ManyTables& tb, hipStream_t 
     return g;
   };
   auto none = [](const mrcm_ctx*) { return 0; };
-  const Seg local = seg([&](const mrcm_ctx* c, int) { return (c->m + gl - 1) / gl; }, none);
+  const Seg local = seg([&](const mrcm_ctx* c, int) {
+    return (c->m + gl.groups - 1) / gl.groups;
+  }, none);
   const Seg crhs = seg([](const mrcm_ctx* c, int) { return c->nc > 0 ? (c->np + 255) / 256 : 0; },
                        none);
   auto level = [&](const std::vector<std::pair<int, int>> mrcm_ctx::*lv, int l, int it) {
@@ -1282,7 +1287,7 @@ void apply_family(const std::vector<ManyRef>& refs, ManyTables& tb, hipStream_t 
     resd[sw] = seg([&](const mrcm_ctx* c, int) { return sw < c->sweeps ? grid_blocks(c->n) : 0; },
                    none);
     patch[sw] = seg([&](const mrcm_ctx* c, int) {
-      return sw < c->sweeps ? (c->m + gp - 1) / gp : 0;
+      return sw < c->sweeps ? (c->m + gp.groups - 1) / gp.groups : 0;
     }, none);
   }
   const Seg sum = seg([](const mrcm_ctx* c, int) { return c->noflow ? mrcm::vec_blocks(c->n) : 0; },
@@ -1311,7 +1316,7 @@ void apply_family(const std::vector<ManyRef>& refs, ManyTables& tb, hipStream_t 
   const mrcm::ManyCol* C = tb.d_cols;
   const int* I = tb.d_ints;
   // the phases of apply_one
-  mrcm::launch_local_many<T, S>(C, I + local.pre, nc, local.blocks, mcl, mbl, s);
+  mrcm::launch_local_many<T, S>(C, I + local.pre, nc, local.blocks, mcl, gl, s);
   mrcm::launch_coarse_rhs_many(C, I + crhs.pre, nc, crhs.blocks, s);
   for (int it = -1; it < nref; ++it) {
     if (it >= 0) mrcm::launch_coarse_resid_many(C, I + resid[it].pre, nc, resid[it].blocks, s);
@@ -1324,7 +1329,7 @@ void apply_family(const std::vector<ManyRef>& refs, ManyTables& tb, hipStream_t 
   mrcm::launch_reconstruct_many<T, S>(C, I + recon.pre, nc, recon.blocks, s);
   for (int sw = 0; sw < nsw; ++sw) {
     mrcm::launch_residual_many<T>(C, I + resd[sw].pre, nc, resd[sw].blocks, s);
-    mrcm::launch_patch_many<T, S>(C, I + patch[sw].pre, nc, patch[sw].blocks, mcp, mbp, s);
+    mrcm::launch_patch_many<T, S>(C, I + patch[sw].pre, nc, patch[sw].blocks, mcp, gp, s);
   }
   mrcm::launch_sum_many<T>(C, I + sum.pre, nc, sum.blocks, s);
   mrcm::launch_finalize_many<T>(C, I + fin.pre, nc, fin.blocks, s);

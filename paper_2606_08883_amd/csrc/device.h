@@ -42,10 +42,17 @@ void launch_rhs(const double* tx, const double* ty, int nx, int ny, const int* b
 
 // ---- preconditioner apply (arithmetic T, factor storage S) ------------------
 // A box (at most 64 cells wide) is solved by one lane group per end of its
-// factor.  Boxes per workgroup of the box kernels (the most that fit; a launch
-// may take fewer, groups_cap > 0, which changes no result); 0 when the boxes are too
-// large.  t, w: bytes of the arithmetic type T and of the factor storage type S.
-int box_groups(int max_bx, int max_cells, size_t t, size_t w);
+// factor.  t, w: bytes of the arithmetic type T and of the factor storage type S.
+// Whether the box kernels take boxes of up to max_bx columns and max_cells cells.
+bool box_fits(int max_bx, int max_cells, size_t t, size_t w);
+// The grid of a launch over m boxes: the code of its kernels' column width, boxes per
+// workgroup and the least number of them (whole waves).  A launch may take fewer than
+// `groups` (groups_cap > 0), which changes no result.  spread: few boxes get a workgroup
+// each.
+struct BoxGrid {
+  int cols, groups, least;
+};
+BoxGrid box_grid(long long m, int max_bx, int max_cells, size_t t, size_t w, bool spread);
 // Source-driven solves on the oversampled boxes (boxes[i]: hat-Omega_i with
 // Omega_i as its owned part): p = the solutions restricted to Omega_i, and
 // the trace moments mU, mP of every coarse dof (dof_side, dof_q, first face
@@ -107,7 +114,6 @@ void launch_convert(const double* src, float* dst, long long n, hipStream_t s);
 // of the oversampled boxes and of the smoothing patches (box i at its
 // coupling offset; as long as the larger of the two coupling arrays).
 // Results equal K one-RHS launches bit for bit.
-size_t box_lds_bytes_k(int k, int max_bx, int max_cells, size_t t, size_t w);
 template <typename T, typename S>
 void launch_local_k(int k, const BoxDesc* boxes, int m, int max_cells, int max_bx, const S* dinv,
                     const S* coup, const double* const* r, T* const* p, T* const* e, int nx,
@@ -182,7 +188,7 @@ struct ManyCol {
 };
 template <typename T, typename S>
 void launch_local_many(const ManyCol* cols, const int* pre, int ncol, int blocks, int max_cells,
-                       int max_bx, hipStream_t s);
+                       BoxGrid g, hipStream_t s);
 void launch_coarse_rhs_many(const ManyCol* cols, const int* pre, int ncol, int blocks,
                             hipStream_t s);
 // Level of the interface solve: column c's chunks first[c] .. of its own
@@ -204,7 +210,7 @@ void launch_residual_many(const ManyCol* cols, const int* pre, int ncol, int blo
                           hipStream_t s);
 template <typename T, typename S>
 void launch_patch_many(const ManyCol* cols, const int* pre, int ncol, int blocks, int max_cells,
-                       int max_bx, hipStream_t s);
+                       BoxGrid g, hipStream_t s);
 template <typename T>
 void launch_sum_many(const ManyCol* cols, const int* pre, int ncol, int blocks, hipStream_t s);
 template <typename T>

@@ -190,8 +190,9 @@ __device__ __forceinline__ Blk hw_blk() { return Blk{(int)blockIdx.x, (int)gridD
 // wherever the boxes do not fill the GPU several times over.
 // A group is one wave: R row lanes, R = 64 for boxes wider than 32 columns, else
 // R = 32 with two lanes per row (halves), which halves
-// the instructions of a row step, the other thing a step waits for.  Lane r of
-// a half owns cell column r of every row.
+// the instructions of a row step, the other thing a step waits for.  Many boxes of up to
+// 16 columns, which fill the GPU, are packed instead: 16 lanes to a group, one per row, four
+// groups to a wave (kPacked).  Lane r of a half owns cell column r of every row.
 // The blocks are symmetric and stored as half blocks (setup_jobs.h): row r's
 // lanes load the entries D(r, r + k), k = 0 .. NB / 2, of each block and fetch
 // D(r, r - k) = D(r - k, r) from the registers of row r - k's lanes.  Exchange
@@ -199,7 +200,7 @@ __device__ __forceinline__ Blk hw_blk() { return Blk{(int)blockIdx.x, (int)gridD
 // slot of LDS, the mirrored entries through cross-lane permutes.  The two groups
 // of a box meet at two workgroup barriers around the middle row.  The row of a
 // step, its addresses and its phase are the same in the whole wave and live in
-// scalar registers; lanes past the box's width repeat its last column (same
+// scalar registers (unless packed); lanes past the box's width repeat its last column (same
 // values to the same addresses), so that a step masks nothing.
 __device__ __forceinline__ void wave_sync() { __builtin_amdgcn_wave_barrier(); }
 
@@ -242,16 +243,25 @@ __device__ __forceinline__ int opaque(int v) {
   return v;
 }
 
+// Boxes of up to 16 columns, packed: the blocks and the arithmetic of column width 16
+// (the same bits) with groups of 16 lanes, one per row, four groups to a wave.  A wave of
+// its own leaves three quarters of the lanes of a narrow box idle, which costs nothing
+// while the boxes do not fill the GPU and up to twice the time once they do
+// (launch_cols).  NB / 2 and the shape of a half block are those of 16.
+constexpr int kPacked = 17;
+
 // Shape of the half blocks of a launch of column width NB: rows 0 .. H, the
 // first K0 of them single words, the others NH quads; R row lanes per half and
-// HV halves per group (one wave).
+// HV halves per group of GL lanes (one wave unless packed).
 template <int NB>
 struct Half {
+  static constexpr bool PACK = NB == kPacked;
   static constexpr int H = NB / 2;
   static constexpr int K0 = half_k0(NB);
   static constexpr int NH = half_quads(NB);
-  static constexpr int R = NB <= 32 ? 32 : 64;
-  static constexpr int HV = 64 / R;
+  static constexpr int R = PACK ? 16 : NB <= 32 ? 32 : 64;
+  static constexpr int HV = PACK ? 1 : 64 / R;
+  static constexpr int GL = R * HV;
   static constexpr int NT = (H + 3) / 4;          // steps of four mirrored entries
   static constexpr int NM = HV == 2 ? 2 * NT : H;  // mirrored entries a lane fetches, at most
   // Place of v in the vector slot: H words hold what lies before it; one more where half
@@ -402,11 +412,13 @@ struct Mirror {
   }
   __device__ Mirror(int rc, int hf, int n) {
     if constexpr (HV == 1) {
+      // the group's first lane
+      const int g0 = Half<NB>::PACK ? (int)(threadIdx.x & 63) / Half<NB>::GL * Half<NB>::GL : 0;
 #pragma unroll
       for (int w = 0; w < (H + 3) / 4; ++w) src[w] = 0;
 #pragma unroll
       for (int k = 1; k <= H; ++k)
-        src[(k - 1) >> 2] |= (4 * col(rc, k, n)) << (8 * ((k - 1) & 3));
+        src[(k - 1) >> 2] |= (4 * (g0 + col(rc, k, n))) << (8 * ((k - 1) & 3));
     } else if constexpr (K0 == 3 && OWN) {
 #pragma unroll
       for (int i = 0; i < 2 * NT; ++i)
@@ -520,16 +532,26 @@ __device__ __forceinline__ T half_dot(const HalfRow<S, NB>& d, const S (&rot)[Ha
 // compiler counts the loads in flight exactly and waits only for the block
 // a step uses; the n % DEPTH last steps, which load nothing, run after the loop
 // (rounding the count up instead ran 24 steps for the 17 to 20 of a 20-wide patch).
+// Packed groups of a wave have different counts: all of them end with the wave's last
+// step and one with fewer starts `late` steps later, on its first block until then
+// (steps below 0; n < 1: it never starts).
 template <typename S, int NB, int DEPTH, typename Step>
-__device__ __forceinline__ void pipelined_sweep(int n, const S* __restrict__ blk, int dir,
-                                                Step step, int bx, int rc, int hf) {
+__device__ __forceinline__ void pipelined_sweep(int n, int late, const S* __restrict__ blk,
+                                                int dir, Step step, int bx, int rc, int hf) {
   const BlockPlaces<S, NB> at(bx, rc, hf);
   HalfRow<S, NB> reg[DEPTH];
-  int left = n - 1;  // blocks after the one at blk
+  constexpr bool PACK = Half<NB>::PACK;
+  int left = n - 1, wait = late;  // blocks after the one at blk; steps before the first
   auto next = [&]() {
-    blk += left > 0 ? dir : 0;
-    --left;
+    const bool go = !PACK || wait <= 0;
+    blk += go && left > 0 ? dir : 0;
+    left -= go ? 1 : 0;
+    if constexpr (PACK) --wait;
   };
+  if constexpr (PACK)
+    n = __builtin_amdgcn_readfirstlane((n > 0 ? n : 0) + late);
+  else
+    late = 0;
 #pragma unroll
   for (int u = 0; u < DEPTH; ++u) {
     load_half<S, NB>(reg[u], blk, at, rc);
@@ -539,14 +561,14 @@ __device__ __forceinline__ void pipelined_sweep(int n, const S* __restrict__ blk
   for (; s0 + DEPTH <= n; s0 += DEPTH) {
 #pragma unroll
     for (int u = 0; u < DEPTH; ++u) {
-      step(s0 + u, reg[u]);
+      step(s0 + u - late, reg[u]);
       load_half<S, NB>(reg[u], blk, at, rc);
       next();
     }
   }
 #pragma unroll
   for (int u = 0; u < DEPTH - 1; ++u)
-    if (s0 + u < n) step(s0 + u, reg[u]);
+    if (s0 + u < n) step(s0 + u - late, reg[u]);
 }
 
 // Words of the group's copy of the step vector for column width NB:
@@ -556,20 +578,39 @@ template <int NB>
 constexpr int vec_words() { return (Half<NB>::V0 + 2 * Half<NB>::R + 3) / 4 * 4; }
 
 // Zero the group's vector slots (count words) before the first step.
-template <typename T>
+template <int GL, typename T>
 __device__ __forceinline__ void zero_slots(T* v, int count) {
-  for (int i = threadIdx.x & 63; i < count; i += 64) v[i] = T(0);
+  for (int i = threadIdx.x % GL; i < count; i += GL) v[i] = T(0);
 }
 
 // Meet the other group of the box, if it has two.  The meeting is the workgroup's: every
 // wave of a launch has to pass the same number of them (two in a box solve, one where the
 // middle row is reached and one when it has been read, whatever the box's rows).
-template <int ENDS>
+// Packed groups of a box share a wave.
+template <typename S, int NB>
 __device__ __forceinline__ void pair_sync() {
-  if constexpr (ENDS == 2)
+  if constexpr (box_ends<S>() == 2 && !Half<NB>::PACK)
     __syncthreads();
   else
     wave_sync();
+}
+
+// Largest value of v over the 64 lanes of the wave, as a wave-uniform value.
+__device__ __forceinline__ int wave_max(int v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const int o = __shfl_xor(v, off, 64);
+    v = o > v ? o : v;
+  }
+  return __builtin_amdgcn_readfirstlane(v);
+}
+// Steps by which a group with n steps starts after the one of its wave with the most.
+template <int NB>
+__device__ __forceinline__ int late_start(int n) {
+  if constexpr (Half<NB>::PACK)
+    return wave_max(n) - n;
+  else
+    return 0;
 }
 
 // The row steps of one end of a box of by rows: from row first, step by dir rows,
@@ -625,52 +666,58 @@ __device__ __forceinline__ void box_solve(T* us, T* vv, const S* cp, const S* __
   // elimination: row j's couplings to the row before it are T_j at end 0 and
   // T_{j+1} at end 1 (none at the first row)
   {
-    int at = st.first * bx, ca = (st.top ? by : 0) * bx;
+    int at = st.first * bx, ca = (st.top && st.n > 1 ? by : 0) * bx;
     T carry = T(0), b = ur[at], c = T(0);
     pipelined_sweep<S, NB, DEPTH>(
-        st.n, Dinv + st.first * bstride, st.dir * bstride,
+        st.n, late_start<NB>(st.n), Dinv + st.first * bstride, st.dir * bstride,
         [&](int s, const HalfRow<S, NB>& d) {
           S rot[Half<NB>::NM];
           mirror_rows<S, NB>(rot, d, mir, hf);
           T y = fmat(c, carry, b);
           if (ENDS == 2 && s == st.n - 1) {
-            pair_sync<ENDS>();  // both ends have reached the middle row
+            pair_sync<S, NB>();  // both ends have reached the middle row
             y = b;
             if (st.h > 0) y = fmat((T)cr[st.h * bx], ur[(st.h - 1) * bx], y);
             if (st.h + 1 < by) y = fmat((T)cr[(st.h + 1) * bx], ur[(st.h + 1) * bx], y);
-            pair_sync<ENDS>();  // both have read it and its neighbours
+            pair_sync<S, NB>();  // both have read it and its neighbours
           }
+          const bool run = !Half<NB>::PACK || s >= 0;  // the group has started
           // the next step's row (the last step stays on its own)
-          const int on = s + 1 < st.n ? dx : 0, cur = at;
+          const int on = run && s + 1 < st.n ? dx : 0, cur = at;
           at += on;
           ca += on;
           b = ur[at];
-          c = (T)cr[ca];
-          carry = product(y, d, rot);
-          if (!(st.top && s == st.n - 1)) ur[cur] = carry;  // end 0 writes the middle row
+          c = run ? (T)cr[ca] : T(0);
+          const T u = product(y, d, rot);
+          carry = run ? u : T(0);
+          if (run && !(st.top && s == st.n - 1)) ur[cur] = u;  // end 0 writes the middle row
         },
         bx, rc, hf);
     xh = carry;
   }
   // substitution: row j's couplings to the row before it are T_{j+1} at end 0 and
   // T_j at end 1
-  if (st.nb > 0) {
-    const int row = st.h - st.dir;
+  const int late = late_start<NB>(st.nb > 0 ? st.nb : 0);
+  if (st.nb > 0 || late > 0) {
+    // (a group without rows stays on the middle one)
+    const int row = st.nb > 0 ? st.h - st.dir : st.h;
     int at = row * bx, ca = (st.top ? row : st.h) * bx;
     T carry = xh, b = ur[at], c = (T)cr[ca];
     pipelined_sweep<S, NB, DEPTH>(
-        st.nb, Dinv + row * bstride, -st.dir * bstride,
+        st.nb, late, Dinv + row * bstride, -st.dir * bstride,
         [&](int s, const HalfRow<S, NB>& d) {
           S rot[Half<NB>::NM];
           mirror_rows<S, NB>(rot, d, mir, hf);
           const T y = c * carry, u = b;
-          const int on = s + 1 < st.nb ? dx : 0, cur = at;
+          const bool run = !Half<NB>::PACK || s >= 0;
+          const int on = run && s + 1 < st.nb ? dx : 0, cur = at;
           at -= on;
           ca -= on;
           b = ur[at];
           c = (T)cr[ca];
-          carry = u + product(y, d, rot);
-          ur[cur] = carry;
+          const T x = u + product(y, d, rot);
+          carry = run ? x : carry;
+          if (run) ur[cur] = x;
         },
         bx, rc, hf);
   }
@@ -682,11 +729,10 @@ __device__ __forceinline__ void box_solve(T* us, T* vv, const S* cp, const S* __
 // turn, both arrays' loads of a run in flight at a time, so that a box of up to
 // 32 rows (16 with one set) costs one memory
 // latency.  Loads are unconditional (row and column clamped into the box).
-template <int NSET, typename T, typename G, typename S>
+template <int NSET, int RUN, typename T, typename G, typename S>
 __device__ __forceinline__ void stage_box(T* dst, const G* __restrict__ src, long long origin,
                                           int nx, S* cdst, const S* __restrict__ csrc, int bx,
                                           int by, int r, int set) {
-  constexpr int RUN = NSET == 4 ? 8 : 16;
   const int col = r < bx ? r : bx - 1;
   const bool act = r < bx;
   for (int jj = 0; jj < by; jj += RUN * NSET) {
@@ -709,19 +755,21 @@ __device__ __forceinline__ void stage_box(T* dst, const G* __restrict__ src, lon
 }
 
 // Copy count (>= 1) contiguous words from global memory into LDS with a
-// box's NL lanes, eight unconditional loads in flight per lane at a time.
+// box's NL lanes, eight (four for a packed pair of groups) unconditional
+// loads in flight per lane at a time.
 template <typename S, int NL>
 __device__ __forceinline__ void words_to_lds(S* dst, const S* __restrict__ src, int count,
                                              int lane) {
-  for (int q0 = 0; q0 < count; q0 += 8 * NL) {
-    S v[8];
+  constexpr int RUN = NL == 32 ? 4 : 8;
+  for (int q0 = 0; q0 < count; q0 += RUN * NL) {
+    S v[RUN];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < RUN; ++u) {
       const int q = q0 + u * NL + lane;
       v[u] = src[q < count ? q : count - 1];
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < RUN; ++u) {
       const int q = q0 + u * NL + lane;
       if (q < count) dst[q] = v[u];
     }
@@ -752,15 +800,19 @@ struct BoxSlot {
 // box's sets of row lanes.
 template <typename S, int NB>
 struct BoxThread {
-  static constexpr int R = Half<NB>::R, HV = Half<NB>::HV;
-  static constexpr int ENDS = box_ends<S>(), NL = ENDS * 64, NSET = ENDS * HV;
+  static constexpr int R = Half<NB>::R, HV = Half<NB>::HV, GL = Half<NB>::GL;
+  static constexpr int ENDS = box_ends<S>(), NL = ENDS * GL, NSET = ENDS * HV;
+  // rows that a set stages at a time: 32 in all, packed or with one set 16
+  static constexpr int RUN = NSET == 4 || (Half<NB>::PACK && NSET == 2) ? 8 : 16;
   int slot, end, lane, r, hf, set, i;
   bool live;
   __device__ BoxThread(int block, int m) {
-    const int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    int g = threadIdx.x / GL;
+    if constexpr (GL == 64) g = __builtin_amdgcn_readfirstlane(g);
+    const int l = threadIdx.x % GL;
     slot = g / ENDS;
     end = g % ENDS;
-    lane = end * 64 + l;
+    lane = end * GL + l;
     r = l % R;
     hf = l / R;
     set = end * HV + hf;
@@ -771,7 +823,8 @@ struct BoxThread {
   // The most faces of a subdomain among the workgroup's boxes (the same in every
   // thread, so that loops with workgroup barriers run the same rounds in all waves).
   __device__ int faces(const BoxDesc* __restrict__ boxes, int block, int m) const {
-    const int n = ENDS == 2 ? (int)(blockDim.x / NL) : 1, i0 = ENDS == 2 ? block * n : i;
+    constexpr bool waves = ENDS == 2 && GL == 64;  // a box is two waves
+    const int n = waves ? (int)(blockDim.x / NL) : 1, i0 = waves ? block * n : i;
     int most = 0;
     for (int q = 0; q < n; ++q) {
       const BoxDesc& d = boxes[i0 + q < m ? i0 + q : m - 1];
@@ -825,68 +878,82 @@ __device__ __forceinline__ void face_cells(const BoxDesc& d, int side, int j, in
 // Flux and pressure moments of the coarse dofs k = (i, side, q) of a subdomain
 // over the faces of their sides: sum_j P_q(xi_j) (cUi p_in + cUo p_out) and
 // likewise with the pressure weights; face_w: the four weights of each face, the
-// subdomain's faces side after side.  v(c) reads the solution at box-local cell
-// c.  The box's NL threads take a face each (flux, pressure and xi_j into buf,
+// subdomain's faces side after side.  v(k, c) reads the solution of column k at
+// box-local cell c; the K columns share what a face needs, their moments are nc apart.
+// The box's NL threads take a face each (flux, pressure and xi_j into buf,
 // 3 NL words of LDS), then one thread per dof adds its side's faces in order:
 // the divisions, weights and cells of all faces cost one pass instead of one per
 // face and dof (14 of k_local's 89 us at 1024^2 in FP64, 8 of 33 us at 505 x 387,
-// were this serial).  The rounds over the faces go to `span`, the workgroup's most
-// (BoxThread::faces): all its waves meet at the same barriers, whatever their boxes' sides.
-// A subdomain has at most 36 dofs (four sides, degree 8): one per thread.
-template <int ENDS, typename V>
-__device__ __forceinline__ void trace_moments(const BoxDesc& d, int lane, bool live, int span,
-                                              const int* __restrict__ dof_side,
+// were this serial; 768 x 768 in 8-wide subdomains, where all lanes are busy, 269 us of T
+// with a search of the dofs for a face's side, 263 with the sides' places).
+// The rounds over the faces go to `span`, the workgroup's most (BoxThread::faces): all its
+// waves meet at the same barriers, whatever their boxes' sides.  A subdomain has at most
+// 36 dofs (four sides, degree 8): one per thread, unless packed.
+template <typename S, int NB, int K, typename V>
+__device__ __forceinline__ void trace_moments(const BoxDesc& d, int nx, int lane, bool live,
+                                              int span, const int* __restrict__ dof_side,
                                               const int* __restrict__ dof_q,
                                               const int* __restrict__ dof_face0, int k0, int nd,
                                               const double* __restrict__ face_w, double* buf,
                                               V v, double* __restrict__ mU,
-                                              double* __restrict__ mP) {
-  constexpr int NL = ENDS * 64;
+                                              double* __restrict__ mP, long long nc) {
+  constexpr int NL = BoxThread<S, NB>::NL;
   const int f0 = dof_face0[k0];
   const int last = dof_face0[k0 + nd - 1] - f0 +
                    (dof_side[k0 + nd - 1] <= 1 ? d.oby : d.obx);  // faces of the subdomain
-  const bool mine = lane < nd;
-  const int k = k0 + (mine ? lane : 0);
-  const int side = dof_side[k], q = dof_q[k], len = side <= 1 ? d.oby : d.obx;
-  const int fa = dof_face0[k] - f0;
-  double su = 0.0, sp = 0.0;
-  for (int base = 0; base < span; base += NL) {
-    const int f = base + lane;
-    if (f < last) {
-      // the face's side: the last dof whose faces start at or before it
-      int fs = 0, fb = 0;
-      for (int e = 0; e < nd; ++e) {
-        const int b = dof_face0[k0 + e] - f0;
-        if (b <= f) {
-          fs = dof_side[k0 + e];
-          fb = b;
-        }
+  // the sides W, E, S, N that have faces (those inside the grid), one after the other
+  const int xw = d.x0 + d.ox, west = xw > 0 ? d.oby : 0;
+  const int east = west + (xw + d.obx < nx ? d.oby : 0);
+  const int south = east + (d.y0 + d.oy > 0 ? d.obx : 0);
+  for (int kb = 0; kb < (NL >= 64 ? 1 : nd); kb += NL) {
+    const bool mine = kb + lane < nd;
+    const int dof = k0 + (mine ? kb + lane : 0);
+    const int side = dof_side[dof], q = dof_q[dof], len = side <= 1 ? d.oby : d.obx;
+    const int fa = dof_face0[dof] - f0;
+    double su[K], sp[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) su[k] = sp[k] = 0.0;
+    for (int base = 0; base < span; base += NL) {
+      const int f = base + lane;
+      f64x2 wu = {0.0, 0.0}, wp = {0.0, 0.0};
+      int ci = 0, co = 0;
+      if (f < last) {
+        const int fs = f < west ? 0 : f < east ? 1 : f < south ? 2 : 3;
+        const int fb = fs == 0 ? 0 : fs == 1 ? west : fs == 2 ? east : south;
+        const f64x2* w = reinterpret_cast<const f64x2*>(face_w + 4LL * (f0 + f));
+        wu = w[0];
+        wp = w[1];
+        const int j = f - fb;
+        face_cells(d, fs, j, ci, co);
+        buf[2 * NL + lane] = (2.0 * j + 1.0) / (fs <= 1 ? d.oby : d.obx) - 1.0;
       }
-      const f64x2* w = reinterpret_cast<const f64x2*>(face_w + 4LL * (f0 + f));
-      const f64x2 wu = w[0], wp = w[1];
-      const int j = f - fb;
-      int ci, co;
-      face_cells(d, fs, j, ci, co);
-      const double pin = v(ci), pout = v(co);
-      buf[lane] = fmat(wu[1], pout, wu[0] * pin);
-      buf[NL + lane] = fmat(wp[1], pout, wp[0] * pin);
-      buf[2 * NL + lane] = (2.0 * j + 1.0) / (fs <= 1 ? d.oby : d.obx) - 1.0;
-    }
-    pair_sync<ENDS>();
-    if (mine) {
       const int a = fa > base ? fa : base;
       const int b = fa + len < base + NL ? fa + len : base + NL;
-      for (int t = a; t < b; ++t) {
-        const double lw = legendre_at(q, buf[2 * NL + t - base]);
-        su = fmat(lw, buf[t - base], su);
-        sp = fmat(lw, buf[NL + t - base], sp);
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        if (f < last) {
+          const double pin = v(k, ci), pout = v(k, co);
+          buf[lane] = fmat(wu[1], pout, wu[0] * pin);
+          buf[NL + lane] = fmat(wp[1], pout, wp[0] * pin);
+        }
+        pair_sync<S, NB>();
+        if (mine) {
+          for (int t = a; t < b; ++t) {
+            const double lw = legendre_at(q, buf[2 * NL + t - base]);
+            su[k] = fmat(lw, buf[t - base], su[k]);
+            sp[k] = fmat(lw, buf[NL + t - base], sp[k]);
+          }
+        }
+        pair_sync<S, NB>();
       }
     }
-    pair_sync<ENDS>();
-  }
-  if (mine && live) {
-    mU[k] = su;
-    mP[k] = sp;
+    if (mine && live) {
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        mU[k * nc + dof] = su[k];
+        mP[k * nc + dof] = sp[k];
+      }
+    }
   }
 }
 
@@ -909,16 +976,16 @@ __device__ __forceinline__ void local_body(
   const BoxDesc d = boxes[t.i];
   const int bx = d.bx, by = d.by;
   const long long origin = (long long)d.y0 * nx + d.x0;
-  stage_box<BT::NSET>(L.us, r, origin, nx, L.cp, coup + d.coff, bx, by, t.r, t.set);
-  zero_slots(L.vv, vec_words<NB>());
-  pair_sync<BT::ENDS>();
+  stage_box<BT::NSET, BT::RUN>(L.us, r, origin, nx, L.cp, coup + d.coff, bx, by, t.r, t.set);
+  zero_slots<BT::GL>(L.vv, vec_words<NB>());
+  pair_sync<S, NB>();
   if (d.pin) {  // one box covers the grid: the same in every group
     if (t.lane == 0) L.us[0] = T(0);
-    pair_sync<BT::ENDS>();
+    pair_sync<S, NB>();
   }
   box_solve<T, S, NB>(L.us, L.vv, L.cp, dinv + d.doff, bx, by, d.bs, t.r, t.hf, t.end,
                             trace_lo(d), trace_hi(d));
-  pair_sync<BT::ENDS>();
+  pair_sync<S, NB>();
   if (t.live && t.r >= d.ox && t.r < d.ox + d.obx) {
     const long long o2 = origin + (long long)d.oy * nx;
     for (int j = t.set; j < d.oby; j += BT::NSET)
@@ -926,9 +993,9 @@ __device__ __forceinline__ void local_body(
   }
   const int k0 = dof_off[t.i], nd = dof_off[t.i + 1] - k0;
   if (nd > 0)  // none where one subdomain is the grid, the only box then
-    trace_moments<BT::ENDS>(d, t.lane, t.live, t.faces(boxes, blk.id, m), dof_side, dof_q,
-                                    dof_face0, k0, nd, face_w, reinterpret_cast<double*>(L.cp),
-                                    [&](int c) { return (double)L.us[c]; }, mU, mP);
+    trace_moments<S, NB, 1>(d, nx, t.lane, t.live, t.faces(boxes, blk.id, m), dof_side, dof_q,
+                            dof_face0, k0, nd, face_w, reinterpret_cast<double*>(L.cp),
+                            [&](int, int c) { return (double)L.us[c]; }, mU, mP, 0);
 }
 template <typename T, typename S, int NB>
 __global__ void MRCM_BOX_KERNEL(T, S, NB)
@@ -1392,19 +1459,19 @@ __device__ __forceinline__ void patch_body(const Blk blk, const BoxDesc* __restr
   const BoxDesc d = boxes[t.i];
   const int bx = d.bx, by = d.by;
   const long long origin = (long long)d.y0 * nx + d.x0;
-  stage_box<BT::NSET>(L.us, rho, origin, nx, L.cp, coup + d.coff, bx, by, t.r, t.set);
-  zero_slots(L.vv, vec_words<NB>());
-  pair_sync<BT::ENDS>();
+  stage_box<BT::NSET, BT::RUN>(L.us, rho, origin, nx, L.cp, coup + d.coff, bx, by, t.r, t.set);
+  zero_slots<BT::GL>(L.vv, vec_words<NB>());
+  pair_sync<S, NB>();
   if (d.pin) {  // one box covers the grid: the same in every group
     if (t.lane == 0) L.us[0] = T(0);
-    pair_sync<BT::ENDS>();
+    pair_sync<S, NB>();
   }
   box_solve<T, S, NB>(L.us, L.vv, L.cp, dinv + d.doff, bx, by, d.bs, t.r, t.hf, t.end,
                             d.oy, d.oy + d.oby - 1);
-  pair_sync<BT::ENDS>();
+  pair_sync<S, NB>();
   // p += e on the owned cells, each set of row lanes a run of rows in turn, all
   // of a run's read-modify-writes in flight
-  constexpr int RUN = BT::NSET == 4 ? 4 : BT::NSET == 2 ? 8 : 16;
+  constexpr int RUN = BT::RUN == 8 ? 4 : BT::NSET == 2 ? 8 : 16;
   const bool own = t.live && t.r >= d.ox && t.r < d.ox + d.obx;
   const int col = own ? t.r : d.ox;
   const long long o2 = origin + (long long)d.oy * nx;
@@ -1925,7 +1992,7 @@ __device__ __forceinline__ void box_solve_k(const In* const (&in)[K], long long 
     wave_sync();
   };
   {
-    int row = st.first, ca = (st.top ? by : 0) * bx;
+    int row = st.first, ca = (st.top && st.n > 1 ? by : 0) * bx;
     T carry[K], nxt[K], c = T(0);
     auto fetch = [&]() {
 #pragma unroll
@@ -1938,10 +2005,11 @@ __device__ __forceinline__ void box_solve_k(const In* const (&in)[K], long long 
     for (int k = 0; k < K; ++k) carry[k] = T(0);
     fetch();
     pipelined_sweep<S, NB, DEPTH>(
-        st.n, Dinv + st.first * bstride, st.dir * bstride,
+        st.n, late_start<NB>(st.n), Dinv + st.first * bstride, st.dir * bstride,
         [&](int s, const HalfRow<S, NB>& d) {
           S rot[Half<NB>::NM];
           mirror_rows<S, NB>(rot, d, mir, hf);
+          const bool run = !Half<NB>::PACK || s >= 0;  // the group has started
           T b[K], y[K];
 #pragma unroll
           for (int k = 0; k < K; ++k) {
@@ -1949,15 +2017,15 @@ __device__ __forceinline__ void box_solve_k(const In* const (&in)[K], long long 
             y[k] = fmat(c, carry[k], b[k]);
           }
           const int cur = row;
-          row += s + 1 < st.n ? st.dir : 0;
-          ca += s + 1 < st.n ? dx : 0;
+          row += run && s + 1 < st.n ? st.dir : 0;
+          ca += run && s + 1 < st.n ? dx : 0;
           fetch();
-          c = (T)cr[ca];
+          c = run ? (T)cr[ca] : T(0);
           if (ENDS == 2 && s == st.n - 1) {
             // both ends have reached the middle row: exchange the rows next to it
 #pragma unroll
             for (int k = 0; k < K; ++k) vv[k * VW + V0 + rc] = carry[k];
-            pair_sync<ENDS>();
+            pair_sync<S, NB>();
             const T cl = (T)cr[st.h * bx], ch = (T)cr[(st.h + 1 < by ? st.h + 1 : st.h) * bx];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -1966,20 +2034,25 @@ __device__ __forceinline__ void box_solve_k(const In* const (&in)[K], long long 
               if (st.h > 0) y[k] = fmat(cl, st.top ? o : carry[k], y[k]);
               if (st.h + 1 < by) y[k] = fmat(ch, st.top ? carry[k] : o, y[k]);
             }
-            pair_sync<ENDS>();
+            pair_sync<S, NB>();
           }
           product(y, d, rot, carry);
-          if (own && !(st.top && s == st.n - 1))
+          if (own && run && !(st.top && s == st.n - 1))
 #pragma unroll
             for (int k = 0; k < K; ++k) work[k][cur * wstride + r] = carry[k];
+          if constexpr (Half<NB>::PACK)
+#pragma unroll
+            for (int k = 0; k < K; ++k) carry[k] = run ? carry[k] : T(0);
         },
         bx, rc, hf);
 #pragma unroll
     for (int k = 0; k < K; ++k) xh[k] = carry[k];
   }
   group_fence();  // lanes of the wave read back the rows that others of it wrote
-  if (st.nb > 0) {
-    int row = st.h - st.dir, ca = (st.top ? row : st.h) * bx;
+  const int late = late_start<NB>(st.nb > 0 ? st.nb : 0);
+  if (st.nb > 0 || late > 0) {
+    // (a group without rows stays on the middle one)
+    int row = st.nb > 0 ? st.h - st.dir : st.h, ca = (st.top ? row : st.h) * bx;
     T carry[K], nxt[K], c = (T)cr[ca];
     auto fetch = [&]() {
 #pragma unroll
@@ -1989,10 +2062,11 @@ __device__ __forceinline__ void box_solve_k(const In* const (&in)[K], long long 
     for (int k = 0; k < K; ++k) carry[k] = xh[k];
     fetch();
     pipelined_sweep<S, NB, DEPTH>(
-        st.nb, Dinv + row * bstride, -st.dir * bstride,
+        st.nb, late, Dinv + row * bstride, -st.dir * bstride,
         [&](int s, const HalfRow<S, NB>& d) {
           S rot[Half<NB>::NM];
           mirror_rows<S, NB>(rot, d, mir, hf);
+          const bool run = !Half<NB>::PACK || s >= 0;
           T u[K], y[K], acc[K];
 #pragma unroll
           for (int k = 0; k < K; ++k) {
@@ -2000,21 +2074,21 @@ __device__ __forceinline__ void box_solve_k(const In* const (&in)[K], long long 
             y[k] = c * carry[k];
           }
           const int cur = row;
-          row -= s + 1 < st.nb ? st.dir : 0;
-          ca -= s + 1 < st.nb ? dx : 0;
+          row -= run && s + 1 < st.nb ? st.dir : 0;
+          ca -= run && s + 1 < st.nb ? dx : 0;
           fetch();
           c = (T)cr[ca];
           product(y, d, rot, acc);
 #pragma unroll
-          for (int k = 0; k < K; ++k) carry[k] = u[k] + acc[k];
-          if (own)
+          for (int k = 0; k < K; ++k) carry[k] = run ? u[k] + acc[k] : carry[k];
+          if (own && run)
 #pragma unroll
             for (int k = 0; k < K; ++k) work[k][cur * wstride + r] = carry[k];
         },
         bx, rc, hf);
   }
   group_fence();
-  pair_sync<ENDS>();
+  pair_sync<S, NB>();
 }
 
 // LDS slot of one box for K right-hand sides:
@@ -2059,8 +2133,8 @@ __global__ void __launch_bounds__(kBoxThreads)
     work[k] = e.v[k] + d.coff;
   }
   words_to_lds<S, BT::NL>(L.cp, coup + d.coff, bx * by, t.lane);
-  zero_slots(L.vv, K * vec_words<NB>());
-  pair_sync<BT::ENDS>();
+  zero_slots<BT::GL>(L.vv, K * vec_words<NB>());
+  pair_sync<S, NB>();
   box_solve_k<T, S, NB, K, double>(in, nx, work, bx, L.vv, L.other, L.cp, dinv + d.doff, bx, by,
                                    d.bs, t.r, t.hf, t.end, t.live, d.pin != 0,
                                    trace_lo(d), trace_hi(d));
@@ -2072,16 +2146,11 @@ __global__ void __launch_bounds__(kBoxThreads)
         p.v[k][o2 + (long long)j * nx + t.r] = work[k][(long long)(d.oy + j) * bx + t.r];
   }
   const int k0 = dof_off[t.i], nd = dof_off[t.i + 1] - k0;
-  const int span = t.faces(boxes, blockIdx.x, m);
   if (nd > 0)  // as in local_body
-#pragma unroll 1
-    for (int k = 0; k < K; ++k) {
-      const T* wk = e.v[k] + d.coff;
-      trace_moments<BT::ENDS>(d, t.lane, t.live, span, dof_side, dof_q, dof_face0, k0, nd,
-                                      face_w, reinterpret_cast<double*>(L.cp),
-                                      [&](int c) { return (double)wk[c]; },
-                                      mU + (long long)k * nc, mP + (long long)k * nc);
-    }
+    trace_moments<S, NB, K>(d, nx, t.lane, t.live, t.faces(boxes, blockIdx.x, m), dof_side, dof_q,
+                            dof_face0, k0, nd, face_w, reinterpret_cast<double*>(L.cp),
+                            [&](int k, int c) { return (double)(e.v[k] + d.coff)[c]; }, mU, mP,
+                            nc);
 }
 
 // k_patch for K right-hand sides: e_k = A[S_i]^-1 rho_k[S_i], built in the
@@ -2107,13 +2176,14 @@ __global__ void __launch_bounds__(kBoxThreads)
     work[k] = e.v[k] + d.coff;
   }
   words_to_lds<S, BT::NL>(L.cp, coup + d.coff, bx * by, t.lane);
-  zero_slots(L.vv, K * vec_words<NB>());
-  pair_sync<BT::ENDS>();
+  zero_slots<BT::GL>(L.vv, K * vec_words<NB>());
+  pair_sync<S, NB>();
   box_solve_k<T, S, NB, K, T>(in, nx, work, bx, L.vv, L.other, L.cp, dinv + d.doff, bx, by,
                               d.bs, t.r, t.hf, t.end, t.live, d.pin != 0, d.oy,
                               d.oy + d.oby - 1);
-  // p += e on the owned cells, each set of row lanes a run of eight rows in
+  // p += e on the owned cells, each set of row lanes a run of rows in
   // turn, all of a run's read-modify-writes in flight
+  constexpr int RUN = Half<NB>::PACK && BT::NSET == 2 ? 4 : 8;
   const bool own = t.live && t.r >= d.ox && t.r < d.ox + d.obx;
   const int col = own ? t.r : d.ox;
   const long long o2 = origin + (long long)d.oy * nx;
@@ -2122,17 +2192,17 @@ __global__ void __launch_bounds__(kBoxThreads)
   for (int k = 0; k < K; ++k) {
     T* pk = p.v[k];
     const T* ek = work[k] + (long long)d.oy * bx;
-    for (int jj = 0; jj < rows; jj += 8 * BT::NSET) {
-      const int j0 = jj + 8 * t.set;
-      T v[8], ev[8];
+    for (int jj = 0; jj < rows; jj += RUN * BT::NSET) {
+      const int j0 = jj + RUN * t.set;
+      T v[RUN], ev[RUN];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < RUN; ++u) {
         const int j = j0 + u < d.oby ? j0 + u : d.oby - 1;
         v[u] = pk[o2 + (long long)j * nx + col];
         ev[u] = ek[(long long)j * bx + col];
       }
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
+      for (int u = 0; u < RUN; ++u)
         if (own && j0 + u < d.oby) pk[o2 + (long long)(j0 + u) * nx + t.r] = v[u] + ev[u];
     }
   }
@@ -2523,17 +2593,19 @@ void launch_rhs(const double* tx, const double* ty, int nx, int ny, const int* b
                      bc[1], bc[2], bc[3], f, g, h, b);
 }
 
-// Column width (registers) for boxes up to max_bx cells wide, row lanes of a
-// group, and threads of one box (a wave per end of its factor: two where the
-// factors are FP64); w: bytes of the factor storage type.
+// Column width (registers) for boxes up to max_bx cells wide; ends of a factor; threads of
+// one box of column width code nb (a wave per end of its factor, or 16 lanes packed);
+// w: bytes of the factor storage type.
 inline int col_width(int max_bx) { return box_cols(max_bx); }
-inline int row_lanes(int max_bx) { return max_bx <= 32 ? 32 : 64; }
 inline int ends_of(size_t w) { return w == 8 ? 2 : 1; }
-inline int box_threads(size_t w) { return 64 * ends_of(w); }
+inline int box_threads(int nb, size_t w) {
+  return (nb == kPacked ? Half<kPacked>::GL : 64) * ends_of(w);
+}
 // Words of a group's vector slot (vec_words of the kernels).
-inline int vec_slot_words(int max_bx) {
-  switch (col_width(max_bx)) {
+inline int vec_slot_words(int nb) {
+  switch (nb) {
     case 16: return vec_words<16>();
+    case kPacked: return vec_words<kPacked>();
     case 20: return vec_words<20>();
     case 24: return vec_words<24>();
     case 32: return vec_words<32>();
@@ -2550,16 +2622,16 @@ inline int round16(long long x, size_t w) {
 }
 // Words of a box's coupling area: the couplings, or the trace moments' buffer
 // (three FP64 words per thread of the box) where that is larger.
-inline int coupling_words(int max_cells, size_t w) {
-  const long long buf = 3LL * box_threads(w) * (8 / (long long)w);
+inline int coupling_words(int nb, int max_cells, size_t w) {
+  const long long buf = 3LL * box_threads(nb, w) * (8 / (long long)w);
   return round16(max_cells > buf ? max_cells : buf, w);
 }
 // LDS bytes of one box: the vector slots of its groups and the box
 // (arithmetic words t) and the coupling area (storage words w), rounded to 16
 // bytes.
-inline size_t group_bytes(int max_bx, int max_cells, size_t t, size_t w) {
-  const size_t b = (size_t)ends_of(w) * vec_slot_words(max_bx) * t +
-                   (size_t)coupling_words(max_cells, w) * w + (size_t)max_cells * t;
+inline size_t group_bytes(int nb, int max_cells, size_t t, size_t w) {
+  const size_t b = (size_t)ends_of(w) * vec_slot_words(nb) * t +
+                   (size_t)coupling_words(nb, max_cells, w) * w + (size_t)max_cells * t;
   return (b + 15) / 16 * 16;
 }
 // Boxes are accepted up to kBoxLds bytes for one vector slot of whole lane groups (16
@@ -2567,19 +2639,43 @@ inline size_t group_bytes(int max_bx, int max_cells, size_t t, size_t w) {
 // launch takes: with the second slot, wider slots and the moments' buffer the largest
 // accepted boxes ask for up to kBoxLdsMax (16 x 254 in FP64: 66 176 bytes).
 constexpr size_t kBoxLds = 64 * 1024, kBoxLdsMax = kBoxLds + 8192;
-inline bool box_fits(int max_bx, int max_cells, size_t t, size_t w) {
-  const int lanes = max_bx <= 16 ? 16 : row_lanes(max_bx);
+bool box_fits(int max_bx, int max_cells, size_t t, size_t w) {
+  const int lanes = max_bx <= 16 ? 16 : max_bx <= 32 ? 32 : 64;
   const size_t slot = (col_width(max_bx) / 2 + 2 * lanes + 3) / 4 * 4;
   const size_t b = slot * t + (size_t)round16(max_cells, w) * w + (size_t)max_cells * t;
   return (b + 15) / 16 * 16 <= kBoxLds;
 }
-// Boxes per workgroup: up to 256 threads, fewer when the boxes' LDS would
-// exceed 64 KB (0 when a box is not accepted).
-int box_groups(int max_bx, int max_cells, size_t t, size_t w) {
-  const int bt = box_threads(w);
-  for (int groups = kBoxThreads / bt; groups > 1; groups /= 2)
-    if (groups * group_bytes(max_bx, max_cells, t, w) <= kBoxLds) return groups;
-  return box_fits(max_bx, max_cells, t, w) ? 1 : 0;
+// Column width code of a launch over m boxes: boxes of up to 16 columns are packed where
+// one wave per end gives the GPU more than two waves per SIMD (256 CUs of four).  One column
+// of T, a wave per end and packed: 256 x 256 in 8-wide subdomains, 1024 boxes, FP64 (2048
+// waves) 74, 75 us; 480 x 480, 12-wide, 1600 boxes, FP64 106, 98, FP32 storage (1600 waves)
+// 102, 109; 256 x 256, 4-wide, 4096 boxes, FP32 storage 117, 111; 768 x 768, 8-wide, 9216
+// boxes, FP64 309, 263 (278 with one-ended factors, four boxes to a wave).
+constexpr long long kPackWaves = 2 * 4 * 256;
+inline int launch_cols(long long m, int max_bx, size_t w) {
+  const int nb = col_width(max_bx);
+  return nb == 16 && m * ends_of(w) > kPackWaves ? kPacked : nb;
+}
+// The most boxes a workgroup of up to 256 threads takes in whole waves, `bytes` of LDS each
+// (0: not one wave's).
+inline int most_groups(int nb, size_t w, size_t bytes) {
+  const int bt = box_threads(nb, w);
+  for (int groups = kBoxThreads / bt; groups * bt >= 64 && groups > 0; groups /= 2)
+    if (groups * bytes <= kBoxLds) return groups;
+  return 0;
+}
+BoxGrid box_grid(long long m, int max_bx, int max_cells, size_t t, size_t w, bool spread) {
+  int nb = launch_cols(m, max_bx, w);
+  if (nb == kPacked) {
+    const int groups = most_groups(kPacked, w, group_bytes(kPacked, max_cells, t, w));
+    if (groups > 0) return BoxGrid{kPacked, groups, 64 / box_threads(kPacked, w)};
+    nb = 16;  // tall boxes: not a wave's worth of them in LDS
+  }
+  // few boxes get a workgroup each, so that they spread over the CUs (up to four waves
+  // per CU)
+  if (spread && m * box_threads(nb, w) <= 4LL * 64 * 256) return BoxGrid{nb, 1, 1};
+  const int groups = most_groups(nb, w, group_bytes(nb, max_cells, t, w));
+  return BoxGrid{nb, groups > 0 ? groups : 1, 1};
 }
 // Launch a box kernel with shm bytes of LDS (past 64 KB gfx950 has to be asked).
 template <typename... A, typename... B>
@@ -2591,37 +2687,46 @@ void launch_box(void (*kernel)(A...), dim3 grid, dim3 block, size_t shm, hipStre
     throw Error(MRCM_EDEVICE, "no workgroup with the LDS of a box");
   hipLaunchKernelGGL(kernel, grid, block, shm, s, args...);
 }
-#define MRCM_BOX_DISPATCH(KERNEL, T, S, max_bx, ...)                     \
-  do {                                                                         \
-    switch (col_width(max_bx)) {                                               \
-      case 16: launch_box(KERNEL<T, S, 16>, __VA_ARGS__); break;               \
-      case 20: launch_box(KERNEL<T, S, 20>, __VA_ARGS__); break;               \
-      case 24: launch_box(KERNEL<T, S, 24>, __VA_ARGS__); break;               \
-      case 32: launch_box(KERNEL<T, S, 32>, __VA_ARGS__); break;               \
-      case 36: launch_box(KERNEL<T, S, 36>, __VA_ARGS__); break;               \
-      case 40: launch_box(KERNEL<T, S, 40>, __VA_ARGS__); break;               \
-      case 48: launch_box(KERNEL<T, S, 48>, __VA_ARGS__); break;               \
-      default: launch_box(KERNEL<T, S, 64>, __VA_ARGS__); break;               \
-    }                                                                          \
+#define MRCM_BOX_DISPATCH(KERNEL, T, S, nb, ...)                          \
+  do {                                                                    \
+    switch (nb) {                                                         \
+      case 16: launch_box(KERNEL<T, S, 16>, __VA_ARGS__); break;          \
+      case kPacked: launch_box(KERNEL<T, S, kPacked>, __VA_ARGS__); break; \
+      case 20: launch_box(KERNEL<T, S, 20>, __VA_ARGS__); break;          \
+      case 24: launch_box(KERNEL<T, S, 24>, __VA_ARGS__); break;          \
+      case 32: launch_box(KERNEL<T, S, 32>, __VA_ARGS__); break;          \
+      case 36: launch_box(KERNEL<T, S, 36>, __VA_ARGS__); break;          \
+      case 40: launch_box(KERNEL<T, S, 40>, __VA_ARGS__); break;          \
+      case 48: launch_box(KERNEL<T, S, 48>, __VA_ARGS__); break;          \
+      default: launch_box(KERNEL<T, S, 64>, __VA_ARGS__); break;          \
+    }                                                                     \
   } while (0)
-// Boxes per workgroup of a launch over m boxes: few boxes get a workgroup each, so
-// that they spread over the CUs (up to four waves per CU).
-inline int launch_groups(int m, int max_bx, int max_cells, size_t t, size_t w) {
-  if ((long long)m * box_threads(w) <= 4LL * 64 * 256) return 1;
-  return box_groups(max_bx, max_cells, t, w);
-}
+// The grid of a launch over m boxes, capped at groups_cap boxes per workgroup, and its
+// LDS: bytes of a box and words of its coupling area.
+struct BoxLaunch {
+  int nb, gb, cp_words;
+  dim3 grid, block;
+  size_t shm;
+  BoxLaunch(int m, int max_bx, int max_cells, size_t t, size_t w, int groups_cap) {
+    const BoxGrid g = box_grid(m, max_bx, max_cells, t, w, true);
+    nb = g.cols;
+    int groups = g.groups;
+    if (groups_cap > 0 && groups_cap < groups) groups = groups_cap > g.least ? groups_cap : g.least;
+    gb = (int)group_bytes(nb, max_cells, t, w);
+    cp_words = coupling_words(nb, max_cells, w);
+    grid = dim3((m + groups - 1) / groups);
+    block = dim3(groups * box_threads(nb, w));
+    shm = (size_t)groups * gb;
+  }
+};
 template <typename T, typename S>
 void launch_local(const BoxDesc* boxes, int m, int max_cells, int max_bx, const S* dinv,
                   const S* coup, const double* r, T* p, int nx, const int* dof_off,
                   const int* dof_side, const int* dof_q, const int* dof_face0,
                   const double* face_w, double* mU, double* mP, hipStream_t s, int groups_cap) {
-  int groups = launch_groups(m, max_bx, max_cells, sizeof(T), sizeof(S));
-  if (groups_cap > 0 && groups_cap < groups) groups = groups_cap;
-  const int gb = (int)group_bytes(max_bx, max_cells, sizeof(T), sizeof(S));
-  const size_t shm = (size_t)groups * gb;
-  const int cp_words = coupling_words(max_cells, sizeof(S));
-  const dim3 grid((m + groups - 1) / groups), block(groups * box_threads(sizeof(S)));
-  MRCM_BOX_DISPATCH(k_local, T, S, max_bx, grid, block, shm, s, boxes, m, gb, cp_words, dinv, coup, r, p, nx, dof_off, dof_side, dof_q, dof_face0, face_w, mU, mP);
+  const BoxLaunch l(m, max_bx, max_cells, sizeof(T), sizeof(S), groups_cap);
+  MRCM_BOX_DISPATCH(k_local, T, S, l.nb, l.grid, l.block, l.shm, s, boxes, m, l.gb, l.cp_words,
+                    dinv, coup, r, p, nx, dof_off, dof_side, dof_q, dof_face0, face_w, mU, mP);
 }
 
 void launch_coarse_rhs(const int4* gsrc, const double* gscale, const double* mU,
@@ -2686,13 +2791,9 @@ void launch_residual(const T* tx, const T* ty, int nx, int ny, const double* r, 
 template <typename T, typename S>
 void launch_patch(const BoxDesc* boxes, int m, int max_cells, int max_bx, const S* dinv,
                   const S* coup, const T* rho, T* p, int nx, hipStream_t s, int groups_cap) {
-  int groups = launch_groups(m, max_bx, max_cells, sizeof(T), sizeof(S));
-  if (groups_cap > 0 && groups_cap < groups) groups = groups_cap;
-  const int gb = (int)group_bytes(max_bx, max_cells, sizeof(T), sizeof(S));
-  const size_t shm = (size_t)groups * gb;
-  const int cp_words = coupling_words(max_cells, sizeof(S));
-  const dim3 grid((m + groups - 1) / groups), block(groups * box_threads(sizeof(S)));
-  MRCM_BOX_DISPATCH(k_patch, T, S, max_bx, grid, block, shm, s, boxes, m, gb, cp_words, dinv, coup, rho, p, nx);
+  const BoxLaunch l(m, max_bx, max_cells, sizeof(T), sizeof(S), groups_cap);
+  MRCM_BOX_DISPATCH(k_patch, T, S, l.nb, l.grid, l.block, l.shm, s, boxes, m, l.gb, l.cp_words,
+                    dinv, coup, rho, p, nx);
 }
 
 // ---- K right-hand sides per launch ----
@@ -2707,46 +2808,66 @@ void check_k(int k) {
   if (k != 2 && k != 4 && k != 8)
     throw Error(MRCM_EINVAL, "multi-RHS launch of unsupported width");
 }
-inline size_t group_bytes_k(int k, int max_bx, int max_cells, size_t t, size_t w) {
-  const size_t b = (size_t)ends_of(w) * k * vec_slot_words(max_bx) * t +
-                   (size_t)coupling_words(max_cells, w) * w;
+inline size_t group_bytes_k(int k, int nb, int max_cells, size_t t, size_t w) {
+  const size_t b = (size_t)ends_of(w) * k * vec_slot_words(nb) * t +
+                   (size_t)coupling_words(nb, max_cells, w) * w;
   return (b + 15) / 16 * 16;
 }
-int box_groups_k(int k, int max_bx, int max_cells, size_t t, size_t w) {
-  const int bt = box_threads(w);
-  for (int groups = kBoxThreads / bt; groups >= 1; groups /= 2)
-    if (groups * group_bytes_k(k, max_bx, max_cells, t, w) <= 64 * 1024) return groups;
-  return 0;
-}
+// As BoxLaunch, for k columns.
+struct BoxLaunchK {
+  int nb, gb;
+  dim3 grid, block;
+  size_t shm;
+  BoxLaunchK(int k, int m, int max_bx, int max_cells, size_t t, size_t w) {
+    nb = launch_cols(m, max_bx, w);
+    int groups = most_groups(nb, w, group_bytes_k(k, nb, max_cells, t, w));
+    if (nb == kPacked && groups <= 0) {
+      nb = 16;
+      groups = most_groups(nb, w, group_bytes_k(k, nb, max_cells, t, w));
+    }
+    if (groups <= 0) throw Error(MRCM_EINVAL, "boxes too large for a multi-RHS launch");
+    gb = (int)group_bytes_k(k, nb, max_cells, t, w);
+    grid = dim3((m + groups - 1) / groups);
+    block = dim3(groups * box_threads(nb, w));
+    shm = (size_t)groups * gb;
+  }
+};
 }  // namespace
-
-size_t box_lds_bytes_k(int k, int max_bx, int max_cells, size_t t, size_t w) {
-  const int groups = box_groups_k(k, max_bx, max_cells, t, w);
-  return groups ? groups * group_bytes_k(k, max_bx, max_cells, t, w) : ~(size_t)0;
-}
 
 // Right-hand sides one box launch takes at most, by column width: what the
 // lane's registers hold without spilling (quads in flight, four partial sums
-// and the rows of every column); 1 = the one-RHS kernels, once per column.
-inline int box_width_k(int nb, size_t w) {
+// and the rows of every column); 1 = the one-RHS kernels, once per column.  Packed, a lane
+// holds a whole row: eight columns spill 148 bytes and four in FP64 leave one wave per SIMD
+// (768 x 768 in 4-wide subdomains, four columns of T: 2342 us, two at a time 2260).
+constexpr int box_width_k(int nb, size_t w) {
+  if (nb == kPacked) return w == 8 ? 2 : 4;
   if (w == 8) return nb <= 16 ? 4 : nb <= 48 ? 2 : 1;
   return nb <= 16 ? 8 : nb <= 32 ? 4 : nb <= 48 ? 2 : 1;
 }
 
-#define MRCM_BOX_DISPATCH_K(KERNEL, T, S, nb, kk, ...)                                  \
-  do {                                                                                 \
-    if (nb == 16 && kk == 8) hipLaunchKernelGGL((KERNEL<T, S, 16, 8>), __VA_ARGS__);   \
-    else if (nb == 16 && kk == 4) hipLaunchKernelGGL((KERNEL<T, S, 16, 4>), __VA_ARGS__); \
-    else if (nb == 16) hipLaunchKernelGGL((KERNEL<T, S, 16, 2>), __VA_ARGS__);         \
-    else if (nb == 20 && kk == 4) hipLaunchKernelGGL((KERNEL<T, S, 20, 4>), __VA_ARGS__); \
-    else if (nb == 20) hipLaunchKernelGGL((KERNEL<T, S, 20, 2>), __VA_ARGS__);         \
-    else if (nb == 24 && kk == 4) hipLaunchKernelGGL((KERNEL<T, S, 24, 4>), __VA_ARGS__); \
-    else if (nb == 24) hipLaunchKernelGGL((KERNEL<T, S, 24, 2>), __VA_ARGS__);         \
-    else if (nb == 32 && kk == 4) hipLaunchKernelGGL((KERNEL<T, S, 32, 4>), __VA_ARGS__); \
-    else if (nb == 32) hipLaunchKernelGGL((KERNEL<T, S, 32, 2>), __VA_ARGS__);         \
-    else if (nb == 36) hipLaunchKernelGGL((KERNEL<T, S, 36, 2>), __VA_ARGS__);         \
-    else if (nb == 40) hipLaunchKernelGGL((KERNEL<T, S, 40, 2>), __VA_ARGS__);         \
-    else hipLaunchKernelGGL((KERNEL<T, S, 48, 2>), __VA_ARGS__);                       \
+#define MRCM_BOX_CASE_K(KERNEL, T, S, NB, K, ...)            \
+  case 16 * NB + K:                                          \
+    if constexpr (K <= box_width_k(NB, sizeof(S)))           \
+      launch_box(KERNEL<T, S, NB, K>, __VA_ARGS__);          \
+    break;
+#define MRCM_BOX_DISPATCH_K(KERNEL, T, S, nb, kk, ...)       \
+  do {                                                       \
+    switch (16 * (nb) + (kk)) {                              \
+      MRCM_BOX_CASE_K(KERNEL, T, S, 16, 8, __VA_ARGS__)      \
+      MRCM_BOX_CASE_K(KERNEL, T, S, 16, 4, __VA_ARGS__)      \
+      MRCM_BOX_CASE_K(KERNEL, T, S, 16, 2, __VA_ARGS__)      \
+      MRCM_BOX_CASE_K(KERNEL, T, S, kPacked, 4, __VA_ARGS__) \
+      MRCM_BOX_CASE_K(KERNEL, T, S, kPacked, 2, __VA_ARGS__) \
+      MRCM_BOX_CASE_K(KERNEL, T, S, 20, 4, __VA_ARGS__)      \
+      MRCM_BOX_CASE_K(KERNEL, T, S, 20, 2, __VA_ARGS__)      \
+      MRCM_BOX_CASE_K(KERNEL, T, S, 24, 4, __VA_ARGS__)      \
+      MRCM_BOX_CASE_K(KERNEL, T, S, 24, 2, __VA_ARGS__)      \
+      MRCM_BOX_CASE_K(KERNEL, T, S, 32, 4, __VA_ARGS__)      \
+      MRCM_BOX_CASE_K(KERNEL, T, S, 32, 2, __VA_ARGS__)      \
+      MRCM_BOX_CASE_K(KERNEL, T, S, 36, 2, __VA_ARGS__)      \
+      MRCM_BOX_CASE_K(KERNEL, T, S, 40, 2, __VA_ARGS__)      \
+      MRCM_BOX_CASE_K(KERNEL, T, S, 48, 2, __VA_ARGS__)      \
+    }                                                        \
   } while (0)
 #define MRCM_K_DISPATCH(k, CALL) \
   do {                           \
@@ -2769,7 +2890,7 @@ void launch_local_k(int k, const BoxDesc* boxes, int m, int max_cells, int max_b
                     const int* dof_face0, const double* face_w, double* mU, double* mP, int nc,
                     hipStream_t s) {
   check_k(k);
-  const int nb = col_width(max_bx), kk = std::min(k, box_width_k(nb, sizeof(S)));
+  const int kk = std::min(k, box_width_k(launch_cols(m, max_bx, sizeof(S)), sizeof(S)));
   for (int k0 = 0; k0 < k; k0 += kk) {
     double* u = mU + (long long)k0 * nc;
     double* v = mP + (long long)k0 * nc;
@@ -2778,14 +2899,12 @@ void launch_local_k(int k, const BoxDesc* boxes, int m, int max_cells, int max_b
                          dof_side, dof_q, dof_face0, face_w, u, v, s);
       continue;
     }
-    const int groups = box_groups_k(kk, max_bx, max_cells, sizeof(T), sizeof(S));
-    const size_t shm = box_lds_bytes_k(kk, max_bx, max_cells, sizeof(T), sizeof(S));
-    const int gb = (int)group_bytes_k(kk, max_bx, max_cells, sizeof(T), sizeof(S));
-    const dim3 grid((m + groups - 1) / groups), block(groups * box_threads(sizeof(S)));
+    const BoxLaunchK l(kk, m, max_bx, max_cells, sizeof(T), sizeof(S));
     const RhsPtrs<const double> rp = rhs_ptrs(kk, r + k0);
     const RhsPtrs<T> pp = rhs_ptrs(kk, p + k0), ep = rhs_ptrs(kk, e + k0);
-    MRCM_BOX_DISPATCH_K(k_local_k, T, S, nb, kk, grid, block, shm, s, boxes, m, gb, dinv, coup,
-                        rp, pp, ep, nx, dof_off, dof_side, dof_q, dof_face0, face_w, u, v, nc);
+    MRCM_BOX_DISPATCH_K(k_local_k, T, S, l.nb, kk, l.grid, l.block, l.shm, s, boxes, m, l.gb,
+                        dinv, coup, rp, pp, ep, nx, dof_off, dof_side, dof_q, dof_face0, face_w, u,
+                        v, nc);
   }
 }
 
@@ -2891,20 +3010,17 @@ void launch_patch_k(int k, const BoxDesc* boxes, int m, int max_cells, int max_b
                     const S* coup, const T* const* rho, T* const* p, T* const* e, int nx,
                     hipStream_t s) {
   check_k(k);
-  const int nb = col_width(max_bx), kk = std::min(k, box_width_k(nb, sizeof(S)));
+  const int kk = std::min(k, box_width_k(launch_cols(m, max_bx, sizeof(S)), sizeof(S)));
   for (int k0 = 0; k0 < k; k0 += kk) {
     if (kk == 1) {
       launch_patch<T, S>(boxes, m, max_cells, max_bx, dinv, coup, rho[k0], p[k0], nx, s);
       continue;
     }
-    const int groups = box_groups_k(kk, max_bx, max_cells, sizeof(T), sizeof(S));
-    const size_t shm = box_lds_bytes_k(kk, max_bx, max_cells, sizeof(T), sizeof(S));
-    const int gb = (int)group_bytes_k(kk, max_bx, max_cells, sizeof(T), sizeof(S));
-    const dim3 grid((m + groups - 1) / groups), block(groups * box_threads(sizeof(S)));
+    const BoxLaunchK l(kk, m, max_bx, max_cells, sizeof(T), sizeof(S));
     const RhsPtrs<const T> rp = rhs_ptrs(kk, rho + k0);
     const RhsPtrs<T> pp = rhs_ptrs(kk, p + k0), ep = rhs_ptrs(kk, e + k0);
-    MRCM_BOX_DISPATCH_K(k_patch_k, T, S, nb, kk, grid, block, shm, s, boxes, m, gb, dinv, coup,
-                        rp, pp, ep, nx);
+    MRCM_BOX_DISPATCH_K(k_patch_k, T, S, l.nb, kk, l.grid, l.block, l.shm, s, boxes, m, l.gb,
+                        dinv, coup, rp, pp, ep, nx);
   }
 }
 
@@ -3158,14 +3274,13 @@ __global__ void __launch_bounds__(kVecThreads)
 
 template <typename T, typename S>
 void launch_local_many(const ManyCol* cols, const int* pre, int ncol, int blocks, int max_cells,
-                       int max_bx, hipStream_t s) {
+                       BoxGrid g, hipStream_t s) {
   if (blocks <= 0) return;
-  const int groups = box_groups(max_bx, max_cells, sizeof(T), sizeof(S));
-  const int gb = (int)group_bytes(max_bx, max_cells, sizeof(T), sizeof(S));
-  const int cp_words = coupling_words(max_cells, sizeof(S));
-  MRCM_BOX_DISPATCH(k_local_many, T, S, max_bx, dim3(blocks),
-                    dim3(groups * box_threads(sizeof(S))), (size_t)groups * gb, s, cols, pre, ncol,
-                    gb, cp_words);
+  const int gb = (int)group_bytes(g.cols, max_cells, sizeof(T), sizeof(S));
+  const int cp_words = coupling_words(g.cols, max_cells, sizeof(S));
+  MRCM_BOX_DISPATCH(k_local_many, T, S, g.cols, dim3(blocks),
+                    dim3(g.groups * box_threads(g.cols, sizeof(S))), (size_t)g.groups * gb, s, cols,
+                    pre, ncol, gb, cp_words);
 }
 void launch_coarse_rhs_many(const ManyCol* cols, const int* pre, int ncol, int blocks,
                             hipStream_t s) {
@@ -3211,14 +3326,13 @@ void launch_residual_many(const ManyCol* cols, const int* pre, int ncol, int blo
 }
 template <typename T, typename S>
 void launch_patch_many(const ManyCol* cols, const int* pre, int ncol, int blocks, int max_cells,
-                       int max_bx, hipStream_t s) {
+                       BoxGrid g, hipStream_t s) {
   if (blocks <= 0) return;
-  const int groups = box_groups(max_bx, max_cells, sizeof(T), sizeof(S));
-  const int gb = (int)group_bytes(max_bx, max_cells, sizeof(T), sizeof(S));
-  const int cp_words = coupling_words(max_cells, sizeof(S));
-  MRCM_BOX_DISPATCH(k_patch_many, T, S, max_bx, dim3(blocks),
-                    dim3(groups * box_threads(sizeof(S))), (size_t)groups * gb, s, cols, pre, ncol,
-                    gb, cp_words);
+  const int gb = (int)group_bytes(g.cols, max_cells, sizeof(T), sizeof(S));
+  const int cp_words = coupling_words(g.cols, max_cells, sizeof(S));
+  MRCM_BOX_DISPATCH(k_patch_many, T, S, g.cols, dim3(blocks),
+                    dim3(g.groups * box_threads(g.cols, sizeof(S))), (size_t)g.groups * gb, s, cols,
+                    pre, ncol, gb, cp_words);
 }
 template <typename T>
 void launch_sum_many(const ManyCol* cols, const int* pre, int ncol, int blocks, hipStream_t s) {
@@ -3268,10 +3382,10 @@ void launch_norm_scale_many(const ManyCol* cols, const int* pre, int ncol, int b
                                               T* const*, int, hipStream_t);                     \
   template void launch_patch_k<T, S>(int, const BoxDesc*, int, int, int, const S*, const S*,    \
                                      const T* const*, T* const*, T* const*, int, hipStream_t); \
-  template void launch_local_many<T, S>(const ManyCol*, const int*, int, int, int, int,         \
+  template void launch_local_many<T, S>(const ManyCol*, const int*, int, int, int, BoxGrid,     \
                                         hipStream_t);                                           \
   template void launch_reconstruct_many<T, S>(const ManyCol*, const int*, int, int, hipStream_t); \
-  template void launch_patch_many<T, S>(const ManyCol*, const int*, int, int, int, int,         \
+  template void launch_patch_many<T, S>(const ManyCol*, const int*, int, int, int, BoxGrid,     \
                                         hipStream_t);
 #define MRCM_INSTANTIATE_T(T)                                                                  \
   template void launch_residual<T>(const T*, const T*, int, int, const double*, const T*, T*,   \
