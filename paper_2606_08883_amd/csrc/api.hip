@@ -602,7 +602,7 @@ void autotune(mrcm_ctx* c, hipStream_t s) {
       return best;
     };
     auto group_opts = [&](int max_bx, int max_cells) {
-      const mrcm::BoxGrid g = mrcm::box_grid(c->m, max_bx, max_cells, sizeof(T), sizeof(S), true);
+      const mrcm::BoxGrid g = mrcm::box_grid(c->m, max_bx, max_cells, sizeof(T), sizeof(S), false);
       std::vector<int> o{g.groups};
       for (int h = g.groups / 2; h >= g.least && (int)o.size() < 3; h /= 2) o.push_back(h);
       return o;
@@ -1227,8 +1227,8 @@ void apply_family(const std::vector<ManyRef>& refs, ManyTables& tb, hipStream_t 
   if (!mrcm::box_fits(mbl, mcl, sizeof(T), sizeof(S)) ||
       (nsw > 0 && !mrcm::box_fits(mbp, mcp, sizeof(T), sizeof(S))))
     throw mrcm::Error(MRCM_EINVAL, "boxes too large for a launch over several contexts");
-  const mrcm::BoxGrid gl = mrcm::box_grid(nboxes, mbl, mcl, sizeof(T), sizeof(S), false);
-  const mrcm::BoxGrid gp = mrcm::box_grid(nboxes, mbp, mcp, sizeof(T), sizeof(S), false);
+  const mrcm::BoxGrid gl = mrcm::box_grid(nboxes, mbl, mcl, sizeof(T), sizeof(S), true);
+  const mrcm::BoxGrid gp = mrcm::box_grid(nboxes, mbp, mcp, sizeof(T), sizeof(S), true);
   // workgroup ranges: prefix sums of per-column counts (and first chunks)
   std::vector<int> ints;
   struct Seg {

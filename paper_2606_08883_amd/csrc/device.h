@@ -47,12 +47,14 @@ void launch_rhs(const double* tx, const double* ty, int nx, int ny, const int* b
 bool box_fits(int max_bx, int max_cells, size_t t, size_t w);
 // The grid of a launch over m boxes: the code of its kernels' column width, boxes per
 // workgroup and the least number of them (whole waves).  A launch may take fewer than
-// `groups` (groups_cap > 0), which changes no result.  spread: few boxes get a workgroup
-// each.
+// `groups` (groups_cap > 0), which changes no result.  many: the launch is one over several
+// contexts; in others few boxes get a workgroup each.
+// dense: there are more waves than SIMDs.
 struct BoxGrid {
   int cols, groups, least;
+  bool dense;
 };
-BoxGrid box_grid(long long m, int max_bx, int max_cells, size_t t, size_t w, bool spread);
+BoxGrid box_grid(long long m, int max_bx, int max_cells, size_t t, size_t w, bool many);
 // Source-driven solves on the oversampled boxes (boxes[i]: hat-Omega_i with
 // Omega_i as its owned part): p = the solutions restricted to Omega_i, and
 // the trace moments mU, mP of every coarse dof (dof_side, dof_q, first face

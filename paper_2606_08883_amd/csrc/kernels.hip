@@ -192,7 +192,8 @@ __device__ __forceinline__ Blk hw_blk() { return Blk{(int)blockIdx.x, (int)gridD
 // R = 32 with two lanes per row (halves), which halves
 // the instructions of a row step, the other thing a step waits for.  Many boxes of up to
 // 16 columns, which fill the GPU, are packed instead: 16 lanes to a group, one per row, four
-// groups to a wave (kPacked).  Lane r of a half owns cell column r of every row.
+// groups to a wave, or 32 lanes for up to 20 columns (kPacked16, kPacked20).  Lane r of a
+// half owns cell column r of every row.
 // The blocks are symmetric and stored as half blocks (setup_jobs.h): row r's
 // lanes load the entries D(r, r + k), k = 0 .. NB / 2, of each block and fetch
 // D(r, r - k) = D(r - k, r) from the registers of row r - k's lanes.  Exchange
@@ -243,23 +244,24 @@ __device__ __forceinline__ int opaque(int v) {
   return v;
 }
 
-// Boxes of up to 16 columns, packed: the blocks and the arithmetic of column width 16
-// (the same bits) with groups of 16 lanes, one per row, four groups to a wave.  A wave of
-// its own leaves three quarters of the lanes of a narrow box idle, which costs nothing
-// while the boxes do not fill the GPU and up to twice the time once they do
-// (launch_cols).  NB / 2 and the shape of a half block are those of 16.
-constexpr int kPacked = 17;
+// Packed forms of boxes of up to 16 and of 17 to 20 columns: the blocks and the arithmetic
+// of column widths 16 and 20 (the same bits) with groups of 16 and 32 lanes, one per row,
+// four and two groups to a wave.  A wave of its own leaves lanes of a narrow box idle, which
+// costs nothing while the boxes do not fill the GPU and up to twice the time once they do
+// (launch_cols).  The codes are odd: NB / 2 and the shape of a half block are those of
+// NB - 1.
+constexpr int kPacked16 = 17, kPacked20 = 21;
 
 // Shape of the half blocks of a launch of column width NB: rows 0 .. H, the
 // first K0 of them single words, the others NH quads; R row lanes per half and
 // HV halves per group of GL lanes (one wave unless packed).
 template <int NB>
 struct Half {
-  static constexpr bool PACK = NB == kPacked;
+  static constexpr bool PACK = NB % 2 == 1;
   static constexpr int H = NB / 2;
   static constexpr int K0 = half_k0(NB);
   static constexpr int NH = half_quads(NB);
-  static constexpr int R = PACK ? 16 : NB <= 32 ? 32 : 64;
+  static constexpr int R = NB == kPacked16 ? 16 : NB <= 32 ? 32 : 64;
   static constexpr int HV = PACK ? 1 : 64 / R;
   static constexpr int GL = R * HV;
   static constexpr int NT = (H + 3) / 4;          // steps of four mirrored entries
@@ -306,21 +308,36 @@ constexpr int block_regs() {
   return (int)sizeof(S) / 4 *
          (Half<NB>::HV == 1 ? half_rows(NB) : 2 * Half<NB>::NH + (Half<NB>::K0 == 3 ? 2 : 1));
 }
-// Waves per SIMD the compiler may aim for in the one-column box kernels.  Left
-// alone it gives up loads in flight for one wave more: with FP32 factors in FP64
-// arithmetic it held 36- to 64-wide boxes to 110 to 149 registers and waited for
-// each block (T on 512 x 512 in 32-wide subdomains, 64-wide oversampled boxes: 271 us, at
-// two waves 184; 40- and 36-wide boxes with two sweeps 212, 182; 1500 x 1500, one
-// sweep, 429, 410).  The others lose where many boxes share a CU (24-wide FP64 at 1024 x
-// 1024: 75.2 us, at three waves 77.3, at two 84.5; 32-wide FP64 gains 1.5 of
-// 16.6 us for 33 boxes and loses 0.7% of T for 2500).
-template <typename T, typename S, int NB>
-constexpr int box_waves() {
-  return sizeof(T) == 8 && sizeof(S) == 4 && NB >= 36 ? 2 : 8;
+// Waves per SIMD the compiler aims for in the box kernels of one box per item, at least and
+// at most.  DENSE: launches over several contexts (of 48-wide FP32 factors in FP64
+// arithmetic only past a wave per SIMD, box_dense) and, for FP64 boxes of 37 to 48 columns, one
+// column past a wave per SIMD.  Left alone the compiler gives up loads in flight for one wave
+// more, or takes a few registers too many for two.  Measured, left alone and as here, us:
+//   one column of T, FP32 factors in FP64 arithmetic, 512 x 512, 64-wide boxes   271   184
+//     (40- and 36-wide boxes, two sweeps)                                        212   182
+//   one column, FP64, local: 1024 boxes 40 wide / 576 of 48                  102 129   91 119
+//     (144 boxes 48 wide, T: 136, on the DENSE kernels 156)
+//   four columns over contexts, local and patch: FP32, 1024 boxes 36 wide    193 153  158 141
+//     FP32, 576 of 48 / 256 of 64                            227 196 143 124  190 160  92 77
+//     FP64, 1024 of 36 / 576 of 48 (spills 32 bytes)         282 350 381 332  280 277 303 262
+//     (FP64 64 wide at two waves: 171 173, left alone 80 72)
+// At three waves FP64 24 wide loses (1024 x 1024: 75.2, 77.3, at two 84.5).
+template <typename T, typename S, int NB, bool DENSE>
+constexpr int box_most_waves() {
+  return (sizeof(T) == 8 && sizeof(S) == 4 && NB >= 36) || (DENSE && sizeof(T) == 4 && NB >= 36)
+             ? 2
+             : 8;
 }
-#define MRCM_BOX_KERNEL(T, S, NB)    \
-  __launch_bounds__(kBoxThreads) \
-      __attribute__((amdgpu_waves_per_eu(1, box_waves<T, S, NB>())))
+template <typename T, typename S, int NB, bool DENSE>
+constexpr int box_least_waves() {
+  return !DENSE                                                                 ? 1
+         : (sizeof(S) == 8 && NB >= 36 && NB <= 48) || (sizeof(T) == 8 && NB == 48) ? 2
+         : sizeof(T) == 4 && NB <= 32 && !Half<NB>::PACK                        ? 4
+                                                                                : 1;
+}
+#define MRCM_BOX_KERNEL(T, S, NB, DENSE)                                                \
+  __launch_bounds__(kBoxThreads) __attribute__((amdgpu_waves_per_eu(                    \
+      box_least_waves<T, S, NB, DENSE>(), box_most_waves<T, S, NB, DENSE>())))
 // Blocks in flight per lane, 2 or 4: as many as about 64 VGPRs of rows hold (more
 // would cost waves per SIMD; 36-wide FP32 patches with four in flight instead
 // of two were a third slower).
@@ -467,6 +484,21 @@ __device__ __forceinline__ void mirror_rows(S (&rot)[Half<NB>::NM], const HalfRo
   }
 }
 
+// One lane per row: the mirrored entry k that is added i-th (1 .. H) and its partial sum,
+// k = 1 .. H in turn, or the order of two lanes per row in FP64 arithmetic with three single
+// words (Mirror, OWN): k = 3 .. H, then 1 and 2.
+template <typename T, int NB>
+constexpr bool own_order() { return Half<NB>::PACK && Half<NB>::K0 == 3 && sizeof(T) == 8; }
+template <typename T, int NB>
+__device__ constexpr int mirror_k(int i) {
+  return !own_order<T, NB>() ? i : i <= Half<NB>::H - 2 ? i + 2 : i - (Half<NB>::H - 2);
+}
+template <typename T, int NB>
+__device__ constexpr int mirror_sum(int i) {
+  const int k = mirror_k<T, NB>(i);
+  return !own_order<T, NB>() ? (k - 1) & 3 : k >= 3 ? (k - 3) & 3 : 2 * k - 1;
+}
+
 // acc = sum_c D(rc, c) v[c]: the rows k against vo[k] = v[(rc + k)
 // mod n], the mirrored entries against vr[-k] = v[(rc - k) mod n] (vo and vr
 // point into the group's doubled copy of v); four partial sums shorten the
@@ -474,7 +506,7 @@ __device__ __forceinline__ void mirror_rows(S (&rot)[Half<NB>::NM], const HalfRo
 // sums 2 hf and 2 hf + 1 (vo and vr shifted by 2 hf by the caller), so the result
 // is that of one lane, bit for bit, unless half hf takes the mirrored words it holds
 // (Mirror).
-template <typename T, typename S, int NB>
+template <typename T, typename S, int NB, bool DENSE>
 __device__ __forceinline__ T half_dot(const HalfRow<S, NB>& d, const S (&rot)[Half<NB>::NM],
                                       const T* vo, const T* vr, int hf) {
   constexpr int NH = Half<NB>::NH, K0 = Half<NB>::K0, H = Half<NB>::H, NT = Half<NB>::NT;
@@ -486,8 +518,14 @@ __device__ __forceinline__ T half_dot(const HalfRow<S, NB>& d, const S (&rot)[Ha
       for (int i = 0; i < 4; ++i) a[i] = fmat((T)d.q[q][i], vo[K0 + 4 * q + i], a[i]);
 #pragma unroll
     for (int k = 0; k < K0; ++k) a[k] = fmat((T)d.h[k], vo[k], a[k]);
+    // fewer vector words in registers at a time, so that two waves fit
+    if constexpr (DENSE && sizeof(T) == 8 && sizeof(S) == 4 && NB == 48)
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int k = 1; k <= H; ++k) a[(k - 1) & 3] = fmat((T)rot[k - 1], vr[-k], a[(k - 1) & 3]);
+    for (int i = 1; i <= H; ++i) {
+      const int k = mirror_k<T, NB>(i), p = mirror_sum<T, NB>(i);
+      a[p] = fmat((T)rot[k - 1], vr[-k], a[p]);
+    }
     return (a[0] + a[1]) + (a[2] + a[3]);
   } else {
     T a[2] = {T(0), T(0)};
@@ -639,7 +677,7 @@ struct EndSteps {
 // type of the factors, T the arithmetic and vector type (FP32 factors may be
 // applied in FP64 arithmetic).  A step waits for its vector's way through LDS and
 // for its sums; what it reads of us and cp is fetched one step ahead.
-template <typename T, typename S, int NB>
+template <typename T, typename S, int NB, bool DENSE>
 __device__ __forceinline__ void box_solve(T* us, T* vv, const S* cp, const S* __restrict__ Dinv,
                                           int bx, int by, int bstride, int r, int hf, int end,
                                           int lo, int hi) {
@@ -659,7 +697,7 @@ __device__ __forceinline__ void box_solve(T* us, T* vv, const S* cp, const S* __
     put[0] = y;
     if constexpr (HV == 1) put[bx] = y;
     wave_sync();
-    const T acc = half_dot<T, S, NB>(d, rot, vo, vr, hf);
+    const T acc = half_dot<T, S, NB, DENSE>(d, rot, vo, vr, hf);
     wave_sync();
     return acc;
   };
@@ -755,12 +793,10 @@ __device__ __forceinline__ void stage_box(T* dst, const G* __restrict__ src, lon
 }
 
 // Copy count (>= 1) contiguous words from global memory into LDS with a
-// box's NL lanes, eight (four for a packed pair of groups) unconditional
-// loads in flight per lane at a time.
-template <typename S, int NL>
+// box's NL lanes, RUN unconditional loads in flight per lane at a time.
+template <typename S, int NL, int RUN>
 __device__ __forceinline__ void words_to_lds(S* dst, const S* __restrict__ src, int count,
                                              int lane) {
-  constexpr int RUN = NL == 32 ? 4 : 8;
   for (int q0 = 0; q0 < count; q0 += RUN * NL) {
     S v[RUN];
 #pragma unroll
@@ -802,8 +838,8 @@ template <typename S, int NB>
 struct BoxThread {
   static constexpr int R = Half<NB>::R, HV = Half<NB>::HV, GL = Half<NB>::GL;
   static constexpr int ENDS = box_ends<S>(), NL = ENDS * GL, NSET = ENDS * HV;
-  // rows that a set stages at a time: 32 in all, packed or with one set 16
-  static constexpr int RUN = NSET == 4 || (Half<NB>::PACK && NSET == 2) ? 8 : 16;
+  // rows that a set stages at a time: 32 in all, with one set or for the narrowest 16
+  static constexpr int RUN = NSET == 4 || (NB == kPacked16 && NSET == 2) ? 8 : 16;
   int slot, end, lane, r, hf, set, i;
   bool live;
   __device__ BoxThread(int block, int m) {
@@ -961,7 +997,7 @@ __device__ __forceinline__ void trace_moments(const BoxDesc& d, int nx, int lane
 // oversampled problem on hat-Omega_i (box d) with source r and zero Robin
 // data, p = its restriction to Omega_i (the owned cells of d), fused with
 // the trace moments of the coarse right-hand side (FP64 sums).
-template <typename T, typename S, int NB>
+template <typename T, typename S, int NB, bool DENSE>
 __device__ __forceinline__ void local_body(
     const Blk blk, const BoxDesc* __restrict__ boxes, int m, int group_bytes, int cp_words,
     const S* __restrict__ dinv, const S* __restrict__ coup, const double* __restrict__ r,
@@ -983,7 +1019,7 @@ __device__ __forceinline__ void local_body(
     if (t.lane == 0) L.us[0] = T(0);
     pair_sync<S, NB>();
   }
-  box_solve<T, S, NB>(L.us, L.vv, L.cp, dinv + d.doff, bx, by, d.bs, t.r, t.hf, t.end,
+  box_solve<T, S, NB, DENSE>(L.us, L.vv, L.cp, dinv + d.doff, bx, by, d.bs, t.r, t.hf, t.end,
                             trace_lo(d), trace_hi(d));
   pair_sync<S, NB>();
   if (t.live && t.r >= d.ox && t.r < d.ox + d.obx) {
@@ -997,8 +1033,8 @@ __device__ __forceinline__ void local_body(
                             dof_face0, k0, nd, face_w, reinterpret_cast<double*>(L.cp),
                             [&](int, int c) { return (double)L.us[c]; }, mU, mP, 0);
 }
-template <typename T, typename S, int NB>
-__global__ void MRCM_BOX_KERNEL(T, S, NB)
+template <typename T, typename S, int NB, bool DENSE>
+__global__ void MRCM_BOX_KERNEL(T, S, NB, DENSE)
     k_local(const BoxDesc* __restrict__ boxes, int m, int group_bytes, int cp_words,
             const S* __restrict__ dinv, const S* __restrict__ coup,
             const double* __restrict__ r, T* __restrict__ p, int nx,
@@ -1006,7 +1042,7 @@ __global__ void MRCM_BOX_KERNEL(T, S, NB)
             const int* __restrict__ dof_q, const int* __restrict__ dof_face0,
             const double* __restrict__ face_w, double* __restrict__ mU,
             double* __restrict__ mP) {
-  local_body<T, S, NB>(hw_blk(), boxes, m, group_bytes, cp_words, dinv, coup, r, p, nx,
+  local_body<T, S, NB, DENSE>(hw_blk(), boxes, m, group_bytes, cp_words, dinv, coup, r, p, nx,
                              dof_off, dof_side, dof_q, dof_face0, face_w, mU, mP);
 }
 
@@ -1445,7 +1481,7 @@ __global__ void __launch_bounds__(kVecThreads)
 // Restricted additive Schwarz: solve A[S_i] e = rho[S_i] on patch i
 // and add e on the owned subdomain Omega_i (each cell
 // is written by one patch only).
-template <typename T, typename S, int NB>
+template <typename T, typename S, int NB, bool DENSE>
 __device__ __forceinline__ void patch_body(const Blk blk, const BoxDesc* __restrict__ boxes,
                                            int m, int group_bytes, int cp_words,
                                            const S* __restrict__ dinv,
@@ -1466,7 +1502,7 @@ __device__ __forceinline__ void patch_body(const Blk blk, const BoxDesc* __restr
     if (t.lane == 0) L.us[0] = T(0);
     pair_sync<S, NB>();
   }
-  box_solve<T, S, NB>(L.us, L.vv, L.cp, dinv + d.doff, bx, by, d.bs, t.r, t.hf, t.end,
+  box_solve<T, S, NB, DENSE>(L.us, L.vv, L.cp, dinv + d.doff, bx, by, d.bs, t.r, t.hf, t.end,
                             d.oy, d.oy + d.oby - 1);
   pair_sync<S, NB>();
   // p += e on the owned cells, each set of row lanes a run of rows in turn, all
@@ -1490,12 +1526,12 @@ __device__ __forceinline__ void patch_body(const Blk blk, const BoxDesc* __restr
         p[o2 + (long long)(j0 + u) * nx + t.r] = v[u] + L.us[(d.oy + j0 + u) * bx + t.r];
   }
 }
-template <typename T, typename S, int NB>
-__global__ void MRCM_BOX_KERNEL(T, S, NB)
+template <typename T, typename S, int NB, bool DENSE>
+__global__ void MRCM_BOX_KERNEL(T, S, NB, DENSE)
     k_patch(const BoxDesc* __restrict__ boxes, int m, int group_bytes, int cp_words,
             const S* __restrict__ dinv, const S* __restrict__ coup, const T* __restrict__ rho,
             T* __restrict__ p, int nx) {
-  patch_body<T, S, NB>(hw_blk(), boxes, m, group_bytes, cp_words, dinv, coup, rho, p, nx);
+  patch_body<T, S, NB, DENSE>(hw_blk(), boxes, m, group_bytes, cp_words, dinv, coup, rho, p, nx);
 }
 
 template <typename T>
@@ -1876,11 +1912,11 @@ __device__ __forceinline__ void half_dot_k(const HalfRow<S, NB>& d,
     for (int g = 1; g <= H; g += 4) {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int e = g; e < g + 4 && e <= H; ++e) {
+      for (int i = g; i < g + 4 && i <= H; ++i) {
+        const int e = mirror_k<T, NB>(i), p = mirror_sum<T, NB>(i);
         const T de = (T)rot[e - 1];
 #pragma unroll
-        for (int k = 0; k < K; ++k)
-          a[k][(e - 1) & 3] = fmat(de, vr[k * VW - e], a[k][(e - 1) & 3]);
+        for (int k = 0; k < K; ++k) a[k][p] = fmat(de, vr[k * VW - e], a[k][p]);
       }
     }
 #pragma unroll
@@ -2132,7 +2168,8 @@ __global__ void __launch_bounds__(kBoxThreads)
     in[k] = r.v[k] + origin;
     work[k] = e.v[k] + d.coff;
   }
-  words_to_lds<S, BT::NL>(L.cp, coup + d.coff, bx * by, t.lane);
+  words_to_lds<S, BT::NL, (NB == kPacked16 && BT::NSET == 2 ? 4 : 8)>(L.cp, coup + d.coff,
+                                                                      bx * by, t.lane);
   zero_slots<BT::GL>(L.vv, K * vec_words<NB>());
   pair_sync<S, NB>();
   box_solve_k<T, S, NB, K, double>(in, nx, work, bx, L.vv, L.other, L.cp, dinv + d.doff, bx, by,
@@ -2175,7 +2212,8 @@ __global__ void __launch_bounds__(kBoxThreads)
     in[k] = rho.v[k] + origin;
     work[k] = e.v[k] + d.coff;
   }
-  words_to_lds<S, BT::NL>(L.cp, coup + d.coff, bx * by, t.lane);
+  words_to_lds<S, BT::NL, (NB == kPacked16 && BT::NSET == 2 ? 4 : 8)>(L.cp, coup + d.coff,
+                                                                      bx * by, t.lane);
   zero_slots<BT::GL>(L.vv, K * vec_words<NB>());
   pair_sync<S, NB>();
   box_solve_k<T, S, NB, K, T>(in, nx, work, bx, L.vv, L.other, L.cp, dinv + d.doff, bx, by,
@@ -2183,7 +2221,7 @@ __global__ void __launch_bounds__(kBoxThreads)
                               d.oy + d.oby - 1);
   // p += e on the owned cells, each set of row lanes a run of rows in
   // turn, all of a run's read-modify-writes in flight
-  constexpr int RUN = Half<NB>::PACK && BT::NSET == 2 ? 4 : 8;
+  constexpr int RUN = NB == kPacked16 && BT::NSET == 2 ? 4 : 8;
   const bool own = t.live && t.r >= d.ox && t.r < d.ox + d.obx;
   const int col = own ? t.r : d.ox;
   const long long o2 = origin + (long long)d.oy * nx;
@@ -2594,18 +2632,19 @@ void launch_rhs(const double* tx, const double* ty, int nx, int ny, const int* b
 }
 
 // Column width (registers) for boxes up to max_bx cells wide; ends of a factor; threads of
-// one box of column width code nb (a wave per end of its factor, or 16 lanes packed);
+// one box of column width code nb (a wave per end of its factor, fewer lanes packed);
 // w: bytes of the factor storage type.
 inline int col_width(int max_bx) { return box_cols(max_bx); }
 inline int ends_of(size_t w) { return w == 8 ? 2 : 1; }
 inline int box_threads(int nb, size_t w) {
-  return (nb == kPacked ? Half<kPacked>::GL : 64) * ends_of(w);
+  return (nb == kPacked16 ? 16 : nb == kPacked20 ? 32 : 64) * ends_of(w);
 }
 // Words of a group's vector slot (vec_words of the kernels).
 inline int vec_slot_words(int nb) {
   switch (nb) {
     case 16: return vec_words<16>();
-    case kPacked: return vec_words<kPacked>();
+    case kPacked16: return vec_words<kPacked16>();
+    case kPacked20: return vec_words<kPacked20>();
     case 20: return vec_words<20>();
     case 24: return vec_words<24>();
     case 32: return vec_words<32>();
@@ -2638,24 +2677,36 @@ inline size_t group_bytes(int nb, int max_cells, size_t t, size_t w) {
 // lanes for boxes of up to 16 columns), the couplings and the box, which is not what a
 // launch takes: with the second slot, wider slots and the moments' buffer the largest
 // accepted boxes ask for up to kBoxLdsMax (16 x 254 in FP64: 66 176 bytes).
-constexpr size_t kBoxLds = 64 * 1024, kBoxLdsMax = kBoxLds + 8192;
+constexpr size_t kBoxLds = 64 * 1024, kBoxLdsMax = kBoxLds + 8192, kCuLds = 160 * 1024;
 bool box_fits(int max_bx, int max_cells, size_t t, size_t w) {
   const int lanes = max_bx <= 16 ? 16 : max_bx <= 32 ? 32 : 64;
   const size_t slot = (col_width(max_bx) / 2 + 2 * lanes + 3) / 4 * 4;
   const size_t b = slot * t + (size_t)round16(max_cells, w) * w + (size_t)max_cells * t;
   return (b + 15) / 16 * 16 <= kBoxLds;
 }
-// Column width code of a launch over m boxes: boxes of up to 16 columns are packed where
+// Column width code of a launch over m boxes.  Boxes of up to 16 columns are packed where
 // one wave per end gives the GPU more than two waves per SIMD (256 CUs of four).  One column
 // of T, a wave per end and packed: 256 x 256 in 8-wide subdomains, 1024 boxes, FP64 (2048
 // waves) 74, 75 us; 480 x 480, 12-wide, 1600 boxes, FP64 106, 98, FP32 storage (1600 waves)
 // 102, 109; 256 x 256, 4-wide, 4096 boxes, FP32 storage 117, 111; 768 x 768, 8-wide, 9216
 // boxes, FP64 309, 263 (278 with one-ended factors, four boxes to a wave).
-constexpr long long kPackWaves = 2 * 4 * 256;
-inline int launch_cols(long long m, int max_bx, size_t w) {
+// Boxes of 17 to 20 columns are packed past kPack20Boxes where that measured faster: FP32
+// arithmetic over several contexts (four columns of T, 16-wide subdomains: 5184 boxes 239,
+// 228 us, 16 384 boxes 522, 468; 1296 boxes 121, 124), and several columns unless FP32
+// factors are applied in FP64 arithmetic (four columns, 4096 boxes, FP64 628, 593, FP32 430, 415;
+// 2304 boxes 399, 421 and 272, 294).  One column gains nothing (4096 boxes, FP64 102, 103 in
+// the box kernels), FP64 over several contexts neither (16 384 boxes 677, 674).
+constexpr long long kPackWaves = 2 * 4 * 256, kPack20Boxes = 3072;
+constexpr bool pack20_many(size_t t) { return t == 4; }
+constexpr bool pack20_columns(size_t t, size_t w) { return t == w; }
+inline int launch_cols(long long m, int max_bx, size_t w, bool pack20) {
   const int nb = col_width(max_bx);
-  return nb == 16 && m * ends_of(w) > kPackWaves ? kPacked : nb;
+  if (nb == 20 && pack20 && m > kPack20Boxes) return kPacked20;
+  return nb == 16 && m * ends_of(w) > kPackWaves ? kPacked16 : nb;
 }
+// Whether a launch over m boxes has more waves than the GPU has SIMDs, so that kernels of one
+// wave per SIMD would take a second round (box_least_waves).
+inline bool box_dense(long long m, size_t w) { return m * ends_of(w) > 4 * 256; }
 // The most boxes a workgroup of up to 256 threads takes in whole waves, `bytes` of LDS each
 // (0: not one wave's).
 inline int most_groups(int nb, size_t w, size_t bytes) {
@@ -2664,18 +2715,28 @@ inline int most_groups(int nb, size_t w, size_t bytes) {
     if (groups * bytes <= kBoxLds) return groups;
   return 0;
 }
-BoxGrid box_grid(long long m, int max_bx, int max_cells, size_t t, size_t w, bool spread) {
-  int nb = launch_cols(m, max_bx, w);
-  if (nb == kPacked) {
-    const int groups = most_groups(kPacked, w, group_bytes(kPacked, max_cells, t, w));
-    if (groups > 0) return BoxGrid{kPacked, groups, 64 / box_threads(kPacked, w)};
-    nb = 16;  // tall boxes: not a wave's worth of them in LDS
+BoxGrid box_grid(long long m, int max_bx, int max_cells, size_t t, size_t w, bool many) {
+  int nb = launch_cols(m, max_bx, w, many && pack20_many(t));
+  const bool dense = box_dense(m, w);
+  if (nb % 2 == 1) {
+    const int groups = most_groups(nb, w, group_bytes(nb, max_cells, t, w));
+    if (groups > 0) return BoxGrid{nb, groups, 64 / box_threads(nb, w), false};
+    --nb;  // tall boxes: not a wave's worth of them in LDS
   }
   // few boxes get a workgroup each, so that they spread over the CUs (up to four waves
   // per CU)
-  if (spread && m * box_threads(nb, w) <= 4LL * 64 * 256) return BoxGrid{nb, 1, 1};
-  const int groups = most_groups(nb, w, group_bytes(nb, max_cells, t, w));
-  return BoxGrid{nb, groups > 0 ? groups : 1, 1};
+  if (!many && m * box_threads(nb, w) <= 4LL * 64 * 256) return BoxGrid{nb, 1, 1, dense};
+  const size_t bytes = group_bytes(nb, max_cells, t, w);
+  int groups = most_groups(nb, w, bytes);
+  // more large boxes over several contexts than run at once: as many on a CU as its 160 KB
+  // hold (48 x 48 with FP32 factors, 29 KB each: two to a workgroup are four on a CU, one is
+  // five; four columns of 960 x 960 1042, 948 us; without the condition 512 x 512 in 40-wide
+  // boxes 243, 251; 24-wide boxes are held by registers, not LDS: a server's three grids 3057 us,
+  // 3182)
+  if (many && nb >= 36 && groups > 1 && m > 256 * (long long)(kCuLds / (groups * bytes) * groups))
+    for (int g = groups / 2; g >= 1; g /= 2)
+      if (kCuLds / (g * bytes) * g > kCuLds / (groups * bytes) * groups) groups = g;
+  return BoxGrid{nb, groups > 0 ? groups : 1, 1, dense};
 }
 // Launch a box kernel with shm bytes of LDS (past 64 KB gfx950 has to be asked).
 template <typename... A, typename... B>
@@ -2687,29 +2748,71 @@ void launch_box(void (*kernel)(A...), dim3 grid, dim3 block, size_t shm, hipStre
     throw Error(MRCM_EDEVICE, "no workgroup with the LDS of a box");
   hipLaunchKernelGGL(kernel, grid, block, shm, s, args...);
 }
-#define MRCM_BOX_DISPATCH(KERNEL, T, S, nb, ...)                          \
-  do {                                                                    \
-    switch (nb) {                                                         \
-      case 16: launch_box(KERNEL<T, S, 16>, __VA_ARGS__); break;          \
-      case kPacked: launch_box(KERNEL<T, S, kPacked>, __VA_ARGS__); break; \
-      case 20: launch_box(KERNEL<T, S, 20>, __VA_ARGS__); break;          \
-      case 24: launch_box(KERNEL<T, S, 24>, __VA_ARGS__); break;          \
-      case 32: launch_box(KERNEL<T, S, 32>, __VA_ARGS__); break;          \
-      case 36: launch_box(KERNEL<T, S, 36>, __VA_ARGS__); break;          \
-      case 40: launch_box(KERNEL<T, S, 40>, __VA_ARGS__); break;          \
-      case 48: launch_box(KERNEL<T, S, 48>, __VA_ARGS__); break;          \
-      default: launch_box(KERNEL<T, S, 64>, __VA_ARGS__); break;          \
-    }                                                                     \
+#define MRCM_BOX_CASE(KERNEL, T, S, NB, ...) \
+  case NB: launch_box(KERNEL<T, S, NB, false>, __VA_ARGS__); break;
+#define MRCM_BOX_CASE_DENSE(KERNEL, T, S, NB, dense, ...)     \
+  case NB:                                                    \
+    if constexpr (sizeof(S) == 8) {                           \
+      if (dense) {                                            \
+        launch_box(KERNEL<T, S, NB, true>, __VA_ARGS__);      \
+        break;                                                \
+      }                                                       \
+    }                                                         \
+    launch_box(KERNEL<T, S, NB, false>, __VA_ARGS__);         \
+    break;
+#define MRCM_BOX_DISPATCH(KERNEL, T, S, nb, dense, ...)            \
+  do {                                                             \
+    switch (nb) {                                                  \
+      MRCM_BOX_CASE(KERNEL, T, S, 16, __VA_ARGS__)                 \
+      MRCM_BOX_CASE(KERNEL, T, S, kPacked16, __VA_ARGS__)          \
+      MRCM_BOX_CASE(KERNEL, T, S, 20, __VA_ARGS__)                 \
+      MRCM_BOX_CASE(KERNEL, T, S, 24, __VA_ARGS__)                 \
+      MRCM_BOX_CASE(KERNEL, T, S, 32, __VA_ARGS__)                 \
+      MRCM_BOX_CASE(KERNEL, T, S, 36, __VA_ARGS__)                 \
+      MRCM_BOX_CASE_DENSE(KERNEL, T, S, 40, dense, __VA_ARGS__)    \
+      MRCM_BOX_CASE_DENSE(KERNEL, T, S, 48, dense, __VA_ARGS__)    \
+      MRCM_BOX_CASE(KERNEL, T, S, 64, __VA_ARGS__)                 \
+    }                                                              \
+  } while (0)
+#define MRCM_MANY_CASE(KERNEL, T, S, NB, ...) \
+  case NB: launch_box(KERNEL<T, S, NB, true>, __VA_ARGS__); break;
+#define MRCM_MANY_DISPATCH(KERNEL, T, S, nb, dense, ...)               \
+  do {                                                          \
+    switch (nb) {                                               \
+      MRCM_MANY_CASE(KERNEL, T, S, 16, __VA_ARGS__)             \
+      MRCM_MANY_CASE(KERNEL, T, S, kPacked16, __VA_ARGS__)      \
+      MRCM_MANY_CASE(KERNEL, T, S, 20, __VA_ARGS__)             \
+      case kPacked20:                                           \
+        if constexpr (pack20_many(sizeof(T)))                   \
+          launch_box(KERNEL<T, S, kPacked20, true>, __VA_ARGS__); \
+        break;                                                  \
+      MRCM_MANY_CASE(KERNEL, T, S, 24, __VA_ARGS__)             \
+      MRCM_MANY_CASE(KERNEL, T, S, 32, __VA_ARGS__)             \
+      MRCM_MANY_CASE(KERNEL, T, S, 36, __VA_ARGS__)             \
+      MRCM_MANY_CASE(KERNEL, T, S, 40, __VA_ARGS__)             \
+      case 48:                                                  \
+        if constexpr (sizeof(T) == 8 && sizeof(S) == 4) {       \
+          if (!(dense)) {                                       \
+            launch_box(KERNEL<T, S, 48, false>, __VA_ARGS__);   \
+            break;                                              \
+          }                                                     \
+        }                                                       \
+        launch_box(KERNEL<T, S, 48, true>, __VA_ARGS__);        \
+        break;                                                  \
+      MRCM_MANY_CASE(KERNEL, T, S, 64, __VA_ARGS__)             \
+    }                                                           \
   } while (0)
 // The grid of a launch over m boxes, capped at groups_cap boxes per workgroup, and its
 // LDS: bytes of a box and words of its coupling area.
 struct BoxLaunch {
   int nb, gb, cp_words;
+  bool dense;
   dim3 grid, block;
   size_t shm;
   BoxLaunch(int m, int max_bx, int max_cells, size_t t, size_t w, int groups_cap) {
-    const BoxGrid g = box_grid(m, max_bx, max_cells, t, w, true);
+    const BoxGrid g = box_grid(m, max_bx, max_cells, t, w, false);
     nb = g.cols;
+    dense = g.dense;
     int groups = g.groups;
     if (groups_cap > 0 && groups_cap < groups) groups = groups_cap > g.least ? groups_cap : g.least;
     gb = (int)group_bytes(nb, max_cells, t, w);
@@ -2725,8 +2828,9 @@ void launch_local(const BoxDesc* boxes, int m, int max_cells, int max_bx, const 
                   const int* dof_side, const int* dof_q, const int* dof_face0,
                   const double* face_w, double* mU, double* mP, hipStream_t s, int groups_cap) {
   const BoxLaunch l(m, max_bx, max_cells, sizeof(T), sizeof(S), groups_cap);
-  MRCM_BOX_DISPATCH(k_local, T, S, l.nb, l.grid, l.block, l.shm, s, boxes, m, l.gb, l.cp_words,
-                    dinv, coup, r, p, nx, dof_off, dof_side, dof_q, dof_face0, face_w, mU, mP);
+  MRCM_BOX_DISPATCH(k_local, T, S, l.nb, l.dense, l.grid, l.block, l.shm, s, boxes, m, l.gb,
+                    l.cp_words, dinv, coup, r, p, nx, dof_off, dof_side, dof_q, dof_face0,
+                    face_w, mU, mP);
 }
 
 void launch_coarse_rhs(const int4* gsrc, const double* gscale, const double* mU,
@@ -2792,8 +2896,8 @@ template <typename T, typename S>
 void launch_patch(const BoxDesc* boxes, int m, int max_cells, int max_bx, const S* dinv,
                   const S* coup, const T* rho, T* p, int nx, hipStream_t s, int groups_cap) {
   const BoxLaunch l(m, max_bx, max_cells, sizeof(T), sizeof(S), groups_cap);
-  MRCM_BOX_DISPATCH(k_patch, T, S, l.nb, l.grid, l.block, l.shm, s, boxes, m, l.gb, l.cp_words,
-                    dinv, coup, rho, p, nx);
+  MRCM_BOX_DISPATCH(k_patch, T, S, l.nb, l.dense, l.grid, l.block, l.shm, s, boxes, m, l.gb,
+                    l.cp_words, dinv, coup, rho, p, nx);
 }
 
 // ---- K right-hand sides per launch ----
@@ -2819,10 +2923,10 @@ struct BoxLaunchK {
   dim3 grid, block;
   size_t shm;
   BoxLaunchK(int k, int m, int max_bx, int max_cells, size_t t, size_t w) {
-    nb = launch_cols(m, max_bx, w);
+    nb = launch_cols(m, max_bx, w, pack20_columns(t, w));
     int groups = most_groups(nb, w, group_bytes_k(k, nb, max_cells, t, w));
-    if (nb == kPacked && groups <= 0) {
-      nb = 16;
+    if (nb % 2 == 1 && groups <= 0) {
+      --nb;
       groups = most_groups(nb, w, group_bytes_k(k, nb, max_cells, t, w));
     }
     if (groups <= 0) throw Error(MRCM_EINVAL, "boxes too large for a multi-RHS launch");
@@ -2840,14 +2944,19 @@ struct BoxLaunchK {
 // holds a whole row: eight columns spill 148 bytes and four in FP64 leave one wave per SIMD
 // (768 x 768 in 4-wide subdomains, four columns of T: 2342 us, two at a time 2260).
 constexpr int box_width_k(int nb, size_t w) {
-  if (nb == kPacked) return w == 8 ? 2 : 4;
+  if (nb % 2 == 1) return w == 8 ? 2 : 4;
   if (w == 8) return nb <= 16 ? 4 : nb <= 48 ? 2 : 1;
   return nb <= 16 ? 8 : nb <= 32 ? 4 : nb <= 48 ? 2 : 1;
 }
 
+inline int columns_width(int m, int max_bx, size_t t, size_t w) {
+  return box_width_k(launch_cols(m, max_bx, w, pack20_columns(t, w)), w);
+}
+
 #define MRCM_BOX_CASE_K(KERNEL, T, S, NB, K, ...)            \
   case 16 * NB + K:                                          \
-    if constexpr (K <= box_width_k(NB, sizeof(S)))           \
+    if constexpr (K <= box_width_k(NB, sizeof(S)) &&         \
+                  (NB != kPacked20 || pack20_columns(sizeof(T), sizeof(S)))) \
       launch_box(KERNEL<T, S, NB, K>, __VA_ARGS__);          \
     break;
 #define MRCM_BOX_DISPATCH_K(KERNEL, T, S, nb, kk, ...)       \
@@ -2856,8 +2965,10 @@ constexpr int box_width_k(int nb, size_t w) {
       MRCM_BOX_CASE_K(KERNEL, T, S, 16, 8, __VA_ARGS__)      \
       MRCM_BOX_CASE_K(KERNEL, T, S, 16, 4, __VA_ARGS__)      \
       MRCM_BOX_CASE_K(KERNEL, T, S, 16, 2, __VA_ARGS__)      \
-      MRCM_BOX_CASE_K(KERNEL, T, S, kPacked, 4, __VA_ARGS__) \
-      MRCM_BOX_CASE_K(KERNEL, T, S, kPacked, 2, __VA_ARGS__) \
+      MRCM_BOX_CASE_K(KERNEL, T, S, kPacked16, 4, __VA_ARGS__) \
+      MRCM_BOX_CASE_K(KERNEL, T, S, kPacked16, 2, __VA_ARGS__) \
+      MRCM_BOX_CASE_K(KERNEL, T, S, kPacked20, 4, __VA_ARGS__) \
+      MRCM_BOX_CASE_K(KERNEL, T, S, kPacked20, 2, __VA_ARGS__) \
       MRCM_BOX_CASE_K(KERNEL, T, S, 20, 4, __VA_ARGS__)      \
       MRCM_BOX_CASE_K(KERNEL, T, S, 20, 2, __VA_ARGS__)      \
       MRCM_BOX_CASE_K(KERNEL, T, S, 24, 4, __VA_ARGS__)      \
@@ -2890,7 +3001,7 @@ void launch_local_k(int k, const BoxDesc* boxes, int m, int max_cells, int max_b
                     const int* dof_face0, const double* face_w, double* mU, double* mP, int nc,
                     hipStream_t s) {
   check_k(k);
-  const int kk = std::min(k, box_width_k(launch_cols(m, max_bx, sizeof(S)), sizeof(S)));
+  const int kk = std::min(k, columns_width(m, max_bx, sizeof(T), sizeof(S)));
   for (int k0 = 0; k0 < k; k0 += kk) {
     double* u = mU + (long long)k0 * nc;
     double* v = mP + (long long)k0 * nc;
@@ -3010,7 +3121,7 @@ void launch_patch_k(int k, const BoxDesc* boxes, int m, int max_cells, int max_b
                     const S* coup, const T* const* rho, T* const* p, T* const* e, int nx,
                     hipStream_t s) {
   check_k(k);
-  const int kk = std::min(k, box_width_k(launch_cols(m, max_bx, sizeof(S)), sizeof(S)));
+  const int kk = std::min(k, columns_width(m, max_bx, sizeof(T), sizeof(S)));
   for (int k0 = 0; k0 < k; k0 += kk) {
     if (kk == 1) {
       launch_patch<T, S>(boxes, m, max_cells, max_bx, dinv, coup, rho[k0], p[k0], nx, s);
@@ -3143,13 +3254,13 @@ __device__ __forceinline__ Blk many_blk(const int* __restrict__ pre, int c) {
   return Blk{(int)blockIdx.x - pre[c], pre[c + 1] - pre[c]};
 }
 
-template <typename T, typename S, int NB>
-__global__ void MRCM_BOX_KERNEL(T, S, NB)
+template <typename T, typename S, int NB, bool DENSE>
+__global__ void MRCM_BOX_KERNEL(T, S, NB, DENSE)
     k_local_many(const ManyCol* __restrict__ cols, const int* __restrict__ pre, int ncol,
                  int group_bytes, int cp_words) {
   const int c = many_col(pre, ncol, blockIdx.x);
   const ManyCol& a = cols[c];
-  local_body<T, S, NB>(many_blk(pre, c), a.lbox, a.m, group_bytes, cp_words,
+  local_body<T, S, NB, DENSE>(many_blk(pre, c), a.lbox, a.m, group_bytes, cp_words,
                            static_cast<const S*>(a.ldinv), static_cast<const S*>(a.lcoup), a.r,
                            static_cast<T*>(a.p), a.nx, a.dof_off, a.dof_side, a.dof_q,
                            a.dof_face0, a.face_w, a.mU, a.mP);
@@ -3213,13 +3324,13 @@ __global__ void __launch_bounds__(kVecThreads)
                    a.nx, a.ny, a.r, static_cast<const T*>(a.p), static_cast<T*>(a.rho));
 }
 
-template <typename T, typename S, int NB>
-__global__ void MRCM_BOX_KERNEL(T, S, NB)
+template <typename T, typename S, int NB, bool DENSE>
+__global__ void MRCM_BOX_KERNEL(T, S, NB, DENSE)
     k_patch_many(const ManyCol* __restrict__ cols, const int* __restrict__ pre, int ncol,
                  int group_bytes, int cp_words) {
   const int c = many_col(pre, ncol, blockIdx.x);
   const ManyCol& a = cols[c];
-  patch_body<T, S, NB>(many_blk(pre, c), a.pbox, a.m, group_bytes, cp_words,
+  patch_body<T, S, NB, DENSE>(many_blk(pre, c), a.pbox, a.m, group_bytes, cp_words,
                            static_cast<const S*>(a.pdinv), static_cast<const S*>(a.pcoup),
                            static_cast<const T*>(a.rho), static_cast<T*>(a.p), a.nx);
 }
@@ -3278,7 +3389,7 @@ void launch_local_many(const ManyCol* cols, const int* pre, int ncol, int blocks
   if (blocks <= 0) return;
   const int gb = (int)group_bytes(g.cols, max_cells, sizeof(T), sizeof(S));
   const int cp_words = coupling_words(g.cols, max_cells, sizeof(S));
-  MRCM_BOX_DISPATCH(k_local_many, T, S, g.cols, dim3(blocks),
+  MRCM_MANY_DISPATCH(k_local_many, T, S, g.cols, g.dense, dim3(blocks),
                     dim3(g.groups * box_threads(g.cols, sizeof(S))), (size_t)g.groups * gb, s, cols,
                     pre, ncol, gb, cp_words);
 }
@@ -3330,7 +3441,7 @@ void launch_patch_many(const ManyCol* cols, const int* pre, int ncol, int blocks
   if (blocks <= 0) return;
   const int gb = (int)group_bytes(g.cols, max_cells, sizeof(T), sizeof(S));
   const int cp_words = coupling_words(g.cols, max_cells, sizeof(S));
-  MRCM_BOX_DISPATCH(k_patch_many, T, S, g.cols, dim3(blocks),
+  MRCM_MANY_DISPATCH(k_patch_many, T, S, g.cols, g.dense, dim3(blocks),
                     dim3(g.groups * box_threads(g.cols, sizeof(S))), (size_t)g.groups * gb, s, cols,
                     pre, ncol, gb, cp_words);
 }

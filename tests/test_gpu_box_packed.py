@@ -1,7 +1,8 @@
-"""Many narrow boxes: launches of more than 2048 waves of boxes up to 16 columns wide, which
-run several boxes to a wave.  Boxes of different heights and widths, down to a row or a
-column, share a wave; T of one, seven and eight columns and through a launch over several
-contexts is the same bit for bit, and the oracle's within the gates.
+"""Many boxes: launches of more than 2048 waves of boxes up to 16 columns wide, and of more
+than 3072 boxes up to 20 wide, run several boxes to a wave, and FP64 boxes of 37 to 48
+columns past 1024 waves run on kernels of their own.  Boxes of different heights and widths,
+down to a row or a column, share a wave; T of one, seven and eight columns and through a
+launch over several contexts is the same bit for bit, and the oracle's within the gates.
 """
 import numpy as np
 import pytest
@@ -24,6 +25,10 @@ SHAPES = [
     (205, 156, 4, 3, 0, 1, 1, (1, 2)),    # 2704, last column of boxes one wide
     (171, 165, 4, 3, 1, 2, 1, (1, 2)),    # 2365
     (130, 122, 5, 4, 1, 1, 1, (0, 1, 2)),  # 806: one column on its own waves, eight packed
+    (545, 190, 17, 2, 0, 1, 1, (0, 1)),    # 3135 boxes, patches 19 x 4, last column one wide
+    (576, 98, 18, 1, 0, 1, 1, (2,)),       # 3136, patches 20 x 3
+    (400, 104, 40, 2, 1, 1, 1, (0,)),      # 520 of 42 x 4: FP64 at two waves per SIMD
+    (360, 156, 36, 3, 1, 2, 1, (0,)),      # 520 of 38 x 5 and 40 x 7
 ]
 CASES = [(s, p) for s in SHAPES for p in s[-1]]
 
