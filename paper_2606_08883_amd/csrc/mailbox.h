@@ -30,11 +30,12 @@ namespace mrcm {
 // kAskEvery: with neither, the waits of 16 threads on 16 cores kept each other's
 // launches, and the runtime's threads, off the cores (64 x 64 solves, wall time per solve
 // over all threads: 0.60 to 1.3 ms, against 0.23 to 0.61 with copies and
-// synchronisations and 0.18 to 0.25 now; one thread 0.48, 0.77, 0.45).
+// synchronisations and 0.17 to 0.25 now; one thread 0.48, 0.77, 0.43 to 0.45; 64
+// looks instead of 256 cost a small 3-D solve 1%, 1060 and 1070 us).
 struct Mailbox {
   static constexpr int kPlaces = kMaxVecBlocks + 256;
   static constexpr uint64_t kUnset = 0x7ff4a5c3e1d2b697ull;
-    static constexpr unsigned kSpins = 64;
+  static constexpr unsigned kSpins = 256;
   static constexpr std::chrono::microseconds kAskEvery{1000};
   double* h = nullptr;  // the same address on the host and the device; owned
   int posted = 0;
