@@ -16,6 +16,13 @@ torch = pytest.importorskip("torch")
 # nx, ny, sx, sy, l, overlap: widest boxes
 SHAPES = [
     (37, 20, 18, 10, 0, 0),  # 18 columns beside a last subdomain of one
+] + [
+    # every column width class at its narrowest and widest, boxes of nine and five rows
+    (2 * w + 3, 14, w, 9, 0, 0) for w in (2, 16, 17, 20, 21, 24, 25, 32, 33, 36, 37, 40, 41, 48, 49,
+                                          64)
+] + [
+    (70, 42, 16, 13, 2, 2),  # oversampled boxes of 20 columns, patches of 20
+    (99, 84, 30, 26, 5, 3),  # 40 and 36
 ]
 
 
