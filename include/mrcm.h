@@ -207,12 +207,12 @@ int gmres_solve(mrcm_ctx* ctx, const double* b, double* p, int32_t nrhs, double 
 /* Batched GMRES over several contexts (Algorithm 1 for every right-hand
  * side of every member; continuous batching): right-hand sides of any
  * number of set-up contexts, added and removed at any time, advance together
- * in ticks.  A tick consumes the scalars fetched by the previous tick (norms
- * and Hessenberg columns), advances every right-hand side on the host as
- * gmres_solve does, runs the Arnoldi steps of all stepping right-hand sides
+ * in ticks.  A tick waits for the scalars of the previous tick (norms
+ * and Hessenberg columns, which the kernels store in pinned host memory),
+ * advances every right-hand side on the host as
+ * gmres_solve does, and runs the Arnoldi steps of all stepping right-hand sides
  * as one launch per phase of T and of the Arnoldi tail over all of them (as
- * mrcm_apply_many), and copies the scalars the host needs next in one
- * transfer.  Each right-hand side runs gmres_solve's kernels in the same
+ * mrcm_apply_many).  Each right-hand side runs gmres_solve's kernels in the same
  * order, so its iterates equal gmres_solve's bit for bit (p_0 = 0, modified
  * Gram-Schmidt, the estimated residual tested after every step, the true
  * FP64 residual at every cycle end).  The batch has its own stream; calls

@@ -227,14 +227,14 @@ void launch_mgs_step_many(const ManyCol* cols, const int* pre, int ncol, int blo
 void launch_norm_scale_many(const ManyCol* cols, const int* pre, int ncol, int blocks,
                             hipStream_t s);
 
-// ---- set-up on the device (FP64; one wave per box or subdomain) ------------
-// Factor the boxes of `jobs` (LDS: two maxn x maxn blocks); status[0] = 1
-// after a non-positive pivot.
+// ---- set-up on the device (FP64) --------------------------------------------
+// Factor the boxes of `jobs`, one wave per end of a factor (LDS: a maxn x maxn block and
+// four vectors per end); status[0] = 1 after a non-positive pivot.
 template <typename S>
 void launch_factor_boxes(const FactorJob* jobs, int njobs, int maxn, const double* K,
                          const double* tx, const double* ty, int nx, int ny, double aL, S* dS,
                          S* cS, double* d64, double* c64, int* status, hipStream_t s);
-// Oversampled problems of every subdomain, their restrictions to Omega_i
+// Oversampled problems of every subdomain, one wave each, their restrictions to Omega_i
 // (the MBFs, storage type) and the moments of their traces on Gamma_i (buf:
 // FP64 work buffer that the SubJob offsets index; over0: no oversampling).
 template <typename S>

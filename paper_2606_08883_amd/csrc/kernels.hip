@@ -2723,8 +2723,9 @@ BoxGrid box_grid(long long m, int max_bx, int max_cells, size_t t, size_t w, boo
     if (groups > 0) return BoxGrid{nb, groups, 64 / box_threads(nb, w), false};
     --nb;  // tall boxes: not a wave's worth of them in LDS
   }
-  // few boxes get a workgroup each, so that they spread over the CUs (up to four waves
-  // per CU)
+  // up to 256 threads per CU a box is a workgroup, so that they spread over the CUs (T, packed
+  // into workgroups of four waves and spread: 512 x 512, 40-wide boxes in FP64 124, 105 us, 256
+  // boxes 20 wide 63, 60; 1024 of them, FP32 storage, 93 both ways; 2500 of 32 in FP64 231, 240)
   if (!many && m * box_threads(nb, w) <= 4LL * 64 * 256) return BoxGrid{nb, 1, 1, dense};
   const size_t bytes = group_bytes(nb, max_cells, t, w);
   int groups = most_groups(nb, w, bytes);
@@ -2938,10 +2939,11 @@ struct BoxLaunchK {
 };
 }  // namespace
 
-// Right-hand sides one box launch takes at most, by column width: what the
-// lane's registers hold without spilling (quads in flight, four partial sums
-// and the rows of every column); 1 = the one-RHS kernels, once per column.  Packed, a lane
-// holds a whole row: eight columns spill 148 bytes and four in FP64 leave one wave per SIMD
+// Right-hand sides one box launch takes at most, by column width; 1 = the one-RHS kernels,
+// once per column.  The bounds of unpacked boxes are what the registers of a lane that owns a
+// whole row hold without spilling; with two lanes to a row FP64 boxes of 20 to 32 columns would
+// hold four (212 to 256 registers), which has not been timed.  Packed, a lane holds a whole
+// row: eight columns spill 148 bytes and four in FP64 leave one wave per SIMD
 // (768 x 768 in 4-wide subdomains, four columns of T: 2342 us, two at a time 2260).
 constexpr int box_width_k(int nb, size_t w) {
   if (nb % 2 == 1) return w == 8 ? 2 : 4;
